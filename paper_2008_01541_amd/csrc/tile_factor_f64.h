@@ -11,19 +11,7 @@ namespace pdk {
 
 constexpr int LDS_LD = NB + 4;   // padded LDS row (doubles)
 
-// DPP row broadcast (row_newbcast: every lane of a row of 16 lanes reads lane
-// S of that row), as volatile asm; s_nop 1 covers the two wait states a DPP
-// read needs after a VALU write of its source.
-template <int S>
-__device__ __forceinline__ double row_bcast(double v) {
-  double o;
-  asm volatile("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf"
-               : "=v"(o)
-               : "v"(v), "i"(S));
-  return o;
-}
-// Per-step update blocks of the 16 x 16 diagonal-block Cholesky:
-// chol16_a_updates<C>(a) -> next pivot, chol16_x_updates<C>(a, x).
+// chol16_eliminate(a, x): the scheduled elimination of a 16 x 16 block.
 #include "chol16_steps.inc"
 
 // 1/sqrt(d): the hardware estimate (relative error up to about 5e-8 on this
@@ -36,72 +24,90 @@ __device__ __forceinline__ double rsqrt_newton(double d) {
   return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// Right-looking elimination of one 16 x 16 block, one pivot per step C: lane
-// r (mod 16) holds row r of the block in a[] and column r of the inverse in
-// x[] (initially the identity); the multipliers L(S, C) are broadcast along
-// each row of 16 lanes (one asm block of DPP operands per step and array).
-// The pivot of step C + 1 is broadcast as soon as its own update is done, so
-// that its square root can overlap the rest of step C.
-template <int C>
-__device__ __forceinline__ void chol16_step(double (&a)[16], double (&x)[16], double d, int r,
-                                            int& bad) {
-  if constexpr (C < 16) {
-    const bool ok = d > 0.0;
-    bad = (!ok && bad == 0) ? C + 1 : bad;
-    const double y = ok ? rsqrt_newton(d) : 1.0;
-    // column C of L, d y on the diagonal and a y below; the lanes above the
-    // diagonal (r < C) only carry values of the upper part, which no later
-    // step reads into the lower part, and are cleared after the last step
-    a[C] *= y;
-    x[C] *= y;
-    double dn = 0.0;
-    if constexpr (C + 1 < 16) {
-      dn = chol16_a_updates<C>(a);
-      chol16_x_updates<C>(a, x);
-    }
-    chol16_step<C + 1>(a, x, dn, r, bad);
-  }
+// One block column of the tile factor, by one wave: the 16 x 16 diagonal block
+// at (b0, b0), b0 = 16 KB, is factored and 64 further rows are solved against
+// it, one per lane of the four rows of 16 lanes:
+//   lanes 0-15            the rows of dinv, which hold the identity and become
+//                         the block's inverse;
+//   the next 3 - KB rows  the panel blocks below (rows b0 + lane), which become
+//                         P L_kk^-T;
+//   the last KB rows      the columns of the staged -Y_kj, j < KB, which become
+//                         X_kj = -L_kk^-1 Y_kj.
+// All rows of 16 lanes hold the block itself (lane r row r), since the
+// multipliers are broadcast within a row of 16 lanes; the riding rows use the
+// issue slots that the block's own pivot chain leaves.  Instruction issue
+// bounds it (386 FP64 instructions of 4 cycles and 16 square roots of 16; the
+// chain of square root, scaling, update and broadcast is 92 cycles a pivot):
+// 1,950 cycles measured for the elimination, 2,700 with the loads and stores
+// (3,580 before the steps were scheduled across pivots, and the panel below
+// and the inverse's off-diagonal blocks then took products of their own).
+// dinv: rows of the block's inverse (dinv[c][b0 + r] = inverse(r, c)).
+__device__ __forceinline__ double* chol16_row(double (*T)[LDS_LD], double (*X)[LDS_LD], int kb,
+                                              double (*dinv)[LDS_LD], int& ld) {
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, b0 = 16 * kb;
+  const bool panel = g >= 1 && g <= 3 - kb;
+  const int col = 16 * (g - 4 + kb) + r;           // column of the inverse, g > 3 - kb
+  ld = panel ? LDS_LD : 1;
+  return g == 0 ? &dinv[r][b0] : (panel ? &T[b0][b0 + lane] : &X[col][b0]);
 }
 
-// Cholesky factor and inverse of the 16 x 16 diagonal block at (b0, b0) of the
-// LDS tile T, by one wave (the four rows of 16 lanes work redundantly), into
-// registers: lane r (mod 16) ends with row r of L in a[] (zeros above the
-// diagonal) and column r of its inverse in x[].  The first non-positive pivot
-// j of the block (inside the first mr rows) is reported in *info as
-// gbase + b0 + j + 1, and its reciprocal square root is taken as 1.
-__device__ __forceinline__ void chol16_factor(double (*T)[LDS_LD], int b0, int mr, int gbase,
-                                              int* info, double (&a)[16], double (&x)[16]) {
-  const int lane = threadIdx.x & 63, r = lane & 15;
-#pragma unroll
+// The same elimination step by step in LDS, for a block with a pivot that is
+// not positive (never on the path of a positive definite matrix): the pivot's
+// reciprocal square root is taken as 1 and the first one, if inside the first
+// mr rows, is reported in *info as gbase + its index + 1.
+__device__ __forceinline__ void chol16_bad_block(double (*T)[LDS_LD], double (*X)[LDS_LD], int kb,
+                                                 double (*dinv)[LDS_LD], int mr, int gbase,
+                                                 int* info) {
+  const int lane = threadIdx.x & 63, r = lane & 15, b0 = 16 * kb;
+  int ld, bad = 0;
+  double* p = chol16_row(T, X, kb, dinv, ld);
+#pragma unroll 1
   for (int c = 0; c < 16; ++c) {
-    a[c] = T[b0 + c][b0 + r];
-    x[c] = (c == r) ? 1.0 : 0.0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const double d = T[b0 + c][b0 + c];
+    const bool ok = d > 0.0;
+    if (!ok && bad == 0) bad = c + 1;
+    const double y = ok ? rsqrt_newton(d) : 1.0;
+    __builtin_amdgcn_wave_barrier();
+    if (lane < 16) T[b0 + c][b0 + r] *= y;
+    p[c * ld] *= y;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+    for (int s = c + 1; s < 16; ++s) {
+      const double l = T[b0 + c][b0 + s];
+      if (lane < 16) T[b0 + s][b0 + r] -= l * T[b0 + c][b0 + r];
+      p[s * ld] -= l * p[c * ld];
+    }
+    __builtin_amdgcn_wave_barrier();
   }
-  int bad = 0;          // first non-positive pivot of the block, 1-based; 0: none
-  chol16_step<0>(a, x, row_bcast<0>(a[0]), r, bad);
   if (lane == 0 && bad > 0 && b0 + bad - 1 < mr) atomicCAS(info, 0, gbase + b0 + bad);
-#pragma unroll
-  for (int c = 0; c < 16; ++c) a[c] = (r >= c) ? a[c] : 0.0;
 }
 
-// L replaces the lower part of the block (zeros above), its inverse goes to
-// the same block of X (zeros above).
-__device__ __forceinline__ void chol16_store(double (*T)[LDS_LD], double (*X)[LDS_LD], int b0,
-                                             const double (&a)[16], const double (&x)[16]) {
-  const int lane = threadIdx.x & 63, r = lane & 15;
+__device__ __forceinline__ void chol16_block(double (*T)[LDS_LD], double (*X)[LDS_LD], int kb,
+                                             double (*dinv)[LDS_LD], int mr, int gbase,
+                                             int* info) {
+  const int lane = threadIdx.x & 63, r = lane & 15, b0 = 16 * kb;
+  int ld;
+  double* p = chol16_row(T, X, kb, dinv, ld);
+  double a[16], x[16];
+#pragma unroll
+  for (int c = 0; c < 16; ++c) a[c] = T[b0 + c][b0 + r];
+#pragma unroll
+  for (int c = 0; c < 16; ++c) x[c] = p[c * ld];
+  const double last = chol16_eliminate(a, x);
+  // a pivot that is not positive makes every later one a NaN
+  if (!(__builtin_amdgcn_readfirstlane((int)(last > 0.0)))) {
+    chol16_bad_block(T, X, kb, dinv, mr, gbase, info);
+    return;
+  }
+  // (above its diagonal the block keeps values that nothing reads)
   if (lane < 16) {
 #pragma unroll
     for (int c = 0; c < 16; ++c) T[b0 + c][b0 + r] = a[c];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) X[b0 + r][b0 + i] = x[i];
   }
-}
-
-__device__ __forceinline__ void chol16_inverse(double (*T)[LDS_LD], double (*X)[LDS_LD], int b0,
-                                               int mr, int gbase, int* info) {
-  double a[16], x[16];
-  chol16_factor(T, b0, mr, gbase, info, a, x);
-  chol16_store(T, X, b0, a, x);
+#pragma unroll
+  for (int c = 0; c < 16; ++c) p[c * ld] = x[c];
 }
 
 // C(m, n) += sum_k A(m, k) B(n, k) over one 16-deep block, m, n, k < 16, for
@@ -124,29 +130,34 @@ __device__ inline void mma16(double4_t& acc, double (*As)[LDS_LD], int am, int a
 // Cholesky of a 64 x 64 tile held in LDS (T[c][r] = tile(r, c), lower part
 // valid, rows/cols >= mr padded with the identity) and the inverse of the
 // factor into X (X[c][r] = inverse(r, c), zero above the diagonal).  Right-
-// looking over 16-wide block columns: wave 0 factors and inverts the diagonal
-// block, the panel below becomes P Dinv^T and the trailing blocks are updated
-// on the matrix cores.  The off-diagonal blocks of the inverse follow from
-// X_ij = -X_ii Y_ij, Y_ij = sum_{p=j}^{i-1} L_ip X_pj; wave 1 + j owns block
-// column j of the inverse and does that work while wave 0 factors the next
-// diagonal block (the staged Y_ij waits in the X_ij slot until X_ii exists),
-// so only the last block row is left after the final diagonal block.  A
-// non-positive pivot stores its 1-based global index gbase + j + 1 in *info
-// (first one wins) and its reciprocal square root is taken as 1 so that the
-// factorization stays finite.  Only the lower triangle of T is meaningful on return.
+// looking over 16-wide block columns.  In step kb wave 0 factors the diagonal
+// block together with its inverse, the panel blocks below it and the finished
+// part of the inverse's block row kb (chol16_block); then the four waves form,
+// one block each on the matrix cores, what the next step reads: the trailing
+// blocks (i, kb + 1) and the staged blocks -Y_{kb+1,j} -= L_{kb+1,kb} X_kj,
+// j <= kb (-Y_ij, Y_ij = sum_{p=j}^{i-1} L_ip X_pj, waits in the X_ij slot).  The
+// blocks that later steps read are updated by waves 1-3 while wave 0 is in
+// its next step.  6.1 us per tile, 6.9 us with the update by B below (8.7 and
+// 9.3 us when the panels and the inverse's rows were products between the
+// blocks).  A non-positive pivot stores its 1-based global index
+// gbase + j + 1 in *info (first one wins) and its reciprocal square root is
+// taken as 1 so that the factorization stays finite.  Only the lower triangle
+// of T is meaningful on return.
 //
 // With lflag != NULL, X enters holding a 64 x 64 tile B (X[k][r] = B(r, k))
-// and the tile factored is T - B B^T: wave 0 subtracts B B^T from the first
-// diagonal block and factors it at once, while waves 1-3 update the nine other
-// lower blocks; once B has been read by every wave, *lflag = epoch is
-// published (after this workgroup's earlier global stores have drained) and X
-// is reused for the inverse.  The last rank-64 update of a diagonal tile thus
-// overlaps the factorization of its first block.
+// and the tile factored is T - B B^T: the waves subtract B B^T from the first
+// block column, one block each, and while wave 0 factors it waves 1-3 update
+// the six other lower blocks; once B has been read by every wave,
+// *lflag = epoch is published (after this workgroup's earlier global stores
+// have drained) and X is reused for the inverse.
 __device__ __forceinline__ void factor_tile_blocked(double (*T)[LDS_LD], double (*X)[LDS_LD], int mr, int gbase,
                                     int* info, int* lflag = nullptr, int epoch = 0) {
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  // zero the six strictly upper 16 x 16 blocks of X: X[16 jb + c][16 ib + r], ib < jb
-  const auto zero_upper_x = [&]() {
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  // zero the six strictly upper 16 x 16 blocks of X, X[16 jb + c][16 ib + r],
+  // ib < jb, and put the identity into the diagonal blocks from kb0 on
+  const auto clear_x = [&](int kb0) {
+    for (int kb = kb0; kb < 4; ++kb)
+      X[16 * kb + (t >> 4)][16 * kb + (t & 15)] = (t >> 4) == (t & 15) ? 1.0 : 0.0;
     for (int e = t; e < 6 * 256; e += 256) {
       const int blk = e >> 8, r = e & 15, c = (e >> 4) & 15;
       const int ib = blk < 3 ? 0 : (blk < 5 ? 1 : 2);
@@ -154,97 +165,85 @@ __device__ __forceinline__ void factor_tile_blocked(double (*T)[LDS_LD], double 
       X[16 * jb + c][16 * ib + r] = 0.0;
     }
   };
-  // Y_ij into the X_ij slot / X_ij = -X_ii Y_ij in place (one wave each)
-  const auto inv_stage = [&](int i, int j) {
-    double4_t acc = {0.0, 0.0, 0.0, 0.0};
-    for (int p = j; p < i; ++p) mma16<true>(acc, T, 16 * i, 16 * p, X, 16 * j, 16 * p);
+  // block (i, j) of D, D[16 j + c][16 i + r], minus the product acc
+  const auto subtract = [&](double (*D)[LDS_LD], int i, int j, auto product) {
+    double v[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) X[16 * j + (lane >> 4) + 4 * q][16 * i + (lane & 15)] = acc[q];
-  };
-  const auto inv_finish = [&](int i, int j) {
+    for (int q = 0; q < 4; ++q) v[q] = D[16 * j + (lane >> 4) + 4 * q][16 * i + (lane & 15)];
     double4_t acc = {0.0, 0.0, 0.0, 0.0};
-    mma16<true>(acc, X, 16 * i, 16 * i, X, 16 * j, 16 * i);
-    __builtin_amdgcn_wave_barrier();      // all lanes have read Y before X_ij overwrites it
+    product(acc);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) X[16 * j + (lane >> 4) + 4 * q][16 * i + (lane & 15)] = -acc[q];
+    for (int q = 0; q < 4; ++q)
+      D[16 * j + (lane >> 4) + 4 * q][16 * i + (lane & 15)] = v[q] - acc[q];
   };
-  if (lflag) {
-    // T block (ib, jb) -= sum_{k < 64} B(16 ib + m, k) B(16 jb + n, k)
-    const auto b_update = [&](int ib, int jb) {
+  // T block (i, j) -= L_ik L_jk^T
+  const auto trail = [&](int i, int j, int k) {
+    subtract(T, i, j, [&](double4_t& acc) { mma16<false>(acc, T, 16 * i, 16 * k, T, 16 * j, 16 * k); });
+  };
+  // -Y_ij -= L_ik X_kj for j < k, and -Y_ik = -L_ik X_kk (X_kk read from dinv)
+  const auto stage = [&](int i, int j, int k, double (*dinv)[LDS_LD]) {
+    if (j < k) {
+      subtract(X, i, j, [&](double4_t& acc) { mma16<true>(acc, T, 16 * i, 16 * k, X, 16 * j, 16 * k); });
+    } else {
       double4_t acc = {0.0, 0.0, 0.0, 0.0};
+      mma16<true>(acc, T, 16 * i, 16 * k, dinv, 0, 16 * k);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) X[16 * j + (lane >> 4) + 4 * q][16 * i + (lane & 15)] = -acc[q];
+    }
+  };
+  // what step kb + 1 reads, one block per wave
+  const auto next_column = [&](int kb, double (*dinv)[LDS_LD]) {
+    if (w < 3 - kb) trail(kb + 1 + w, kb + 1, kb);
+    else stage(kb + 1, w - (3 - kb), kb, dinv);
+  };
+  // T block (ib, jb) -= sum_{k < 64} B(16 ib + m, k) B(16 jb + n, k)
+  const auto b_update = [&](int ib, int jb) {
+    subtract(T, ib, jb, [&](double4_t& acc) {
 #pragma unroll
       for (int s = 0; s < 4; ++s) mma16<false>(acc, X, 16 * ib, 16 * s, X, 16 * jb, 16 * s);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) T[16 * jb + (lane >> 4) + 4 * q][16 * ib + (lane & 15)] -= acc[q];
-    };
-    if (w == 0) {
-      b_update(0, 0);
-      // the block just written by other lanes of this wave is read below
-      __builtin_amdgcn_wave_barrier();
-      double a[16], x[16];
-      chol16_factor(T, 0, mr, gbase, info, a, x);
-      // L_00 in place; its inverse waits in the unused upper block (0, 1) of
-      // T, in the layout of X (T[16 + c][r] = inverse(r, c)), until B has
-      // been read
-      chol16_store(T, T + 16, 0, a, x);
-    } else {
-      // lower blocks of block rows 1..3 in row order, three per wave:
-      // (1,0) (1,1) (2,0) | (2,1) (2,2) (3,0) | (3,1) (3,2) (3,3)
-      for (int u = 0; u < 3; ++u) {
-        const int idx = 3 * (w - 1) + u;
-        const int ib = idx < 2 ? 1 : (idx < 5 ? 2 : 3);
-        const int jb = idx - (ib == 1 ? 0 : (ib == 2 ? 2 : 5));
-        b_update(ib, jb);
-      }
-    }
-    publish_flag(lflag, epoch);           // B read by every wave: X is free
-    zero_upper_x();
-    X[t >> 4][t & 15] = T[16 + (t >> 4)][t & 15];   // X_00 (256 threads, one element each)
+    });
+  };
+  // while X holds B, the first inverse block takes the unused upper block
+  // (0, 1) of T, in the layout of X (T[16 + c][r] = inverse(r, c))
+  double (*dinv)[LDS_LD] = lflag ? T + 16 : X;
+  if (lflag) {
+    T[16 + (t >> 4)][t & 15] = (t >> 4) == (t & 15) ? 1.0 : 0.0;
+    b_update(w, 0);
   } else {
-    zero_upper_x();
-    if (w == 0) chol16_inverse(T, X, 0, mr, gbase, info);
+    clear_x(0);
   }
   __syncthreads();
-  for (int kb = 0; kb < 3; ++kb) {
-    const int b0 = 16 * kb;
-    // panel: block row ib = kb + 1 + w becomes P Dinv^T
-    if (kb + 1 + w <= 3) {
-      const int ib = kb + 1 + w;
-      double4_t acc = {0.0, 0.0, 0.0, 0.0};
-      mma16<false>(acc, T, 16 * ib, b0, X, b0, b0);
+  // unrolled: with kb a run-time value the block addresses cost 1 us per tile,
+  // more than the fetch of the longer code when it is not cached
 #pragma unroll
-      for (int q = 0; q < 4; ++q) T[b0 + (lane >> 4) + 4 * q][16 * ib + (lane & 15)] = acc[q];
-    }
-    __syncthreads();
-    // trailing blocks (ib, jb), kb < jb <= ib <= 3; wave 0 takes the next
-    // diagonal block and goes straight on to factor it
-    const int R = 3 - kb, nblk = R * (R + 1) / 2;
-    for (int bi = (w == 0 ? 0 : w); bi < nblk; bi += (w == 0 ? nblk : 3)) {
-      int jb = kb + 1, rem = bi;
-      while (rem >= 4 - jb) { rem -= 4 - jb; ++jb; }
-      const int ib = jb + rem;
-      double4_t acc = {0.0, 0.0, 0.0, 0.0};
-      mma16<false>(acc, T, 16 * ib, b0, T, 16 * jb, b0);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) T[16 * jb + (lane >> 4) + 4 * q][16 * ib + (lane & 15)] -= acc[q];
-    }
+  for (int kb = 0; kb < 4; ++kb) {
     if (w == 0) {
-      chol16_inverse(T, X, b0 + 16, mr, gbase, info);
-    } else {
-      // meanwhile, block column j = w - 1 of the inverse: finish row kb,
-      // stage row kb + 1 (the panels up to kb and X_kk are final)
-      const int j = w - 1;
-      if (j < kb) inv_finish(kb, j);
-      // X_{kb,j} just written by other lanes of this wave is read below: the
-      // wave barrier keeps the compiler from moving loads across those stores
-      __builtin_amdgcn_wave_barrier();
-      if (j <= kb) inv_stage(kb + 1, j);
+      chol16_block(T, X, kb, dinv, mr, gbase, info);
+    } else if (kb == 0) {
+      if (lflag) {
+        // (1,1) (2,1) | (3,1) (2,2) | (3,2) (3,3)
+        for (int u = 0; u < 2; ++u)
+          b_update(u == 0 ? (w == 1 ? 1 : 3) : (w == 3 ? 3 : 2), u == 0 ? (w == 3 ? 2 : 1) : w);
+      }
+    } else if (kb == 1) {
+      trail(w < 3 ? 1 + w : 3, w < 3 ? 2 : 3, 0);
+      if (w < 3) stage(1 + w, 0, 0, X);
+    } else if (kb == 2) {
+      if (w == 1) trail(3, 3, 1);
+      else stage(3, w - 2, 1, X + 16);
     }
+    if (kb == 0 && lflag) {
+      publish_flag(lflag, epoch);           // B read by every wave: X is free
+      clear_x(1);
+      X[t >> 4][t & 15] = T[16 + (t >> 4)][t & 15];   // X_00 (256 threads, one element each)
+    } else {
+      __syncthreads();
+    }
+    if (kb == 3) break;
+    next_column(kb, dinv);
     __syncthreads();
+    dinv = X + 16 * (kb + 1);
   }
-  // last block row of the inverse: X_3j = -X_33 Y_3j
-  if (w >= 1) inv_finish(3, w - 1);
-  __syncthreads();
 }
 
 // Compute-unit courtesy.  The diagonal tasks form the critical path of the
