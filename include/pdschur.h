@@ -344,7 +344,7 @@ pd_status pd_chol_destroy(pd_chol *h);
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * factorization of pd_chol_factor without a handle.  Its workspace is a
  * static device array of the library sized for n <= PD_CHOL_NOALLOC_MAX_N
- * (about 8.1 MB), one copy per GPU, held until the process ends and shared by
+ * (about 12.7 MB), one copy per GPU, held until the process ends and shared by
  * every call on that GPU: calls that overlap on one GPU (e.g. on two streams)
  * race and must be serialized by the caller.  The first call on a GPU also
  * enqueues a fill that zeroes the array's flags.  Enqueued on hip_stream
@@ -361,10 +361,12 @@ pd_status pd_chol_factor_noalloc(double *A, int64_t lda, int64_t n, int32_t n_wo
  * its index ranges on the host (no GPU work; the kernels decode their
  * tickets with the same code).  For order n (tiles of 64, nt = ceil(n/64)),
  * rhs = 1 when the three right-hand sides ride along as an extra tile row:
- * *ntask receives the number of tasks, and for 0 <= q < *ntask the tile
- * (*i, *j) of ticket q (*i == nt: the right-hand-side row) and *kend, the
- * number of 64-column steps the task accumulates.  n < 1, rhs not 0/1, or q
- * outside [0, *ntask) (q < 0 only queries the count) -> PD_ERR_INVALID. */
+ * *ntask receives the number of tiles, and for 0 <= q < *ntask the q-th tile
+ * (*i, *j) in the order in which tickets are given out (*i == nt: the
+ * right-hand-side row; a ticket of two tiles gives two consecutive entries),
+ * and *kend, the number of 64-column steps summed for the tile before its own
+ * last step.  n < 1, rhs not 0/1, or q outside [0, *ntask) (q < 0 only queries
+ * the count) -> PD_ERR_INVALID. */
 pd_status pd_dataflow_task(int64_t n, int32_t rhs, int64_t q, int32_t *i, int32_t *j,
                            int32_t *kend, int64_t *ntask);
 

@@ -468,7 +468,7 @@ pd_status build_impl(pd_ctx* c, const pd_mesh* M) {
   c->ntm = (int)((m + NB - 1) / NB);
   const int64_t ntmax = (std::max<int64_t>(c->maxw, m) + NB - 1) / NB;
   CK(c->alloc(&c->d_linv, ntmax * NB * NB));
-  CK(c->alloc(&c->d_sbuf, ntmax * NB * NB));
+  CK(c->alloc(&c->d_sbuf, 2 * ntmax * NB * NB));
   CK(c->alloc(&c->d_info, 1));
   CK(c->alloc(&c->d_err, 1));
   CK(c->alloc(&c->d_ticket, 4));
@@ -476,7 +476,7 @@ pd_status build_impl(pd_ctx* c, const pd_mesh* M) {
   HIPCK(c, hipMemsetAsync(c->d_err, 0, sizeof(int), c->st));
   HIPCK(c, hipMemsetAsync(c->d_ticket, 0, 4 * sizeof(unsigned long long), c->st));
   {
-    const int64_t nt2 = ntmax * (ntmax + 2);
+    const int64_t nt2 = ntmax * (ntmax + 3);
     CK(c->alloc(&c->d_tflags, nt2));
     CK(c->alloc(&c->d_tticket, 4));
     CK(c->alloc(&c->d_cumarks, potrf_cu_slots()));

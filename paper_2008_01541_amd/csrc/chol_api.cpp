@@ -15,8 +15,8 @@ struct pd_chol {
   int64_t n_max = 0;
   int n_wg = 512;
   double* linv = nullptr;      // tile inverses, nt x 64 x 64
-  double* sbuf = nullptr;      // partial sums of the first sub-diagonal tiles, nt x 64 x 64
-  int* flags = nullptr;        // (nt + 2) x nt ready flags (launch epochs)
+  double* sbuf = nullptr;      // partial sums of the tiles left of the diagonal, 2 nt x 64 x 64
+  int* flags = nullptr;        // (nt + 3) x nt ready flags (launch epochs)
   unsigned* ticket = nullptr;  // task ticket and launch epoch
   int* info = nullptr;
   int* err = nullptr;
@@ -36,8 +36,8 @@ struct pd_chol {
 constexpr int64_t NA_NT = (PD_CHOL_NOALLOC_MAX_N + NB - 1) / NB;
 constexpr int64_t NA_LINV = 0;                               // doubles
 constexpr int64_t NA_SBUF = NA_LINV + NA_NT * NB * NB;       // doubles
-constexpr int64_t NA_INTS = NA_SBUF + NA_NT * NB * NB;       // doubles: start of the int area
-constexpr int64_t NA_FLAGS_N = (NA_NT + 2) * NA_NT;
+constexpr int64_t NA_INTS = NA_SBUF + 2 * NA_NT * NB * NB;       // doubles: start of the int area
+constexpr int64_t NA_FLAGS_N = (NA_NT + 3) * NA_NT;
 constexpr int64_t NA_MARKS_N = 2048;
 constexpr int64_t NA_INT_N = NA_FLAGS_N + 4 + 1 + 1 + NA_MARKS_N;
 constexpr int64_t NA_DOUBLES = NA_INTS + (NA_INT_N + 1) / 2;
@@ -89,8 +89,8 @@ pd_status pd_chol_create(int64_t n_max, void* stream, pd_chol** out) {
     h->n_wg = 2 * ncu;
   const int nmarks = potrf_cu_slots();
   bool ok = hipMalloc(&h->linv, nt * NB * NB * sizeof(double)) == hipSuccess &&
-            hipMalloc(&h->sbuf, nt * NB * NB * sizeof(double)) == hipSuccess &&
-            hipMalloc(&h->flags, (nt + 2) * nt * sizeof(int)) == hipSuccess &&
+            hipMalloc(&h->sbuf, 2 * nt * NB * NB * sizeof(double)) == hipSuccess &&
+            hipMalloc(&h->flags, (nt + 3) * nt * sizeof(int)) == hipSuccess &&
             hipMalloc(&h->ticket, 4 * sizeof(unsigned)) == hipSuccess &&
             hipMalloc(&h->info, sizeof(int)) == hipSuccess &&
             hipMalloc(&h->err, sizeof(int)) == hipSuccess &&
@@ -99,7 +99,7 @@ pd_status pd_chol_create(int64_t n_max, void* stream, pd_chol** out) {
     delete h;
     return PD_ERR_OOM;
   }
-  ok = hipMemsetAsync(h->flags, 0, (nt + 2) * nt * sizeof(int), h->st) == hipSuccess &&
+  ok = hipMemsetAsync(h->flags, 0, (nt + 3) * nt * sizeof(int), h->st) == hipSuccess &&
        hipMemsetAsync(h->ticket, 0, 4 * sizeof(unsigned), h->st) == hipSuccess &&
        hipMemsetAsync(h->marks, 0, nmarks * sizeof(int), h->st) == hipSuccess &&
        hipStreamSynchronize(h->st) == hipSuccess;
@@ -198,7 +198,7 @@ pd_status pd_dataflow_task(int64_t n, int32_t rhs, int64_t q, int32_t* i, int32_
   if (q < 0) return PD_OK;
   if (q >= *ntask || !i || !j || !kend) return PD_ERR_INVALID;
   int ti, tj;
-  df_task_of_ticket((int)q, nt, rhs, ti, tj);
+  df64_tile(q, nt, df64_wide(nt), rhs, ti, tj);
   *i = ti;
   *j = tj;
   *kend = df_task_kend(ti, tj);

@@ -69,7 +69,7 @@ struct pd_ctx {
   double* d_S = nullptr;
   double* d_H = nullptr;
   double* d_linv = nullptr;
-  double* d_sbuf = nullptr;           // partial sums of the first sub-diagonal tiles (factor)
+  double* d_sbuf = nullptr;           // partial sums of the tiles left of the diagonal (factor)
   double* d_y = nullptr;               // scratch of the residual products
   double* d_ys = nullptr;              // forward-solve result (holds the sentinel between solves)
   double* d_Yt = nullptr;             // 64 x m right-hand-side tile row of the fused solve

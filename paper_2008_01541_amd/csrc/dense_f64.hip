@@ -17,6 +17,7 @@ constexpr int KC = 16;           // K-chunk staged through LDS per step
 struct Acc {                     // one wave's 32 x 32 share of a 64 x 64 tile
   double4_t c[2][2];
 };
+typedef double double2_t __attribute__((ext_vector_type(2)));
 
 __device__ inline void acc_zero(Acc& a) {
 #pragma unroll
@@ -135,99 +136,203 @@ __global__ void k_reset_counter(unsigned* ctr) {
   ctr[1] = ctr[1] + 1u;
 }
 
-// acc += sum_{k<kend} L_ik L_jk^T, one 64-deep k-step at a time.  The two
-// operand tiles of step k+1 are loaded into registers while the products of
-// step k run from LDS, and the ready flags of step k+2 are read while step
-// k+1 is loaded, so neither the flag round trip nor the operand latency sits
-// on the path when the producers are ahead.
-__device__ bool df_accumulate(Acc& acc, double (*As)[LDS_LD], double (*Bs)[LDS_LD],
-                              const double* __restrict__ Ar, int ldar, int r0, int mr,
-                              const double* __restrict__ A, int lda, int c0,
-                              int mc, int i, int j, int kend, int nt, const int* flags, int epoch,
-                              int* err, int* s_ok, const int* mark) {
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int wr = w >> 1, wc = w & 1;
-  const int r = t & 63;
-  const int kq = __builtin_amdgcn_readfirstlane(t >> 6);   // the wave index, uniform: addresses stay scalar
-  if (kend == 0) return true;
-  double ra[16], rb[16];
-  auto load_tile = [&](int k) {
+// Paired layout of a wave's 32 x 32 share of a tile: accumulator element
+// (mb, nb, q) of a lane is the tile's (pair_row(t, mb), pair_col(nb, q)).  A lane's
+// two row (column) operands are neighbours, so one 16-byte LDS read fetches both.
+__device__ inline int pair_row(int t, int mb) {
+  return (t >> 7) * 32 + 2 * (t & 15) + mb;
+}
+__device__ inline int pair_col(int t, int nb, int q) {
+  return ((t >> 6) & 1) * 32 + 2 * (((t & 63) >> 4) + 4 * q) + nb;
+}
+
+// acc(r, c) += sum_{k0 <= k < k1} As[k][r] Bs[k][c] (paired layout).
+__device__ __forceinline__ void pair_product(Acc& acc, double (*As)[LDS_LD], double (*Bs)[LDS_LD],
+                                             int k0, int k1) {
+  const int t = task_tid(), lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int ar = (w >> 1) * 32 + 2 * (lane & 15), bc = (w & 1) * 32 + 2 * (lane & 15);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const long kc = (long)(k * NB + kq + 4 * q);
-      ra[q] = (r < mr) ? Ar[(long)(r0 + r) + kc * ldar] : 0.0;
-      rb[q] = (r < mc) ? A[(long)(c0 + r) + kc * lda] : 0.0;
+  for (int ks = k0; ks < k1; ks += 4) {
+    const double2_t a = *(const double2_t*)&As[ks + (lane >> 4)][ar];
+    const double2_t b = *(const double2_t*)&Bs[ks + (lane >> 4)][bc];
+    acc.c[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[0], a[0], acc.c[0][0], 0, 0, 0);
+    acc.c[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[1], a[0], acc.c[0][1], 0, 0, 0);
+    acc.c[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[0], a[1], acc.c[1][0], 0, 0, 0);
+    acc.c[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[1], a[1], acc.c[1][1], 0, 0, 0);
+  }
+}
+
+// T[c][r] = f(element of this thread, its index 0..15) in the paired layout.
+template <typename F>
+__device__ __forceinline__ void pair_to_lds(double (*T)[LDS_LD], F f) {
+  const int t = task_tid();
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+    for (int qq = 0; qq < 4; ++qq) {
+      const double2_t v = {f(0, nb, qq), f(1, nb, qq)};
+      *(double2_t*)&T[pair_col(t, nb, qq)][pair_row(t, 0)] = v;
+    }
+}
+
+// The sixteen elements of this thread (paired layout, index 8 mb + 4 nb + q) of
+// the mr x mc tile of A at (r0, c0), read coherently: a task's own input tile
+// (0 outside the tile).
+__device__ __forceinline__ void load_own_tile(double (&v)[16], const double* A, long lda, int r0,
+                                              int c0, int mr, int mc) {
+  const int t = task_tid();
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int r = pair_row(t, e >> 3), c = pair_col(t, (e >> 2) & 1, e & 3);
+    v[e] = coherent_load(&A[(long)(r0 + min(r, mr - 1)) + (long)(c0 + min(c, mc - 1)) * lda]);
+  }
+  regs_ready(v);
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int r = pair_row(t, e >> 3), c = pair_col(t, (e >> 2) & 1, e & 3);
+    if (r >= mr || c >= mc) v[e] = 0.0;
+  }
+}
+
+// acc[u] += sum_{k<kend} L_ik L_{j+u,k}^T, u < CT (paired layout): one tile row
+// and CT tile columns.  The operands pass through LDS in chunks of KD columns,
+// double-buffered (each buffer the row operand's chunk over the column
+// operands'): the products of chunk q run while chunk q + 1 is written to the
+// other buffer from registers and chunk q + 2 is loaded into them, with one
+// barrier a chunk.  Thread 0 reads the ready flags of a later 64-column step
+// during each chunk, so neither the flag round trip nor the operand latency is
+// on the path when the producers are ahead; a step whose flags are not set yet
+// is awaited after the last chunk before it.  512 workgroups of 45 steps each,
+// all operands ready: 53 TFLOP/s for CT = 1 (41 with one buffer, two barriers a
+// step and 8-byte LDS reads) and 58 for CT = 2; the rest is the barrier and the
+// LDS round trip per chunk (128 x 128 tiles reach 69, but finish a row's tile
+// too late for the next one).  buf: 2 NB rows; s_rdy: three LDS ints.
+template <int CT>
+__device__ bool df_accumulate(Acc (&acc)[CT], double (*buf)[LDS_LD], const double* __restrict__ Ar,
+                              int ldar, int r0, int mr, const double* __restrict__ A, int lda,
+                              int c0, int mc, int i, int j, int kend, int nt, const int* flags,
+                              int epoch, int* err, int* s_rdy, const int* mark) {
+  if (kend == 0) return true;
+  constexpr int KD = CT == 1 ? 32 : 16;                      // columns per chunk
+  constexpr int CPS = NB / KD;                               // chunks per 64-column step
+  static_assert(2 * (1 + CT) * KD <= 2 * NB, "two chunks must fit the two tile buffers");
+  const int t = task_tid();
+  const int rp = 2 * (t & 31), k8 = t >> 5;
+  // rows past the tile's edge: the address is clamped to the last pair of rows
+  // (leading dimensions are even, so a pair never leaves its column) and the
+  // value replaced by zero
+  const double* pa = Ar + r0 + min(rp, (mr - 1) & ~1) + (long)k8 * ldar;
+  const double* pb = A + c0 + min(rp, (mc - 1) & ~1) + (long)k8 * lda;
+  const bool ragged = mr < NB || mc < NB;
+  double2_t va[KD / 8], vb[CT][KD / 8];
+  const auto load = [&](int ch) {
+#pragma unroll
+    for (int q = 0; q < KD / 8; ++q) {
+      va[q] = *(const double2_t*)(pa + (long)(ch * KD + 8 * q) * ldar);
+#pragma unroll
+      for (int u = 0; u < CT; ++u)
+        vb[u][q] = *(const double2_t*)(pb + u * NB + (long)(ch * KD + 8 * q) * lda);
     }
   };
-  int fi = 0, fj = 0;          // thread 0: flags of the next step, read ahead
-  int fm = 0;                  // thread 0: this unit's courtesy mark (mark != NULL)
-  if (t == 0) {
-    if (!df_wait(&flags[i * nt], epoch, err) || !df_wait(&flags[j * nt], epoch, err)) *s_ok = 0;
-  }
-  __syncthreads();
-  if (!*s_ok) return false;
-  load_tile(0);
-  if (t == 0 && kend > 1) {
-    fi = __hip_atomic_load(&flags[i * nt + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    fj = __hip_atomic_load(&flags[j * nt + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  for (int k = 0; k < kend; ++k) {
-    __syncthreads();                         // previous step's products are done with LDS
+  const auto put = [&](double (*b)[LDS_LD]) {
+    if (ragged) {
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      As[kq + 4 * q][r] = ra[q];
-      Bs[kq + 4 * q][r] = rb[q];
-    }
-    const bool nxt = k + 1 < kend;
-    if (t == 0 && fm == epoch) cu_pause(mark, epoch);
-    if (t == 0 && nxt && (fi != epoch || fj != epoch)) {
-      if (!df_wait(&flags[i * nt + k + 1], epoch, err) ||
-          !df_wait(&flags[j * nt + k + 1], epoch, err))
-        *s_ok = 0;
-    }
-    __syncthreads();
-    if (!*s_ok) return false;
-    if (nxt) {
-      load_tile(k + 1);
-      if (t == 0 && k + 2 < kend) {
-        fi = __hip_atomic_load(&flags[i * nt + k + 2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        fj = __hip_atomic_load(&flags[j * nt + k + 2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int q = 0; q < KD / 8; ++q) {
+        va[q] = double2_t{rp < mr ? va[q][0] : 0.0, rp + 1 < mr ? va[q][1] : 0.0};
+        if (CT == 1) vb[0][q] = double2_t{rp < mc ? vb[0][q][0] : 0.0, rp + 1 < mc ? vb[0][q][1] : 0.0};
       }
-      if (t == 0 && mark) fm = __hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 #pragma unroll
-    for (int ks = 0; ks < NB / 4; ++ks) {
-      const int kk = ks * 4 + (lane >> 4);
-      const double a0 = As[kk][wr * 32 + (lane & 15)];
-      const double a1 = As[kk][wr * 32 + 16 + (lane & 15)];
-      const double b0 = Bs[kk][wc * 32 + (lane & 15)];
-      const double b1 = Bs[kk][wc * 32 + 16 + (lane & 15)];
-      acc.c[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(b0, a0, acc.c[0][0], 0, 0, 0);
-      acc.c[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(b1, a0, acc.c[0][1], 0, 0, 0);
-      acc.c[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(b0, a1, acc.c[1][0], 0, 0, 0);
-      acc.c[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(b1, a1, acc.c[1][1], 0, 0, 0);
+    for (int q = 0; q < KD / 8; ++q) {
+      *(double2_t*)&b[k8 + 8 * q][rp] = va[q];
+#pragma unroll
+      for (int u = 0; u < CT; ++u) *(double2_t*)&b[(1 + u) * KD + k8 + 8 * q][rp] = vb[u][q];
+    }
+  };
+  // columns k0 .. k1 - 1 of a chunk in LDS
+  const auto products = [&](double (*b)[LDS_LD], int k0, int k1) {
+    const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int ar = (w >> 1) * 32 + 2 * (lane & 15), bc = (w & 1) * 32 + 2 * (lane & 15);
+#pragma unroll
+    for (int ks = k0; ks < k1; ks += 4) {
+      const double2_t a = *(const double2_t*)&b[ks + (lane >> 4)][ar];
+#pragma unroll
+      for (int u = 0; u < CT; ++u) {
+        const double2_t c = *(const double2_t*)&b[(1 + u) * KD + ks + (lane >> 4)][bc];
+        acc[u].c[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[0], a[0], acc[u].c[0][0], 0, 0, 0);
+        acc[u].c[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[1], a[0], acc[u].c[0][1], 0, 0, 0);
+        acc[u].c[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[0], a[1], acc[u].c[1][0], 0, 0, 0);
+        acc[u].c[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[1], a[1], acc[u].c[1][1], 0, 0, 0);
+      }
+    }
+  };
+  const int* const fi = &flags[i * nt];
+  const int* const fj = &flags[j * nt];
+  // thread 0 waits for the flags of 64-column step k
+  const auto await = [&](int k) {
+    if (t == 0)
+      s_rdy[2] = df_wait(&fi[k], epoch, err) && df_wait(&fj[k], epoch, err) &&
+                         (CT == 1 || df_wait(&fj[nt + k], epoch, err))
+                     ? k + 1 : -1;
+    __syncthreads();
+    return s_rdy[2];
+  };
+  double (*const oth0)[LDS_LD] = buf + (1 + CT) * KD;
+  const int nch = kend * CPS;
+  int rdy = await(0);                          // 64-column steps known to be published
+  if (rdy < 0) return false;
+  load(0);
+  put(buf);
+  load(1);
+  int held = 1;                                // chunk in va, vb (-1: none)
+  __syncthreads();
+  for (int ch = 0; ch < nch; ++ch) {
+    double (*const cur)[LDS_LD] = (ch & 1) ? oth0 : buf;
+    double (*const oth)[LDS_LD] = (ch & 1) ? buf : oth0;
+    int gi = 0, gj = 0, gj1 = 0, gm = 0;
+    const bool peek = t == 0 && rdy < kend;
+    if (peek) {
+      gi = __hip_atomic_load(&fi[rdy], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      gj = __hip_atomic_load(&fj[rdy], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      gj1 = CT == 1 ? epoch
+                    : __hip_atomic_load(&fj[nt + rdy], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (t == 0 && mark) gm = __hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    products(cur, 0, KD / 2);
+    const bool have = held == ch + 1;
+    if (have) {
+      put(oth);
+      held = -1;
+    }
+    const int want = have ? ch + 2 : ch + 1;
+    if (held < 0 && want < nch && want / CPS < rdy) {
+      load(want);
+      held = want;
+    }
+    products(cur, KD / 2, KD);
+    if (t == 0) s_rdy[ch & 1] = rdy + (peek && gi == epoch && gj == epoch && gj1 == epoch ? 1 : 0);
+    if (t == 0 && mark && gm == epoch) cu_pause(mark, epoch);
+    __syncthreads();
+    rdy = s_rdy[ch & 1];                       // not written again before the next barrier
+    if (ch + 1 < nch && !have) {
+      if (held < 0) {
+        if ((ch + 1) / CPS >= rdy) {
+          rdy = await((ch + 1) / CPS);
+          if (rdy < 0) return false;
+        }
+        load(ch + 1);
+      }
+      put(oth);
+      held = -1;
+      if (ch + 2 < nch && (ch + 2) / CPS < rdy) {
+        load(ch + 2);
+        held = ch + 2;
+      }
+      __syncthreads();
     }
   }
   return true;
-}
-
-// acc(r, c) += sum_kk As[kk][r] Bs[kk][c] over one 64-deep block in LDS (this
-// wave's 32 x 32 share, the layout of Acc).
-__device__ inline void lds_product(Acc& acc, double (*As)[LDS_LD], double (*Bs)[LDS_LD]) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int wr = w >> 1, wc = w & 1;
-#pragma unroll 4
-  for (int ks = 0; ks < NB / 4; ++ks) {
-    const int k = ks * 4 + (lane >> 4);
-    const double a0 = As[k][wr * 32 + (lane & 15)];
-    const double a1 = As[k][wr * 32 + 16 + (lane & 15)];
-    const double b0 = Bs[k][wc * 32 + (lane & 15)];
-    const double b1 = Bs[k][wc * 32 + 16 + (lane & 15)];
-    acc.c[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(b0, a0, acc.c[0][0], 0, 0, 0);
-    acc.c[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(b1, a0, acc.c[0][1], 0, 0, 0);
-    acc.c[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(b0, a1, acc.c[1][0], 0, 0, 0);
-    acc.c[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(b1, a1, acc.c[1][1], 0, 0, 0);
-  }
 }
 
 // Triangular right factor: acc(r, c) = sum_k As[k][r] Bs[k][c] where
@@ -237,17 +342,18 @@ __device__ inline void lds_product(Acc& acc, double (*As)[LDS_LD], double (*Bs)[
 // (40 products per wave instead of 64); accumulator block nb of this wave is
 // column block tri_cb(nb).  Only exact zeros are skipped, so the result is
 // the full product's.
-__device__ inline int tri_cb(int nb) {
-  const int wc = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) & 1;
+__device__ inline int tri_cb(int t, int nb) {
+  const int wc = __builtin_amdgcn_readfirstlane(t >> 6) & 1;
   return wc ? 1 + nb : 3 * nb;
 }
-__device__ inline int tri_col(int nb, int q) {
-  return 16 * tri_cb(nb) + (int)((threadIdx.x & 63) >> 4) + 4 * q;
+__device__ inline int tri_col(int t, int nb, int q) {
+  return 16 * tri_cb(t, nb) + ((t & 63) >> 4) + 4 * q;
 }
+__device__ inline int tri_row(int t, int mb) { return (t >> 7) * 32 + mb * 16 + (t & 15); }
 __device__ inline void lds_product_tri(Acc& acc, double (*As)[LDS_LD], double (*Bs)[LDS_LD]) {
-  const int lane = threadIdx.x & 63;
-  const int wr = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) >> 1;
-  const int cb0 = tri_cb(0), cb1 = tri_cb(1);
+  const int t = task_tid(), lane = t & 63;
+  const int wr = __builtin_amdgcn_readfirstlane(t >> 6) >> 1;
+  const int cb0 = tri_cb(t, 0), cb1 = tri_cb(t, 1);
   const int kA = 4 * (cb0 + 1), kB = 4 * (cb1 + 1);     // 4-deep steps per block, kA < kB
 #pragma unroll 4
   for (int ks = 0; ks < kA; ++ks) {
@@ -272,43 +378,45 @@ __device__ inline void lds_product_tri(Acc& acc, double (*As)[LDS_LD], double (*
   }
 }
 
-// T[c][r] = sign * acc(r, c)
-__device__ inline void acc_to_lds(const Acc& acc, double (*T)[LDS_LD], double sign) {
+// T[c][r] = src[r + c ld] for a full 64 x 64 tile of published data, 16 bytes
+// a load, with all eight loads of a thread in flight before the LDS writes.
+__device__ inline void stage_tile(double (*T)[LDS_LD], const double* __restrict__ src, long ld) {
+  const int t = task_tid();
+  double2_t v[8];
 #pragma unroll
-  for (int mb = 0; mb < 2; ++mb)
+  for (int q = 0; q < 8; ++q) v[q] = *(const double2_t*)&src[2 * (t & 31) + ((t >> 5) + 8 * q) * ld];
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-      for (int qq = 0; qq < 4; ++qq) T[acc_col(nb, qq)][acc_row(mb)] = sign * acc.c[mb][nb][qq];
-}
-
-// T[e >> 6][e & 63] = src[e] for the 4096 elements of a 64 x 64 tile, with
-// all sixteen loads of a thread in flight before the LDS writes.
-__device__ inline void stage_tile(double (*T)[LDS_LD], const double* __restrict__ src) {
-  const int t = threadIdx.x;
-  double v[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) v[q] = src[t + 256 * q];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) T[(t >> 6) + 4 * q][t & 63] = v[q];
+  for (int q = 0; q < 8; ++q) *(double2_t*)&T[(t >> 5) + 8 * q][2 * (t & 31)] = v[q];
 }
 
 // Task kinds in column j (tickets in this order):
-//  * diagonal (j, j): accumulates k < j - 1, then finishes the sub-diagonal
-//    tile itself, L_{j,j-1} = (A_{j,j-1} - S_j) Linv_{j-1}^T with the partial
-//    sum S_j of the task below, adds its last product and factors the tile.
-//    The first sub-diagonal tile thus never takes a hand-off of its own on the
-//    chain diag(j-1) -> diag(j), the critical path of the factorization.
-//  * sub-diagonal (j + 1, j): S_{j+1} = sum_{k<j} L_{j+1,k} L_{j,k}^T into
-//    the workspace sbuf (published with its own flag, no Linv wait).
-//  * (i, j), i >= j + 2: accumulates k < j, waits for Linv_jj, forms
-//    L_ij = (A_ij - acc) Linv_jj^T.
+//  * diagonal (j, j): accumulates k < j - 2, finishes the two tiles to its left
+//    itself and factors the tile:
+//      L_{j,j-2} = (A_{j,j-2} - P2_j) Linv_{j-2}^T, while Linv_{j-1} is awaited,
+//      L_{j,j-1} = (A_{j,j-1} - P1_j - L_{j,j-2} L_{j-1,j-2}^T) Linv_{j-1}^T,
+//    with the partial sums P1_j, P2_j (k < j - 2) of the two tasks below.  The
+//    chain diag(j-1) -> diag(j), the critical path, thus has one hand-off per
+//    column, Linv_{j-1}, and what feeds it from the column before that is
+//    computed by the diagonal's own workgroup.
+//  * (j + 1, j) and (j + 2, j): the partial sums P1_{j+1} (k < j - 1) and
+//    P2_{j+2} (k < j) of tiles left of a diagonal, into the workspace sbuf
+//    (published with flags of their own, no Linv wait).
+//  * (i, j), i >= j + 3: accumulates k < j, waits for Linv_jj, forms
+//    L_ij = (A_ij - acc) Linv_jj^T.  Large matrices (df64_wide) take two tiles
+//    of a row, (i, j) and (i, j + 1) with j even and i >= j + 4, as one task:
+//    they share the row operand, and after L_ij the step k = j of the second
+//    tile is added from LDS.  Not a 2 x 2 block of tiles: the time from Linv_jj
+//    to the published L_ij, which the next tile of the row waits for, is a
+//    chain in every row (n = 6,498: 2.6 ms with 2 x 2 blocks from the eighth
+//    pair below the diagonal on).
 //  * with Yt != NULL the three right-hand sides ride along as an extra tile
 //    row (Yt: 64 x n, column-major, rows 0..2 = g^T on entry): its tasks
 //    compute Y_j = (G_j - sum_{k<j} Y_k L_jk^T) Linv_jj^T, i.e. the forward
 //    substitution y = L^-1 g, on the same schedule.
-// Flags: nt x nt for the tiles, nt more for the right-hand-side row, nt more
-// for the partial sums.
+// Flags: nt x nt for the tiles, nt for the right-hand-side row, nt for P1 and
+// nt for P2.  sbuf: nt slots for P1, then nt for P2, in the register order of
+// the task that writes them.
+template <int WIDE>
 __global__ __launch_bounds__(256, 2) void k_potrf_dataflow(double* A, int lda, int n, int nt,
                                                            double* linv_ws, double* sbuf,
                                                            int* flags, unsigned* ticket, int* info,
@@ -316,146 +424,233 @@ __global__ __launch_bounds__(256, 2) void k_potrf_dataflow(double* A, int lda, i
   const int epoch = (int)ticket[1];
   const int rhs = Yt != nullptr ? 1 : 0;
   int* const mark = cu_marks ? cu_marks + cu_slot() : nullptr;
-  int* sflags = flags + (nt + 1) * nt;
-  // two 64 x 68 double tiles (69,632 bytes): operands of the accumulation,
-  // then the tile and its inverse / Linv during the finishing step
-  __shared__ double buf0[NB][LDS_LD];
-  __shared__ double buf1[NB][LDS_LD];
-  __shared__ int s_task, s_ok;
-  const int t = threadIdx.x;
-  const int ntask = df_task_count(nt, rhs);
+  int* const p1flags = flags + (nt + 1) * nt;
+  int* const p2flags = p1flags + nt;
+  // two 64 x 68 double tiles (69,632 bytes): the operand chunks of the
+  // accumulation, then a tile and an operand of the finishing steps
+  __shared__ __attribute__((aligned(16))) double buf0[2 * NB][LDS_LD];
+  double (*const buf1)[LDS_LD] = buf0 + NB;
+  __shared__ int s_task, s_ok, s_rdy[3], s_drained;
+  const int ntask = df64_task_count(nt, WIDE, rhs);
+  // thread 0 waits for a flag; false (for every thread) if the wait was given up
+  const auto await = [&](const int* f) {
+    if (threadIdx.x == 0 && !df_wait(f, epoch, err)) s_ok = 0;
+    __syncthreads();
+    return s_ok != 0;
+  };
   for (;;) {
+    const int t = task_tid();
     __syncthreads();
     if (t == 0) {
       s_task = (int)atomicAdd(ticket, 1u);
       s_ok = 1;
+      s_drained = 0;
     }
     __syncthreads();
     const int q = s_task;
     if (q >= ntask) return;
-    int i, j;
-    df_task_of_ticket(q, nt, rhs, i, j);
+    const DfTask task = df64_task(q, nt, WIDE, rhs);
+    const int i = task.i, j = task.j;
     const bool rrow = (i == nt);
-    const bool diag = (i == j), sub = !rrow && i == j + 1;
+    const bool diag = (i == j), part = !rrow && !diag && i <= j + 2;
+    const int kend = df_acc_steps(i, j, nt);
+    if (part && kend == 0) continue;             // an empty sum: nobody reads it
     double* Ai = rrow ? Yt : A;
     const int ldai = rrow ? NB : lda;
     const int r0 = rrow ? 0 : i * NB, c0 = j * NB;
     const int mr = rrow ? 3 : min(NB, n - r0), mc = min(NB, n - c0);
-    // the diagonal chain issues first
-    const bool critical = diag || sub;
-    if (critical) __builtin_amdgcn_s_setprio(2);
-    // acc <- -A_ij (read now so that the load is off the path after the last
-    // product; padding: identity on the diagonal tile, zero elsewhere), or 0
-    Acc acc;
+    // l -> T (T[c][r]), the layout of lds_product_tri
+    const auto tri_to_lds = [&](const Acc& l, double (*T)[LDS_LD]) {
+      const int t = task_tid();
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
+      for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
+        for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-          const int r = acc_row(mb), c = acc_col(nb, qq);
-          acc.c[mb][nb][qq] = sub ? 0.0
-                            : (r < mr && c < mc)
-                                ? -coherent_load(&Ai[(long)(r0 + r) + (long)(c0 + c) * ldai])
-                                : ((diag && r == c) ? -1.0 : 0.0);
-        }
-    const int kend = df_task_kend(i, j);
-    if (!df_accumulate(acc, buf0, buf1, Ai, ldai, r0, mr, A, lda, c0, mc, i, j, kend, nt, flags,
-                       epoch, err, &s_ok, critical ? nullptr : mark))
-      return;
-    // the diagonal task's local phase: no waits from here to the inverse's flag
-    const auto mark_unit = [&]() {
-      if (t == 0 && mark) __hip_atomic_store(mark, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          for (int qq = 0; qq < 4; ++qq) T[tri_col(t, nb, qq)][tri_row(t, mb)] = l.c[mb][nb][qq];
     };
-    if (sub) {
-      double* Sb = sbuf + (long)i * NB * NB;
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-          for (int qq = 0; qq < 4; ++qq)
-            coherent_store(&Sb[acc_row(mb) + NB * acc_col(nb, qq)], acc.c[mb][nb][qq]);
-      publish_flag(&sflags[i], epoch);
-      __builtin_amdgcn_s_setprio(0);
-      continue;
-    }
-    if (diag && j > 0) {
-      // tile (j, j - 1): rows of block j (mr of them), 64 columns
-      const int cs = (j - 1) * NB;
-      __syncthreads();                             // last products done with buf0
-      {
-        const int r = t & 63;
-        double v[16];
-#pragma unroll
-        for (int qq = 0; qq < 16; ++qq)
-          v[qq] = coherent_load(&A[(long)(r0 + min(r, mr - 1)) + (long)(cs + (t >> 6) + 4 * qq) * lda]);
-        regs_ready(v);
-#pragma unroll
-        for (int qq = 0; qq < 16; ++qq) buf0[(t >> 6) + 4 * qq][r] = (r < mr) ? v[qq] : 0.0;
-      }
-      // the partial sum is usually published well before Linv_{j-1}: take it
-      // (each thread the elements it loaded above) while Linv is awaited
-      if (t == 0 && !df_wait(&sflags[j], epoch, err)) s_ok = 0;
-      __syncthreads();
-      if (!s_ok) return;
-      {
-        const double* Sb = sbuf + (long)j * NB * NB;
-        double v[16];
-#pragma unroll
-        for (int qq = 0; qq < 16; ++qq) v[qq] = Sb[t + 256 * qq];
-#pragma unroll
-        for (int qq = 0; qq < 16; ++qq) buf0[(t >> 6) + 4 * qq][t & 63] -= v[qq];   // S(r, c)
-      }
-      if (t == 0 && !df_wait(&flags[(j - 1) * nt + (j - 1)], epoch, err)) s_ok = 0;
-      __syncthreads();
-      if (!s_ok) return;
-      mark_unit();
-      stage_tile(buf1, linv_ws + (long)(j - 1) * NB * NB);   // buf1[kk][c] = Linv(c, kk)
-      __syncthreads();
-      Acc l;                                       // columns tri_col(nb, q)
-      acc_zero(l);
-      lds_product_tri(l, buf0, buf1);              // L = S Linv^T
-      __syncthreads();
-      // L into buf1 (the tile factor's inverse slot, which takes the last
-      // rank-64 update C -= L L^T block by block while its first diagonal
-      // block is factored), C without that term into buf0
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-          for (int qq = 0; qq < 4; ++qq) buf1[tri_col(nb, qq)][acc_row(mb)] = l.c[mb][nb][qq];
-      acc_to_lds(acc, buf0, -1.0);
-      // the tile goes to memory straight from the registers (each lane's
-      // sixteen rows of 16-lane runs); the tile factor publishes its flag
-      // once the stores have drained
+    // l -> rows < mr and columns < mc of the tile of M at (r0, cj * NB), straight from the registers
+    const auto tri_to_mem = [&](const Acc& l, double* M, long ld, int cj, int mcols) {
+      const int t = task_tid();
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
         for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
           for (int qq = 0; qq < 4; ++qq) {
-            const int r = acc_row(mb), c = tri_col(nb, qq);
-            if (r < mr) coherent_store(&A[(long)(r0 + r) + (long)(cs + c) * lda], l.c[mb][nb][qq]);
+            const int r = tri_row(t, mb), c = tri_col(t, nb, qq);
+            if (r < mr && c < mcols)
+              coherent_store(&M[(long)(r0 + r) + (long)(cj * NB + c) * ld], l.c[mb][nb][qq]);
           }
-      // (its transposed copy is written after the tile, off the critical path)
-    } else {
-      __syncthreads();
-      acc_to_lds(acc, buf0, -1.0);                 // C = A_ij - sum_k L_ik L_jk^T
+    };
+    // transposed copy of the tile (i, cj) in T (T[c][r] = L(r, c)), read only by
+    // the backward solve after this launch:
+    // U(cj NB + r', r0 + c') = L(r0 + c', cj NB + r') with r' = e & 63, c' = e >> 6
+    const auto transposed = [&](double (*T)[LDS_LD], int cj, int mcols) {
+      for (int e = task_tid(); e < NB * NB; e += 256) {
+        const int r = e & 63, c = e >> 6;
+        if (c < mr && r < mcols) A[(long)(cj * NB + r) + (long)(r0 + c) * lda] = T[r][c];
+      }
+    };
+    if (WIDE && task.cols == 2) {
+      Acc acc[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        double v[16];
+        load_own_tile(v, A, lda, r0, c0 + u * NB, mr, NB);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[u].c[e >> 3][(e >> 2) & 1][e & 3] = -v[e];
+      }
+      if (!df_accumulate<2>(acc, buf0, A, lda, r0, mr, A, lda, c0, NB, i, j, j, nt, flags, epoch,
+                            err, s_rdy, mark))
+        return;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        pair_to_lds(buf0, [&](int mb, int nb, int qq) { return -acc[u].c[mb][nb][qq]; });
+        if (!await(&flags[(j + u) * nt + (j + u)])) return;
+        stage_tile(buf1, linv_ws + (long)(j + u) * NB * NB, NB);
+        __syncthreads();
+        Acc l;
+        acc_zero(l);
+        lds_product_tri(l, buf0, buf1);
+        tri_to_mem(l, A, lda, j + u, NB);
+        __syncthreads();
+        tri_to_lds(l, buf0);
+        if (u == 0) {
+          if (!await(&flags[(j + 1) * nt + j])) return;
+          stage_tile(buf1, A + (long)(j + 1) * NB + (long)c0 * lda, lda);
+          __syncthreads();
+          pair_product(acc[1], buf0, buf1, 0, NB);
+        }
+        publish_flag(&flags[i * nt + j + u], epoch);
+        transposed(buf0, j + u, NB);
+        __syncthreads();
+      }
+      continue;
     }
-    __syncthreads();
+    // the diagonal chain issues first
+    const bool critical = diag || part;
+    if (critical) __builtin_amdgcn_s_setprio(2);
+    // acc <- -A_ij (read now so that the load is off the path after the last
+    // product; padding: identity on the diagonal tile, zero elsewhere), or 0
+    Acc acc1[1];
+    Acc& acc = acc1[0];
+    {
+      double v[16];
+      if (part) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = 0.0;
+      } else {
+        load_own_tile(v, Ai, ldai, r0, c0, mr, mc);
+      }
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int mb = e >> 3, nb = (e >> 2) & 1, qq = e & 3;
+        const bool pad = diag && pair_row(t, mb) == pair_col(t, nb, qq) && pair_row(t, mb) >= mr;
+        acc.c[mb][nb][qq] = pad ? -1.0 : -v[e];
+      }
+    }
+    if (!df_accumulate<1>(acc1, buf0, Ai, ldai, r0, mr, A, lda, c0, mc, i, j, kend, nt, flags, epoch,
+                          err, s_rdy, critical ? nullptr : mark))
+      return;
+    // the diagonal task's local phase: no waits from here to the inverse's flag
+    const auto mark_unit = [&]() {
+      if (t == 0 && mark) __hip_atomic_store(mark, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (part) {
+      const int slot = i == j + 1 ? i : nt + i;
+      double* Sb = sbuf + (long)slot * NB * NB;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) coherent_store(&Sb[e * 256 + t], acc.c[e >> 3][(e >> 2) & 1][e & 3]);
+      publish_flag(&p1flags[slot], epoch);
+      __builtin_amdgcn_s_setprio(0);
+      continue;
+    }
+    // v -= the partial sum in a slot of sbuf (paired layout)
+    const auto subtract_part = [&](double (&v)[16], int slot) {
+      const int tt = task_tid();
+      const double* Sb = sbuf + (long)slot * NB * NB;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v[e] -= Sb[e * 256 + tt];
+    };
+    const auto own_to_lds = [&](const double (&v)[16], double (*T)[LDS_LD]) {
+      pair_to_lds(T, [&](int mb, int nb, int qq) { return v[8 * mb + 4 * nb + qq]; });
+    };
     if (diag) {
-      if (j == 0) mark_unit();
-      factor_tile_blocked(buf0, buf1, mr, r0, info, j > 0 ? &flags[j * nt + (j - 1)] : nullptr,
-                          epoch);
-      // only the inverse is read inside this launch: publish it first, then
-      // write L (lower) and its transposed copy (strictly upper) for the solves
-      double* Li = linv_ws + (long)j * NB * NB;
-      for (int e = t; e < NB * NB; e += 256) coherent_store(&Li[e], buf1[e >> 6][e & 63]);
-      // the mark is cleared before the flag is stored (publish_flag waits for
-      // both), so the next diagonal task, which may run on this unit, sets its
-      // own mark after this clear
+      if (j > 0) {
+        double v[16];                              // what becomes L_{j,j-1}
+        load_own_tile(v, A, lda, r0, (j - 1) * NB, mr, NB);
+        if (j > 1) {
+          {
+            double v2[16];                         // what becomes L_{j,j-2}
+            load_own_tile(v2, A, lda, r0, (j - 2) * NB, mr, NB);
+            if (!await(&flags[(j - 2) * nt + (j - 2)])) return;
+            stage_tile(buf1, linv_ws + (long)(j - 2) * NB * NB, NB);   // buf1[kk][c] = Linv(c, kk)
+            if (j > 2) {
+              if (!await(&p1flags[nt + j])) return;
+              subtract_part(v2, nt + j);
+            }
+            own_to_lds(v2, buf0);
+          }
+          __syncthreads();
+          Acc l;
+          acc_zero(l);
+          lds_product_tri(l, buf0, buf1);
+          __syncthreads();
+          tri_to_lds(l, buf0);
+          tri_to_mem(l, A, lda, j - 2, NB);
+          __syncthreads();
+          pair_product(acc, buf0, buf0, 0, NB);
+          publish_flag(&flags[j * nt + (j - 2)], epoch);
+          if (t == 0 && (!df_wait(&flags[(j - 1) * nt + (j - 2)], epoch, err) ||
+                         (j > 2 && !df_wait(&p1flags[j], epoch, err))))
+            s_ok = 0;
+          __syncthreads();
+          if (!s_ok) return;
+          stage_tile(buf1, A + (long)(j - 1) * NB + (long)(j - 2) * NB * lda, lda);
+          if (j > 2) subtract_part(v, j);
+          __syncthreads();
+          Acc s;                                   // L_{j,j-2} L_{j-1,j-2}^T
+          acc_zero(s);
+          pair_product(s, buf0, buf1, 0, NB);
+#pragma unroll
+          for (int e = 0; e < 16; ++e) v[e] -= s.c[e >> 3][(e >> 2) & 1][e & 3];
+          __syncthreads();
+        }
+        own_to_lds(v, buf0);
+        if (!await(&flags[(j - 1) * nt + (j - 1)])) return;
+        mark_unit();
+        stage_tile(buf1, linv_ws + (long)(j - 1) * NB * NB, NB);
+        __syncthreads();
+        Acc l;
+        acc_zero(l);
+        lds_product_tri(l, buf0, buf1);            // L = S Linv^T
+        __syncthreads();
+        // L into buf1 (the tile factor's inverse slot, which takes the last
+        // rank-64 update C -= L L^T block by block), C without that term into
+        // buf0; the tile factor also writes L and the inverse to memory
+        tri_to_lds(l, buf1);
+      } else {
+        mark_unit();
+      }
+      pair_to_lds(buf0, [&](int mb, int nb, int qq) { return -acc.c[mb][nb][qq]; });
+      __syncthreads();
+      TilePublish pub;
+      pub.epoch = epoch;
+      pub.inv = linv_ws + (long)j * NB * NB;
+      if (j > 0) {
+        pub.lflag = &flags[j * nt + (j - 1)];
+        pub.l = A + (long)r0 + (long)(j - 1) * NB * lda;
+        pub.ldl = lda;
+        pub.lrows = mr;
+        pub.drained = &s_drained;
+      }
+      factor_tile_blocked(buf0, buf1, mr, r0, info, pub);
+      // only the inverse is read inside this launch: it is published first,
+      // then L (lower) and its transposed copy (strictly upper) are written for
+      // the solves.  The mark is cleared before the flag is stored
+      // (publish_flag waits for both), so the next diagonal task, which may run
+      // on this unit, sets its own mark after this clear
       if (t == 0 && mark) __hip_atomic_store(mark, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       publish_flag(&flags[i * nt + j], epoch);
       for (int e = t; e < NB * NB; e += 256) {
@@ -463,11 +658,11 @@ __global__ __launch_bounds__(256, 2) void k_potrf_dataflow(double* A, int lda, i
         if (r < mr && c < mr)
           A[(long)(r0 + r) + (long)(r0 + c) * lda] = (r >= c) ? buf0[c][r] : buf0[r][c];
       }
-      if (j > 0) {
-        // transposed copy of the sub-diagonal tile finished above, read back
-        // (coalesced, coherent) and turned through LDS:
-        // U(cs + r', r0 + c') = L(r0 + c', cs + r')
-        const int cs = (j - 1) * NB;
+      // transposed copies of the tiles finished above, read back (coalesced,
+      // coherent) and turned through LDS: U(cs + r', r0 + c') = L(r0 + c', cs + r')
+      for (int cj = max(j - 2, 0); cj < j; ++cj) {
+        const int cs = cj * NB;
+        __syncthreads();
         {
           const int r = t & 63;
           double v[16];
@@ -485,37 +680,19 @@ __global__ __launch_bounds__(256, 2) void k_potrf_dataflow(double* A, int lda, i
         }
       }
     } else {
-      if (t == 0 && !df_wait(&flags[j * nt + j], epoch, err)) s_ok = 0;
-      __syncthreads();
-      if (!s_ok) return;
-      stage_tile(buf1, linv_ws + (long)j * NB * NB);   // buf1[kk][c] = Linv(c, kk)
+      pair_to_lds(buf0, [&](int mb, int nb, int qq) { return -acc.c[mb][nb][qq]; });
+      if (!await(&flags[j * nt + j])) return;
+      stage_tile(buf1, linv_ws + (long)j * NB * NB, NB);
       __syncthreads();
       acc_zero(acc);
-      lds_product(acc, buf0, buf1);
-      // stored straight from the registers (the right-hand-side row also runs
-      // over the last, ragged, column block); the LDS copy is for the
-      // transposed copy below
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-          for (int qq = 0; qq < 4; ++qq) {
-            const int r = acc_row(mb), c = acc_col(nb, qq);
-            if (r < mr && c < mc)
-              coherent_store(&Ai[(long)(r0 + r) + (long)(c0 + c) * ldai], acc.c[mb][nb][qq]);
-          }
+      lds_product_tri(acc, buf0, buf1);            // (A_ij - sum) Linv_jj^T
+      // (the right-hand-side row also runs over the last, ragged, column
+      // block); the LDS copy is for the transposed copy below
+      tri_to_mem(acc, rrow ? Yt : A, ldai, j, mc);
       __syncthreads();
-      acc_to_lds(acc, buf0, 1.0);
+      if (!rrow) tri_to_lds(acc, buf0);
       publish_flag(&flags[i * nt + j], epoch);
-      // transposed copy, read only by the backward solve after this launch:
-      // U(c0 + r', r0 + c') = L(r0 + c', c0 + r') with r' = e & 63, c' = e >> 6
-      if (!rrow) {
-        for (int e = t; e < NB * NB; e += 256) {
-          const int r = e & 63, c = e >> 6;
-          if (c < mr && r < mc) A[(long)(c0 + r) + (long)(r0 + c) * lda] = buf0[r][c];
-        }
-      }
+      if (!rrow) transposed(buf0, j, mc);
     }
     if (critical) __builtin_amdgcn_s_setprio(0);
   }
@@ -525,11 +702,15 @@ void potrf_dataflow(double* A, int lda, int n, double* linv_ws, double* sbuf, in
                     unsigned* ticket, int* info, int* err, int n_wg, double* Yt, hipStream_t st,
                     int* cu_marks, hipEvent_t after_reset) {
   const int nt = (n + NB - 1) / NB;
-  const int ntask = df_task_count(nt, Yt ? 1 : 0);
+  const int wide = df64_wide(nt);
+  const int ntask = df64_task_count(nt, wide, Yt ? 1 : 0);
   k_reset_counter<<<1, 1, 0, st>>>(ticket);
   if (after_reset) (void)hipEventRecord(after_reset, st);
-  k_potrf_dataflow<<<std::min(ntask, n_wg), 256, 0, st>>>(A, lda, n, nt, linv_ws, sbuf, flags,
-                                                          ticket, info, err, Yt, cu_marks);
+  // two instances: the code of the two-tile task, unused, would cost the
+  // diagonal chain 1.7 us per column through the register allocation
+  const auto kernel = wide ? k_potrf_dataflow<1> : k_potrf_dataflow<0>;
+  kernel<<<std::min(ntask, n_wg), 256, 0, st>>>(A, lda, n, nt, linv_ws, sbuf, flags, ticket, info,
+                                                err, Yt, cu_marks);
 }
 
 int potrf_cu_slots() { return CU_SLOTS; }

@@ -403,7 +403,7 @@ __global__ __launch_bounds__(256, 2) void k_potrf_dataflow_lp(float* A, int lda,
       __syncthreads();
       if (j == 0 && t == 0 && mark)
         __hip_atomic_store(mark, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      factor_tile_blocked(Tf, Xf, mr, r0, info);
+      factor_tile_blocked(Tf, Xf, mr, r0, info, TilePublish{});
       float* Li = linv_ws + (long)j * NB * NB;
       for (int e = t; e < NB * NB; e += 256) cstore(&Li[e], (float)Xf[e >> 6][e & 63]);
       if (t == 0 && mark) __hip_atomic_store(mark, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -7,6 +7,17 @@
 
 namespace pdk {
 
+// The thread index, opaque to the compiler: a persistent kernel's task loop
+// otherwise keeps the addresses that each of its phases derives from it in
+// registers over all the other phases (and spills).  For workgroups of 256
+// threads; the mask tells the compiler the range, without which it cannot fold
+// offsets into LDS addresses.
+__device__ __forceinline__ int task_tid() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t & 255;
+}
+
 __device__ inline double coherent_load(const double* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

@@ -69,3 +69,26 @@ def test_orders_around_the_edges(n):
     lo, info = factor(a, (n + 15) // 16 * 16)
     assert info == 0
     assert close(lo, np.linalg.cholesky(a), n)
+
+
+@pytest.mark.parametrize("n", [10177, 10240, 10300])
+def test_two_tile_tasks(n):
+    """Orders from which a task holds two tiles of a row (160 tile columns on;
+    even and odd counts, ragged last tile) against torch on the device."""
+    import torch
+    from paper_2008_01541_amd import DenseCholesky
+    lda = (n + 15) // 16 * 16
+    g = torch.Generator(device="cuda").manual_seed(n)
+    a = torch.rand(n, n, dtype=torch.float64, device="cuda", generator=g) - 0.5
+    a = torch.tril(a) + torch.tril(a, -1).T
+    a.diagonal().add_(0.5 * n)
+    buf = torch.full((n, lda), float("nan"), dtype=torch.float64, device="cuda")
+    buf[:, :n] = a
+    chol = DenseCholesky(n)
+    assert chol.factor(buf.view(-1), n, lda) == 0
+    chol.close()
+    ref = torch.linalg.cholesky(a)
+    lo = torch.tril(buf[:, :n].T)
+    assert torch.equal(torch.triu(buf[:, :n].T, 1), torch.tril(lo, -1).T)
+    eps = torch.finfo(torch.float64).eps
+    assert float((lo - ref).abs().max()) <= 64 * n * eps * float(ref.abs().max())
