@@ -10,18 +10,21 @@
 #include "common.h"
 
 namespace pdk {
-void mlp_gemm(int M, int N, int K, const void* A, bool a_bf16, bool a_kcontig, long lda,
-              const void* B, bool b_bf16, bool b_kcontig, long ldb, float* part, int nsplit,
-              hipStream_t st);
+void mlp_gemm(int M, int N, int K, const float* A, long lda, const float* B, long ldb, float* part,
+              int nsplit, hipStream_t st);
 int mlp_gemm_nsplit(int M, int N, int K, int nsplit);
 void mlp_split_reduce(int M, int N, int nsplit, const float* part, const float* bias, int relu,
-                      float* out, hipStream_t st);
+                      const float* H, float* out, hipStream_t st);
+void mlp_rows(int M, int N, int K, const float* X, const __bf16* W, const float* bias, int relu,
+              float* part, int nsplit, float* out, hipStream_t st);
+void mlp_cols(int M, int N, int K, const float* X, const __bf16* W, const float* H, float* part,
+              int nsplit, float* out, hipStream_t st);
 void mlp_loss_grad(long total, int n_out_times_b, const float* Y, const float* T, float* dY,
                    double* part, double* loss, hipStream_t st);
-void mlp_relu_back(long n, const float* H, float* dA, hipStream_t st);
 void mlp_colsum(int M, int N, const float* dZ, float* gb, hipStream_t st);
-void mlp_adam(long n, float* w, const float* g, float* m, float* v, __bf16* wb, float lr, int step,
-              hipStream_t st);
+void mlp_grad_adam(int B, const int* M, const int* N, const float* const* dZ, const float* const* X,
+                   float* w, float* m, float* v, __bf16* wb, const long* off, const long* boff,
+                   float lr, int step, hipStream_t st);
 void mlp_to_bf16(long n, const float* w, __bf16* wb, hipStream_t st);
 void mlp_gather_rows_scaled(int B, int n_cols, const float* src, const int32_t* rows, int n_scaled,
                             float scale, float* dst, hipStream_t st);
@@ -67,27 +70,22 @@ int pick_split(int M, int N, int K) {
   return s;
 }
 
-// out = opA opB^T (+ bias) (relu) through the split-K workspace
-void gemm_to(pd_mlp* h, int M, int N, int K, const void* A, bool abf, bool akc, long lda,
-             const void* B, bool bbf, bool bkc, long ldb, const float* bias, int relu, float* out) {
+// W-shaped gradient out [M][N] = dZ^T X over the batch (K rows of both)
+void gradient(pd_mlp* h, int M, int N, int K, const float* dZ, const float* X, float* out) {
   const int s = pick_split(M, N, K);
   const int nz = mlp_gemm_nsplit(M, N, K, s);
-  if (nz == 1 && !bias && !relu) {
-    mlp_gemm(M, N, K, A, abf, akc, lda, B, bbf, bkc, ldb, out, s, h->st);
-    return;
-  }
-  mlp_gemm(M, N, K, A, abf, akc, lda, B, bbf, bkc, ldb, h->part, s, h->st);
-  mlp_split_reduce(M, N, nz, h->part, bias, relu, out, h->st);
+  mlp_gemm(M, N, K, dZ, M, X, N, nz == 1 ? out : h->part, s, h->st);
+  if (nz > 1) mlp_split_reduce(M, N, nz, h->part, nullptr, 0, nullptr, out, h->st);
 }
 
 void forward(pd_mlp* h, const float* x, int B, float* y) {
   const float* P = h->p;
-  gemm_to(h, B, h->nh1, h->nin, x, false, true, h->nin, h->wb + h->boff[0], true, true, h->nin,
-          P + h->off[1], 1, h->H1);
-  gemm_to(h, B, h->nh2, h->nh1, h->H1, false, true, h->nh1, h->wb + h->boff[1], true, true, h->nh1,
-          P + h->off[3], 1, h->H2);
-  gemm_to(h, B, h->nout, h->nh2, h->H2, false, true, h->nh2, h->wb + h->boff[2], true, true, h->nh2,
-          P + h->off[5], 0, y);
+  const auto layer = [&](int N, int K, const float* in, long wo, long bo, int relu, float* out) {
+    mlp_rows(B, N, K, in, h->wb + wo, P + bo, relu, h->part, pick_split(B, N, K), out, h->st);
+  };
+  layer(h->nh1, h->nin, x, h->boff[0], h->off[1], 1, h->H1);
+  layer(h->nh2, h->nh1, h->H1, h->boff[1], h->off[3], 1, h->H2);
+  layer(h->nout, h->nh2, h->H2, h->boff[2], h->off[5], 0, y);
 }
 
 bool bad_batch(const pd_mlp* h, int B) { return B <= 0 || B > h->maxb; }
@@ -161,39 +159,26 @@ pd_status pd_mlp_train_step(pd_mlp* h, const float* x, const float* target, int3
   float* P = h->p;
   float* G = h->g;
   forward(h, x, B, h->Y);
-  mlp_loss_grad((long)B * h->nout, B * h->nout, h->Y, target, h->dY, h->lpart, h->loss, h->st);
-  // layer 3
-  gemm_to(h, h->nout, h->nh2, B, h->dY, false, false, h->nout, h->H2, false, false, h->nh2, nullptr,
-          0, G + h->off[4]);
-  mlp_colsum(B, h->nout, h->dY, G + h->off[5], h->st);
-  gemm_to(h, B, h->nh2, h->nout, h->dY, false, true, h->nout, h->wb + h->boff[2], true, false,
-          h->nh2, nullptr, 0, h->dA2);
-  mlp_relu_back((long)B * h->nh2, h->H2, h->dA2, h->st);
-  // layer 2
-  gemm_to(h, h->nh2, h->nh1, B, h->dA2, false, false, h->nh2, h->H1, false, false, h->nh1, nullptr,
-          0, G + h->off[2]);
-  mlp_colsum(B, h->nh2, h->dA2, G + h->off[3], h->st);
-  gemm_to(h, B, h->nh1, h->nh2, h->dA2, false, true, h->nh2, h->wb + h->boff[1], true, false,
-          h->nh1, nullptr, 0, h->dA1);
-  mlp_relu_back((long)B * h->nh1, h->H1, h->dA1, h->st);
-  // layer 1
-  gemm_to(h, h->nh1, h->nin, B, h->dA1, false, false, h->nh1, x, false, false, h->nin, nullptr, 0,
-          G + h->off[0]);
-  mlp_colsum(B, h->nh1, h->dA1, G + h->off[1], h->st);
+  mlp_loss_grad((long)B * h->nout, B * h->nout, h->Y, target, h->dY, h->lpart,
+                loss_host ? h->loss : nullptr, h->st);
+  mlp_cols(B, h->nh2, h->nout, h->dY, h->wb + h->boff[2], h->H2, h->part,
+           pick_split(B, h->nh2, h->nout), h->dA2, h->st);
+  mlp_cols(B, h->nh1, h->nh2, h->dA2, h->wb + h->boff[1], h->H1, h->part,
+           pick_split(B, h->nh1, h->nh2), h->dA1, h->st);
+  const int M[3] = {h->nh1, h->nh2, h->nout}, N[3] = {h->nin, h->nh1, h->nh2};
+  const float* const dZ[3] = {h->dA1, h->dA2, h->dY};
+  const float* const X[3] = {x, h->H1, h->H2};
   if (grads_host) {
+    for (int i = 0; i < 3; ++i) {
+      gradient(h, M[i], N[i], B, dZ[i], X[i], G + h->off[2 * i]);
+      mlp_colsum(B, M[i], dZ[i], G + h->off[2 * i + 1], h->st);
+    }
     if (hipMemcpyAsync(grads_host, G, h->off[6] * sizeof(float), hipMemcpyDeviceToHost, h->st) !=
         hipSuccess)
       return PD_ERR_HIP;
   } else {
     h->step += 1;
-    for (int sgm = 0; sgm < 6; ++sgm) {
-      __bf16* wbp = nullptr;
-      if (sgm == 0) wbp = h->wb + h->boff[0];
-      if (sgm == 2) wbp = h->wb + h->boff[1];
-      if (sgm == 4) wbp = h->wb + h->boff[2];
-      mlp_adam(h->off[sgm + 1] - h->off[sgm], P + h->off[sgm], G + h->off[sgm], h->m + h->off[sgm],
-               h->v + h->off[sgm], wbp, lr, h->step, h->st);
-    }
+    mlp_grad_adam(B, M, N, dZ, X, P, h->m, h->v, h->wb, h->off, h->boff, lr, h->step, h->st);
   }
   if (loss_host) {
     if (hipMemcpyAsync(loss_host, h->loss, sizeof(double), hipMemcpyDeviceToHost, h->st) != hipSuccess ||
