@@ -588,6 +588,9 @@ pd_status build_impl(pd_ctx* c, const pd_mesh* M) {
   CK(c->alloc(&c->d_Yt, (int64_t)NB * m));
   CK(c->alloc(&c->d_res, 3 * m));
   CK(c->alloc(&c->d_norms, 8));
+  // boxes of the level-set detection's candidates: as many as E_beta has tets
+  c->box_len = 12 * ((c->nbeta + 63) / 64);
+  CK(c->alloc(&c->d_box, std::max<int64_t>(c->box_len, 1)));
   CK(c->alloc(&c->d_fhat, 3 * std::max<int64_t>(1, c->n1)));
   CK(c->alloc(&c->d_v, 3 * std::max<int64_t>(1, c->n1)));
   CK(c->alloc(&c->d_xs, 3 * std::max<int64_t>(1, c->n1)));
@@ -850,7 +853,7 @@ pd_status pd_detect_levelset(pd_ctx* c, int32_t n_prox, const int32_t* eidx, con
   if (c->broken) return PD_ERR_HIP;
   PhaseTimer tm(c, PD_PHASE_DETECT);
   detect_levelset(n_prox, eidx, ew, prox_body, n_cand, cand, cand_phi, cand_body, rest2, k, x2,
-                  (int)c->m, idx, w, cc, t, c->st);
+                  (int)c->m, c->d_box, c->box_len, idx, w, cc, t, c->st);
   return c->check("pd_detect_levelset");
 }
 
@@ -861,11 +864,8 @@ pd_status pd_collision_update(pd_ctx* c, int32_t n_pen, const int32_t* idx, cons
   if (c->broken) return PD_ERR_HIP;
   CK(ensure_pen_cap(c, std::max<int32_t>(n_pen, 1)));
   PhaseTimer tm(c, PD_PHASE_COLLISION);
-  if (n_pen > 0) {                    // copies by kernels (capturable like every other step)
-    copy_i32(8 * (long)n_pen, idx, c->d_pidx, c->st);
-    copy_f64(8 * (long)n_pen, w, c->d_pw, c->st);
-    copy_f64((long)n_pen, cc, c->d_pc, c->st);
-    copy_f64(3 * (long)n_pen, t, c->d_pt, c->st);
+  if (n_pen > 0) {                    // copied by a kernel (capturable like every other step)
+    copy_penalties(n_pen, idx, w, cc, t, c->d_pidx, c->d_pw, c->d_pc, c->d_pt, c->st);
   }
   c->n_pen = n_pen;
   penalty_prepare(n_pen, (int)c->m, c->d_pc, c->d_pidx, c->d_pact, c->d_pnact, c->d_prow,

@@ -143,7 +143,11 @@ void detect_embedded_spheres(int n_prox, const int32_t* eidx, const double* ew, 
 void detect_levelset(int n_prox, const int32_t* eidx, const double* ew, const int32_t* prox_body,
                      int nc, const int32_t* cand, const double* cand_phi,
                      const int32_t* cand_body, const double* rest2, double k, const double* x2,
-                     int m, int32_t* idx, double* w, double* c, double* t, hipStream_t st);
+                     int m, double* box, int64_t box_len, int32_t* idx, double* w, double* c,
+                     double* t, hipStream_t st);   // box: box_len doubles of scratch
+// copies of a penalty set's four arrays in one launch
+void copy_penalties(int n, const int32_t* idx, const double* w, const double* c, const double* t,
+                    int32_t* oidx, double* ow, double* oc, double* ot, hipStream_t st);
 // act[0..*cnt) <- indices j < n_pen with c[j] != 0, increasing (device count);
 // rowptr (m + 1) and ent (8 n_pen) <- for every region row a, the keys 8 q + s
 // of the active slots naming it (act[q], slot s), increasing; cursor: m ints

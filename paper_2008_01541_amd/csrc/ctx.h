@@ -69,6 +69,8 @@ struct pd_ctx {
   double* d_S = nullptr;
   double* d_H = nullptr;
   double* d_linv = nullptr;
+  double* d_box = nullptr;            // boxes of 64 candidates each (level-set detection)
+  int64_t box_len = 0;
   double* d_sbuf = nullptr;           // partial sums of the tiles left of the diagonal (factor)
   double* d_y = nullptr;               // scratch of the residual products
   double* d_ys = nullptr;              // forward-solve result (holds the sentinel between solves)

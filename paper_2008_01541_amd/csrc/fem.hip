@@ -583,14 +583,30 @@ __device__ inline int block_exclusive_scan(int v, int* wsum, int* total) {
   return off + x - v;
 }
 
+// CNT_LDS: the row counters and, if all fit, the keys live in dynamic LDS (m
+// ints, then up to ent_cap ints) instead of cursor[] and ent[].  One workgroup: with
+// everything in global memory it is a chain of dependent loads and atomics
+// (92 us for 2,688 level-set penalties of eight slots, 58 us for 2,990 pairs);
+// in LDS, with eight entries of a thread in flight, 38 and 30 us.
+template <bool CNT_LDS>
 __global__ __launch_bounds__(1024) void k_penalty_prepare(int n_pen, int m, const double* __restrict__ c,
                                                           const int32_t* __restrict__ idx,
                                                           int32_t* __restrict__ act,
                                                           int32_t* __restrict__ cnt,
                                                           int32_t* __restrict__ rowptr,
-                                                          int32_t* cursor, int32_t* ent) {
+                                                          int32_t* cursor, int32_t* ent_out,
+                                                          int ent_cap) {
+  extern __shared__ int32_t dyn[];
   __shared__ int32_t wsum[16];
   const int t = threadIdx.x;
+  const auto cnt_set = [&](int a, int v) {
+    if (CNT_LDS) dyn[a] = v;
+    else __hip_atomic_store(&cursor[a], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  const auto cnt_get = [&](int a) {
+    return CNT_LDS ? dyn[a] : __hip_atomic_load(&cursor[a], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  const auto cnt_add = [&](int a) { return atomicAdd(CNT_LDS ? &dyn[a] : &cursor[a], 1); };
   // active list
   int na = 0;
   for (int j0 = 0; j0 < n_pen; j0 += 1024) {
@@ -603,33 +619,45 @@ __global__ __launch_bounds__(1024) void k_penalty_prepare(int n_pen, int m, cons
   }
   if (t == 0) *cnt = na;
   // per-row counts
-  for (int a = t; a < m; a += 1024) __hip_atomic_store(&cursor[a], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int a = t; a < m; a += 1024) cnt_set(a, 0);
   __syncthreads();
-  for (int e = t; e < 8 * na; e += 1024) {
-    const int r = idx[(int64_t)act[e >> 3] * 8 + (e & 7)];
-    if (r >= 0 && r < m) atomicAdd(&cursor[r], 1);
-  }
+  // row of each slot of the active penalties, eight per thread at a time
+  const auto each_slot = [&](auto f) {
+    constexpr int U = 8;
+    for (int e0 = t; e0 < 8 * na; e0 += U * 1024) {
+      int r[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = min(e0 + 1024 * u, 8 * na - 1);
+        r[u] = idx[(int64_t)act[e >> 3] * 8 + (e & 7)];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = e0 + 1024 * u;
+        if (e < 8 * na && r[u] >= 0 && r[u] < m) f(e, r[u]);
+      }
+    }
+  };
+  each_slot([&](int, int r) { cnt_add(r); });
   __syncthreads();
   // row pointers; the cursors restart at the row starts
   int base = 0;
   for (int a0 = 0; a0 < m; a0 += 1024) {
     const int a = a0 + t;
-    const int v = a < m ? __hip_atomic_load(&cursor[a], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    const int v = a < m ? cnt_get(a) : 0;
     int tot;
     const int pos = block_exclusive_scan(v, wsum, &tot);
     if (a < m) {
       rowptr[a] = base + pos;
-      __hip_atomic_store(&cursor[a], base + pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      cnt_set(a, base + pos);
     }
     base += tot;
   }
   if (t == 0) rowptr[m] = base;
   __syncthreads();
   // fill, then order each row's keys
-  for (int e = t; e < 8 * na; e += 1024) {
-    const int r = idx[(int64_t)act[e >> 3] * 8 + (e & 7)];
-    if (r >= 0 && r < m) ent[atomicAdd(&cursor[r], 1)] = e;
-  }
+  int32_t* const ent = CNT_LDS && base <= ent_cap ? dyn + m : ent_out;
+  each_slot([&](int e, int r) { ent[cnt_add(r)] = e; });
   __syncthreads();
   for (int a = t; a < m; a += 1024) {
     const int e0 = rowptr[a], e1 = rowptr[a + 1];
@@ -643,6 +671,26 @@ __global__ __launch_bounds__(1024) void k_penalty_prepare(int n_pen, int m, cons
       ent[k + 1] = key;
     }
   }
+  if (ent == ent_out) return;
+  __syncthreads();
+  for (int e = t; e < base; e += 1024) ent_out[e] = ent[e];
+}
+
+__global__ void k_copy_penalties(int n, const int32_t* __restrict__ idx, const double* __restrict__ w,
+                                 const double* __restrict__ c, const double* __restrict__ t,
+                                 int32_t* __restrict__ oidx, double* __restrict__ ow,
+                                 double* __restrict__ oc, double* __restrict__ ot) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= 8 * (int64_t)n) return;
+  oidx[e] = idx[e];
+  ow[e] = w[e];
+  if (e < 3 * (int64_t)n) ot[e] = t[e];
+  if (e < n) oc[e] = c[e];
+}
+void copy_penalties(int n, const int32_t* idx, const double* w, const double* c, const double* t,
+                    int32_t* oidx, double* ow, double* oc, double* ot, hipStream_t st) {
+  if (n > 0)
+    k_copy_penalties<<<grid1(8 * (int64_t)n), 256, 0, st>>>(n, idx, w, c, t, oidx, ow, oc, ot);
 }
 
 // Two-sided contact of paired region nodes (a = lower lip, b = upper lip):
@@ -677,24 +725,19 @@ void detect_pairs(int n_pairs, const int32_t* pairs, double k, const double* x2,
     k_detect_pairs<<<grid1(n_pairs), 256, 0, st>>>(n_pairs, pairs, k, x2, m, idx, w, c, t);
 }
 
-// Penalty terms, one thread per region node a (row a of W^T C W and entry a
-// of f_col), over the active slots that name a (its incidence list, in
-// increasing penalty order):
-//   H[a + b*ldh] += c_j w_ja w_jb  for b <= a   (lower triangle, H may be NULL)
-//   fcol[:, a]    = -sum_j c_j w_ja (W_j x2 - tscale t_j)
-__global__ __launch_bounds__(64) void k_penalty_apply(int n_pen, const int32_t* __restrict__ act,
-                                                      const int32_t* __restrict__ rowptr,
-                                                      const int32_t* __restrict__ ent,
-                                                      const int32_t* __restrict__ idx,
-                                                      const double* __restrict__ w,
-                                                      const double* __restrict__ c,
-                                                      const double* __restrict__ t,
-                                                      double tscale,
-                                                      const double* __restrict__ x2, int m,
-                                                      double* H, int ldh, double* fcol) {
+// Penalty terms of region node a over the active slots that name it (its
+// incidence list, in increasing penalty order):
+//   H[a + b*ldh] += c_j w_ja w_jb  for b <= a   (lower triangle)
+// one thread per row.
+__global__ __launch_bounds__(64) void k_penalty_matrix(const int32_t* __restrict__ act,
+                                                       const int32_t* __restrict__ rowptr,
+                                                       const int32_t* __restrict__ ent,
+                                                       const int32_t* __restrict__ idx,
+                                                       const double* __restrict__ w,
+                                                       const double* __restrict__ c, int m,
+                                                       double* H, int ldh) {
   const int a = blockIdx.x * blockDim.x + threadIdx.x;
   if (a >= m) return;
-  double f0 = 0.0, f1 = 0.0, f2 = 0.0;
   const int e1 = rowptr[a + 1];
   for (int e = rowptr[a]; e < e1; ++e) {
     const int key = ent[e];
@@ -702,31 +745,74 @@ __global__ __launch_bounds__(64) void k_penalty_apply(int n_pen, const int32_t* 
     const int32_t* ij = idx + (int64_t)j * 8;
     const double* wj = w + (int64_t)j * 8;
     const double coef = c[j] * wj[s];
-    if (fcol) {
-      double r0 = 0.0, r1 = 0.0, r2 = 0.0;
+    for (int sb = 0; sb < 8; ++sb) {
+      const int b = ij[sb];
+      if (b >= 0 && b <= a) H[(int64_t)a + (int64_t)b * ldh] += coef * wj[sb];
+    }
+  }
+}
+
+//   fcol[:, a] = -sum_j c_j w_ja (W_j x2 - tscale t_j)
+// Eight lanes per row, one slot each: a slot is a chain of four dependent loads
+// (key, penalty, nodes, positions), so a thread that takes a row's slots one
+// after the other is bound by their latency (40 us for 2,688 level-set
+// penalties, 7.4 us so).  The lanes' terms are added in slot order by
+// every lane, which keeps the sum of the serial loop.
+__global__ __launch_bounds__(256) void k_penalty_force(int n_pen, const int32_t* __restrict__ act,
+                                                       const int32_t* __restrict__ rowptr,
+                                                       const int32_t* __restrict__ ent,
+                                                       const int32_t* __restrict__ idx,
+                                                       const double* __restrict__ w,
+                                                       const double* __restrict__ c,
+                                                       const double* __restrict__ t, double tscale,
+                                                       const double* __restrict__ x2, int m,
+                                                       double* fcol) {
+  const int a = (blockIdx.x * blockDim.x + threadIdx.x) >> 3, lane = threadIdx.x & 7;
+  if (a >= m) return;
+  double f0 = 0.0, f1 = 0.0, f2 = 0.0;
+  const int e1 = rowptr[a + 1];
+  for (int e = rowptr[a]; e < e1; e += 8) {
+    double coef = 0.0, r0 = 0.0, r1 = 0.0, r2 = 0.0;
+    if (e + lane < e1) {
+      const int key = ent[e + lane];
+      const int j = act[key >> 3], s = key & 7;
+      const int32_t* ij = idx + (int64_t)j * 8;
+      const double* wj = w + (int64_t)j * 8;
+      int b[8];
+      double ws[8], x[8][3];
+#pragma unroll
       for (int sb = 0; sb < 8; ++sb) {
-        const int b = ij[sb];
-        if (b < 0 || b >= m) continue;
-        const double ws = wj[sb];
-        r0 += ws * x2[b];
-        r1 += ws * x2[m + b];
-        r2 += ws * x2[2 * m + b];
+        b[sb] = ij[sb];
+        ws[sb] = wj[sb];
+      }
+      coef = c[j] * wj[s];
+#pragma unroll
+      for (int sb = 0; sb < 8; ++sb) {
+        const int bb = b[sb] >= 0 && b[sb] < m ? b[sb] : 0;
+        x[sb][0] = x2[bb];
+        x[sb][1] = x2[m + bb];
+        x[sb][2] = x2[2 * m + bb];
+      }
+#pragma unroll
+      for (int sb = 0; sb < 8; ++sb) {
+        if (b[sb] < 0 || b[sb] >= m) continue;
+        r0 += ws[sb] * x[sb][0];
+        r1 += ws[sb] * x[sb][1];
+        r2 += ws[sb] * x[sb][2];
       }
       r0 -= tscale * t[j];
       r1 -= tscale * t[n_pen + j];
       r2 -= tscale * t[2 * n_pen + j];
-      f0 -= coef * r0;
-      f1 -= coef * r1;
-      f2 -= coef * r2;
     }
-    if (H) {
-      for (int sb = 0; sb < 8; ++sb) {
-        const int b = ij[sb];
-        if (b >= 0 && b <= a) H[(int64_t)a + (int64_t)b * ldh] += coef * wj[sb];
-      }
+    const int cnt = min(8, e1 - e);
+    for (int u = 0; u < cnt; ++u) {
+      const double cu = __shfl(coef, u, 8);
+      f0 -= cu * __shfl(r0, u, 8);
+      f1 -= cu * __shfl(r1, u, 8);
+      f2 -= cu * __shfl(r2, u, 8);
     }
   }
-  if (fcol) {
+  if (lane == 0) {
     fcol[a] = f0;
     fcol[m + a] = f1;
     fcol[2 * m + a] = f2;
@@ -735,16 +821,28 @@ __global__ __launch_bounds__(64) void k_penalty_apply(int n_pen, const int32_t* 
 
 void penalty_prepare(int n_pen, int m, const double* c, const int32_t* idx, int32_t* act,
                      int32_t* cnt, int32_t* rowptr, int32_t* cursor, int32_t* ent, hipStream_t st) {
-  k_penalty_prepare<<<1, 1024, 0, st>>>(n_pen, m, c, idx, act, cnt, rowptr, cursor, ent);
+  // the counters in LDS while they fit a third of a compute unit's 160 KB, the
+  // keys beside them as far as 144 KB in all reach (no more than can be there)
+  const int64_t cap = 144 * 1024 / 4;
+  if (m <= cap / 3) {
+    const int ent_cap = (int)std::min<int64_t>(8 * (int64_t)n_pen, cap - m);
+    const size_t bytes = sizeof(int32_t) * (m + (size_t)ent_cap);
+    k_penalty_prepare<true><<<1, 1024, bytes, st>>>(n_pen, m, c, idx, act, cnt, rowptr, cursor, ent,
+                                                    ent_cap);
+  } else {
+    k_penalty_prepare<false><<<1, 1024, 0, st>>>(n_pen, m, c, idx, act, cnt, rowptr, cursor, ent, 0);
+  }
 }
 
 void penalty_apply(int n_pen, const int32_t* act, const int32_t* rowptr, const int32_t* ent,
                    const int32_t* idx, const double* w, const double* c, const double* t,
                    double tscale, const double* x2, int m, double* H, int ldh, double* fcol,
                    hipStream_t st) {
-  if (m > 0)
-    k_penalty_apply<<<grid1(m, 64), 64, 0, st>>>(n_pen, act, rowptr, ent, idx, w, c, t, tscale, x2,
-                                                 m, H, ldh, fcol);
+  if (m <= 0) return;
+  if (fcol)
+    k_penalty_force<<<grid1(8 * (int64_t)m), 256, 0, st>>>(n_pen, act, rowptr, ent, idx, w, c, t, tscale,
+                                                           x2, m, fcol);
+  if (H) k_penalty_matrix<<<grid1(m, 64), 64, 0, st>>>(act, rowptr, ent, idx, w, c, m, H, ldh);
 }
 
 // Sum of squares of each of the three columns of a [3][m], one workgroup per
