@@ -87,6 +87,8 @@ struct CSRBuild {
   std::vector<int64_t> plan_idx;  // position in the plan for each entry
 };
 
+pd_status plan_level_sweeps(pd_ctx* c);
+
 pd_status build_impl(pd_ctx* c, const pd_mesh* M) {
   const int64_t n = M->n_nodes, T = M->n_tets;
   c->n = n;
@@ -591,13 +593,70 @@ pd_status build_impl(pd_ctx* c, const pd_mesh* M) {
   // boxes of the level-set detection's candidates: as many as E_beta has tets
   c->box_len = 12 * ((c->nbeta + 63) / 64);
   CK(c->alloc(&c->d_box, std::max<int64_t>(c->box_len, 1)));
-  CK(c->alloc(&c->d_fhat, 3 * std::max<int64_t>(1, c->n1)));
   CK(c->alloc(&c->d_v, 3 * std::max<int64_t>(1, c->n1)));
-  CK(c->alloc(&c->d_xs, 3 * std::max<int64_t>(1, c->n1)));
-  CK(c->alloc(&c->d_tmp, 3 * std::max<int64_t>(1, c->maxw)));
+  if (K > 0 && c->maxw <= LEVEL_MAX) {
+    CK(plan_level_sweeps(c));
+  } else {
+    CK(c->alloc(&c->d_fhat, 3 * std::max<int64_t>(1, c->n1)));
+    CK(c->alloc(&c->d_xs, 3 * std::max<int64_t>(1, c->n1)));
+    CK(c->alloc(&c->d_tmp, 3 * std::max<int64_t>(1, c->maxw)));
+  }
   CK(c->alloc(&c->d_P, std::max(sweep_workspace(c->maxw), sweep_workspace(m))));
   HIPCK(c, hipStreamSynchronize(c->st));
   return PD_OK;
+}
+
+// Tables, published vectors and tickets of the sweeps that take one launch.
+// A task is a block of rows of a level, or of the region (level K), in the
+// order in which the sweep comes to them.
+pd_status plan_level_sweeps(pd_ctx* c) {
+  const int K = c->K;
+  auto width = [&](int k) { return (int)(c->lev_off[k + 1] - c->lev_off[k]); };
+  for (int d = 0; d < 2; ++d) {
+    const bool fwd = d == 0;
+    std::vector<SweepLevel> lev(K + 1);
+    std::vector<int32_t> task;
+    auto add_tasks = [&](int k, int64_t rows, int per) {
+      for (int64_t b = 0; b * per < rows; ++b) {
+        task.push_back(k);
+        task.push_back((int32_t)b);
+      }
+    };
+    for (int q = 0; q <= K; ++q) {
+      const int k = fwd || q == K ? q : K - 1 - q;
+      add_tasks(k, k == K ? c->m : width(k), level_sweep_rows(k == K));
+      SweepLevel& L = lev[k];
+      L = SweepLevel{0, -1, 0, 0, -1, -1, 0, 0, 0};
+      if (k < K) {
+        L.mat = c->lev_mat_off[k];
+        L.off = c->lev_off[k];
+        L.w = width(k);
+        L.ld = c->ldw[k];
+      }
+      const int p = fwd ? k - 1 : k + 1;               // the level awaited
+      const int g = fwd ? k - 2 : k + 2;
+      if (p >= 0 && p < K) {
+        L.poff = c->lev_off[p];
+        L.pw = width(p);
+      }
+      if (g >= 0 && g < K) L.goff = c->lev_off[g];
+      if (fwd && k > 0) {
+        L.ptr = c->B_ptr_off[k - 1];
+        L.nnz = c->B_nnz_off[k - 1];
+      } else if (!fwd && k < K) {
+        L.ptr = c->Bt_ptr_off[k];
+        L.nnz = c->Bt_nnz_off[k];
+      }
+    }
+    CK(c->upload(&c->d_slev[d], lev));
+    CK(c->upload(&c->d_stask[d], task));
+    c->n_stask[d] = (int)(task.size() / 2);
+    CK(c->alloc(&c->d_spub[d], 6 * c->n1));
+    sentinel_fill(6 * c->n1, c->d_spub[d], c->st);
+  }
+  CK(c->alloc(&c->d_sticket, 2));
+  HIPCK(c, hipMemsetAsync(c->d_sticket, 0, 2 * sizeof(unsigned long long), c->st));
+  return c->check("level sweeps");
 }
 
 pd_status ensure_pen_cap(pd_ctx* c, int32_t n) {
@@ -712,13 +771,42 @@ pd_status pd_time_step_advance(pd_ctx* c, const double* x, double* x_prev, doubl
   return c->check("pd_time_step_advance");
 }
 
+static LevelSweep level_sweep_args(pd_ctx* c, int d, const double* in, int64_t ldi, double* v,
+                                   double* out, int64_t ldo) {
+  LevelSweep a;
+  a.lev = c->d_slev[d];
+  a.task = c->d_stask[d];
+  a.Z = c->d_levmat;
+  a.ptr = d == 0 ? c->d_Bptr : c->d_Btptr;
+  a.col = d == 0 ? c->d_Bcol : c->d_Btcol;
+  a.val = d == 0 ? c->d_Bval : c->d_Btval;
+  a.nodes = c->d_lev_nodes;
+  a.region = c->d_region_ids;
+  a.in = in;
+  a.v = v;
+  a.out = out;
+  a.pub = c->d_spub[d];
+  a.ticket = c->d_sticket + d;
+  a.err = c->d_err;
+  a.n1 = c->n1;
+  a.ldi = ldi;
+  a.ldo = ldo;
+  a.ntask = c->n_stask[d];
+  a.K = c->K;
+  a.m = (int)c->m;
+  return a;
+}
+
 pd_status pd_condense_rhs(pd_ctx* c, const double* f, double* y2) {
   if (bad_ctx(c) || !f || !y2) return PD_ERR_INVALID;
   if (c->broken) return PD_ERR_HIP;
   const int64_t n1 = c->n1, m = c->m;
   PhaseTimer tm(c, PD_PHASE_CONDENSE);
-  if (c->nd) {
-    nd_condense(c, f, y2);
+  if (c->nd || c->n_stask[0] > 0) {
+    if (c->nd)
+      nd_condense(c, f, y2);
+    else
+      level_sweep(level_sweep_args(c, 0, f, c->n, c->d_v, y2, m), (int)c->maxw, true, c->st);
     c->have_condense = true;
     return c->check("pd_condense_rhs");
   }
@@ -749,6 +837,11 @@ pd_status pd_condense_rhs(pd_ctx* c, const double* f, double* y2) {
 // With the nested-dissection factor the interior part runs its sweep instead.
 static void backsub_levels(pd_ctx* c, const double* delta2, double* x, bool zero_w) {
   const int64_t n1 = c->n1, m = c->m;
+  if (c->n_stask[1] > 0) {
+    level_sweep(level_sweep_args(c, 1, delta2, m, zero_w ? nullptr : c->d_v, x, c->n),
+                (int)c->maxw, false, c->st);
+    return;
+  }
   if (c->nd) {
     nd_backsub(c, delta2, x, zero_w);
   } else if (n1 > 0) {

@@ -100,6 +100,34 @@ void sweep_symv(const double* Z, long ldz, int w, const double* x, long ldx, dou
                 hipStream_t st);
 void sweep_assemble(int w, const double* P, const double* base, long ldb, double* out, long ldo,
                     hipStream_t st);
+// All levels of a sweep in one launch, for levels of up to LEVEL_MAX nodes.
+// A level's rows (or, for level K of a forward sweep, the region's), and where
+// its coupling and the vector that it waits for are: offsets into nodes / ptr /
+// val and the published vector, -1 for none.
+constexpr int LEVEL_MAX = 2048;
+struct SweepLevel {
+  long mat, ptr, nnz;                  // Z_k; row pointers and entries of the coupling
+  long off, poff, goff;                // rows; the level awaited; the one awaited before it
+  int w, ld, pw;                       // widths of the level and of the one awaited
+};
+struct LevelSweep {
+  const SweepLevel* lev;
+  const int* task;                     // (level, block) of each ticket
+  const double* Z;
+  const int32_t *ptr, *col;
+  const double* val;
+  const int32_t *nodes, *region;
+  const double* in;                    // forward: f (ldi = nodes); backward: delta2 (ldi = m)
+  double* v;                           // forward: result; backward: added (null: zero)
+  double* out;                         // forward: y2 (ldo = m); backward: x (ldo = nodes)
+  double* pub;                         // two copies of 3 n1 values, filled with the sentinel
+  unsigned long long* ticket;
+  int* err;
+  long n1, ldi, ldo;
+  int ntask, K, m;
+};
+int level_sweep_rows(bool region);     // rows of a task: of a level, of the region
+void level_sweep(const LevelSweep& a, int maxw, bool forward, hipStream_t st);
 
 // FEM / sparse
 void tet_geometry(const double* rest, int64_t n, const int32_t* tets, int64_t T,

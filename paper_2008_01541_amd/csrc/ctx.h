@@ -104,6 +104,11 @@ struct pd_ctx {
   double* d_cgs = nullptr;
   // sweeps
   double *d_fhat = nullptr, *d_v = nullptr, *d_xs = nullptr, *d_tmp = nullptr;
+  pdk::SweepLevel* d_slev[2] = {nullptr, nullptr};   // one-launch sweeps: levels and tasks of
+  int32_t* d_stask[2] = {nullptr, nullptr};     // the forward and the backward one,
+  double* d_spub[2] = {nullptr, nullptr};       // their published vectors (null: one
+  int n_stask[2] = {0, 0};                      // launch per step of a level)
+  unsigned long long* d_sticket = nullptr;
   double* d_ext = nullptr;     // warm start: predicted region increment in FP64
   double dt = 0.0;             // backward-Euler time step (0: quasistatic)
   double mu_p = 0.0, smin = 0.0, smax = 0.0;   // biphasic material (mu_p = 0: corotated)

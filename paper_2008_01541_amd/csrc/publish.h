@@ -25,6 +25,21 @@ __device__ inline void coherent_store(double* p, double v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Publication by value: what a vector holds before its values are published, a
+// signalling NaN, which no arithmetic returns.
+constexpr unsigned long long SENTINEL = 0x7FF0DEAD00000001ull;
+__device__ inline bool is_sentinel(double v) {
+  return __builtin_bit_cast(unsigned long long, v) == SENTINEL;
+}
+
+// Workgroup barrier for data exchanged through LDS only: waits for this
+// wave's LDS operations, not for its global loads and stores in flight (the
+// barrier of __syncthreads also waits for those, which puts the latency of
+// every write-through store of a published value on the chain).
+__device__ inline void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 constexpr long SPIN_LIMIT_DF = 1L << 24;
 
 // Cross-workgroup publication protocol.  Tiles, tile inverses and solve

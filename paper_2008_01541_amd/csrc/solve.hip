@@ -26,11 +26,6 @@ namespace pdk {
 // back into y as it reads y, and sentinel_fill() prepares a vector once.
 
 constexpr long SPIN_LIMIT = 1L << 24;
-constexpr unsigned long long SENTINEL = 0x7FF0DEAD00000001ull;   // signalling NaN
-
-__device__ inline bool is_sentinel(double v) {
-  return __builtin_bit_cast(unsigned long long, v) == SENTINEL;
-}
 
 __global__ void k_sentinel_fill(long n, double* p) {
   const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -38,14 +33,6 @@ __global__ void k_sentinel_fill(long n, double* p) {
 }
 void sentinel_fill(long n, double* p, hipStream_t st) {
   if (n > 0) k_sentinel_fill<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(n, p);
-}
-
-// Workgroup barrier for data exchanged through LDS only: waits for this
-// wave's LDS operations, not for its global loads and stores in flight (the
-// barrier of __syncthreads also waits for those, which puts the latency of
-// every write-through store of a published value on the chain).
-__device__ inline void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // Polls the cnt values v[0 .. cnt - 1] of the three columns (v[c * ldv + e])

@@ -2,7 +2,10 @@
 // breadth-first levels, Z_k = S_k^-1 dense and symmetric, B_k the sparse
 // coupling of level k to level k+1 or to the region).  The level chain is
 // sequential; each level is a dense product with Z_k, the assembly of its
-// result, and a sparse coupling update (csr_spmv3).
+// result, and a sparse coupling update.  Contexts whose levels have at most
+// LEVEL_MAX nodes run a sweep in one launch (k_level_sweep below); wider ones,
+// where the bytes of Z_k outweigh the launches, take the three launches of a
+// level (sweep_symv, sweep_assemble, csr_spmv3).
 //
 // Dense product y = Z_k x with only the lower triangle read: Z_k is stored in
 // full (column-major), but the kernels walk the lower 64 x 64 tiles (I, J),
@@ -15,6 +18,7 @@
 // scheduling.  HBM traffic is half the full matrix.
 #include <algorithm>
 #include "common.h"
+#include "publish.h"
 
 namespace pdk {
 
@@ -175,7 +179,275 @@ __global__ void k_sweep_assemble(int w, int nb, const double* __restrict__ Prow,
   if (live && q == 0) out[(long)v * ldo + g] = base ? base[(long)v * ldb + g] - tot : tot;
 }
 
+
+// ---------------------------------------------------------------------------
+// All levels of a sweep in one launch, for levels of up to LEVEL_MAX nodes.
+//
+// A chain of K levels in separate launches (product, assembly, coupling) is
+// bound by the launches: 12 us a level, of which the bytes of a level of 1,184
+// nodes need 2.  Here a workgroup takes 16 rows of one level, by ticket in the
+// order of the sweep, and hands its 48 values on by value: the vector that a
+// sweep produces holds a sentinel before it (a signalling NaN, which no
+// arithmetic returns), each value is one agent-coherent store, and a workgroup
+// of the next level polls the whole vector of the level before it.  Whatever
+// does not depend on that vector is read before it is awaited: the 16 rows of
+// Z_k (registers, all of them: at most 64 values per thread), the right-hand
+// side, and the first four coupling entries of every row.  What is left on the
+// chain is one hand-off, the coupling product (every workgroup forms the whole
+// operand of its level itself: a second hand-off would take longer), and
+// 16 x w products per column.  The full Z_k is read, twice the bytes of the
+// lower triangle.  A workgroup only waits for lower tickets, whose workgroups
+// are running, so any number of resident workgroups makes progress.
+//
+// The published vectors are kept twice; a launch uses the copy of its parity
+// (from the ticket, so that replays of a captured launch alternate too) and
+// puts the sentinel back into the other.
+constexpr long SWEEP_SPIN_LIMIT = 1L << 22;
+constexpr int LT = 512;                // threads of a workgroup
+constexpr int LB = 16;                 // rows of a task
+
+// NP: pairs of columns per thread (thread t holds row t & 15 and the columns
+// 2 (t / 16 + 32 i) + {0, 1}); levels of up to 64 NP nodes.
+template <int NP, bool FWD>
+__global__ __launch_bounds__(LT, 2) void k_level_sweep(LevelSweep a) {
+  constexpr int S = 64 * NP, RPT = (S + LT - 1) / LT;
+  constexpr int LE = NP > 24 ? 2 : 4;   // coupling entries of a row read ahead (registers)
+  __shared__ __attribute__((aligned(16))) double xs[3][S];
+  __shared__ double red[LT / 64][3][LB];
+  __shared__ int s_bad[LT / 64];
+  __shared__ unsigned long long s_tk;
+  const int t = threadIdx.x, wv = t >> 6;
+  if (t == 0) s_tk = atomicAdd(a.ticket, 1ull);
+  lds_barrier();
+  const unsigned long long tk = s_tk;
+  const int epoch = __builtin_amdgcn_readfirstlane((int)((tk / (unsigned)a.ntask) & 1));
+  const int id = __builtin_amdgcn_readfirstlane((int)(tk % (unsigned)a.ntask));
+  double* pub = a.pub + (epoch ? 3L * a.n1 : 0);
+  double* clear = a.pub + (epoch ? 0 : 3L * a.n1);
+  const int k = a.task[2 * id], blk = a.task[2 * id + 1];
+  const bool region = k == a.K;
+  if (!FWD && region) {                 // x2 += delta2
+    const int r = blk * LT + t;
+    if (r < a.m) {
+      const int g = a.region[r];
+      for (int c = 0; c < 3; ++c) a.out[c * a.ldo + g] += a.in[c * a.ldi + r];
+    }
+    return;
+  }
+  const SweepLevel L = a.lev[k];
+  const int r0 = (region ? LT : LB) * blk;
+  const int w = region ? min(LT, a.m - r0) : L.w;      // rows of the operand formed here
+  const int rb = region ? r0 : 0;                      // first of them
+  // ---- everything that does not depend on the level before
+  double z[2 * NP];
+  const int r = t & (LB - 1), cg = t / LB;
+  if (!region) {
+    const double* zp = a.Z + L.mat + r0 + r;           // r0 + r < ld, a multiple of 16
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+      if (64 * i < w) {
+        const int c = 2 * (cg + 32 * i);
+        // columns past the last one re-read it: they meet zeros of the operand
+        z[2 * i] = zp[(long)min(c, w - 1) * L.ld];
+        z[2 * i + 1] = zp[(long)min(c + 1, w - 1) * L.ld];
+      }
+    if (t < 3 * LB && r0 + r < w)
+      clear[(long)cg * a.n1 + L.off + r0 + r] = __builtin_bit_cast(double, SENTINEL);
+  }
+  double b[RPT][3], cv[RPT][LE];
+  int es[RPT], ee[RPT], cc[RPT][LE];
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    const int row = t + LT * i;
+    es[i] = ee[i] = 0;
+    b[i][0] = b[i][1] = b[i][2] = 0.0;
+    if (row < w) {
+      if (L.ptr >= 0) {
+        es[i] = a.ptr[L.ptr + rb + row];
+        ee[i] = a.ptr[L.ptr + rb + row + 1];
+      }
+      if (FWD) {
+        const int g = region ? a.region[rb + row] : a.nodes[L.off + row];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) b[i][c] = a.in[c * a.ldi + g];
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < RPT; ++i)
+#pragma unroll
+    for (int j = 0; j < LE; ++j) {
+      cv[i][j] = 0.0;
+      cc[i][j] = 0;
+      if (es[i] + j < ee[i]) {
+        cv[i][j] = a.val[L.nnz + es[i] + j];
+        cc[i][j] = a.col[L.nnz + es[i] + j];
+      }
+    }
+  double vown = 0.0;
+  if (!FWD && a.v && t < 3 * LB && r0 + r < w) vown = a.v[(long)cg * a.n1 + L.off + r0 + r];
+  // ---- the level before: nothing (first of a forward sweep), the caller's
+  // region vector (first of a backward one), or the published vector
+  const bool polled = L.poff >= 0;
+  if (polled) {
+    bool bad = false;
+    // far from its turn, a workgroup polls one value of the level before that
+    if (L.goff >= 0) {
+      long spins = 0;
+      while (is_sentinel(coherent_load(&pub[L.goff]))) {
+        __builtin_amdgcn_s_sleep(8);
+        if (++spins > SWEEP_SPIN_LIMIT ||
+            __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+          bad = true;
+          break;
+        }
+      }
+    }
+    double pv[RPT][3];
+#pragma unroll
+    for (int i = 0; i < RPT; ++i)
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        pv[i][c] = t + LT * i < L.pw ? __builtin_bit_cast(double, SENTINEL) : 0.0;
+    for (long spins = 0; !bad; ++spins) {
+      int miss = 0;
+#pragma unroll
+      for (int i = 0; i < RPT; ++i)
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+          if (is_sentinel(pv[i][c])) pv[i][c] = coherent_load(&pub[(long)c * a.n1 + L.poff + t + LT * i]);
+#pragma unroll
+      for (int i = 0; i < RPT; ++i)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) miss |= is_sentinel(pv[i][c]) ? 1 : 0;
+      if (__ballot(miss) == 0) break;
+      if (spins > SWEEP_SPIN_LIMIT ||
+          __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
+        bad = true;
+    }
+    if ((t & 63) == 0) s_bad[wv] = bad ? 1 : 0;
+#pragma unroll
+    for (int i = 0; i < RPT; ++i)
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (t + LT * i < S) xs[c][t + LT * i] = pv[i][c];
+    lds_barrier();
+    int any = 0;
+#pragma unroll
+    for (int q = 0; q < LT / 64; ++q) any |= s_bad[q];
+    if (any) {
+      if (t == 0) atomicExch(a.err, 1);
+      return;
+    }
+  }
+  // ---- operand of this level: f - B v (forward) or B^T x (backward)
+  const double* src = polled ? &xs[0][0] : a.in;
+  const long lds = polled ? S : a.ldi;
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+    if (polled) {
+#pragma unroll
+      for (int j = 0; j < LE; ++j) {
+        s0 += cv[i][j] * xs[0][cc[i][j]];
+        s1 += cv[i][j] * xs[1][cc[i][j]];
+        s2 += cv[i][j] * xs[2][cc[i][j]];
+      }
+      for (int e = es[i] + LE; e < ee[i]; ++e) {
+        const double v = a.val[L.nnz + e];
+        const int c = a.col[L.nnz + e];
+        s0 += v * xs[0][c];
+        s1 += v * xs[1][c];
+        s2 += v * xs[2][c];
+      }
+    } else {
+      for (int e = es[i]; e < ee[i]; ++e) {
+        const double v = a.val[L.nnz + e];
+        const long c = a.col[L.nnz + e];
+        s0 += v * src[c];
+        s1 += v * src[lds + c];
+        s2 += v * src[2 * lds + c];
+      }
+    }
+    b[i][0] = FWD ? b[i][0] - s0 : s0;
+    b[i][1] = FWD ? b[i][1] - s1 : s1;
+    b[i][2] = FWD ? b[i][2] - s2 : s2;
+  }
+  if (region) {                         // y2 = f2 - B v
+    if (t < w)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) a.out[c * a.ldo + rb + t] = b[0][c];
+    return;
+  }
+  lds_barrier();
+#pragma unroll
+  for (int i = 0; i < RPT; ++i)
+    if (t + LT * i < S)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) xs[c][t + LT * i] = b[i][c];
+  lds_barrier();
+  // ---- the 16 rows of Z times the operand
+  double s[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int i = 0; i < NP; ++i)
+    if (64 * i < w) {
+      const int c = 2 * (cg + 32 * i);
+#pragma unroll
+      for (int v = 0; v < 3; ++v) {
+        const double2 x2 = *reinterpret_cast<const double2*>(&xs[v][c]);
+        s[v] += z[2 * i] * x2.x;
+        s[v] += z[2 * i + 1] * x2.y;
+      }
+    }
+#pragma unroll
+  for (int v = 0; v < 3; ++v) {
+    s[v] += __shfl_xor(s[v], 16, 64);
+    s[v] += __shfl_xor(s[v], 32, 64);
+    if ((t & 63) < LB) red[wv][v][r] = s[v];
+  }
+  lds_barrier();
+  if (t < 3 * LB && r0 + r < w) {
+    double y = red[0][cg][r];
+#pragma unroll
+    for (int q = 1; q < LT / 64; ++q) y += red[q][cg][r];
+    if (!FWD) y = vown - y;
+    const long e = (long)cg * a.n1 + L.off + r0 + r;
+    coherent_store(&pub[e], y);
+    if (FWD)
+      a.v[e] = y;
+    else
+      a.out[cg * a.ldo + a.nodes[L.off + r0 + r]] += y;
+  }
+}
+
+template <bool FWD>
+void launch_level_sweep(const LevelSweep& a, int maxw, hipStream_t st) {
+  const dim3 g((unsigned)a.ntask);
+  if (maxw <= 128)
+    k_level_sweep<2, FWD><<<g, LT, 0, st>>>(a);
+  else if (maxw <= 256)
+    k_level_sweep<4, FWD><<<g, LT, 0, st>>>(a);
+  else if (maxw <= 512)
+    k_level_sweep<8, FWD><<<g, LT, 0, st>>>(a);
+  else if (maxw <= 1024)
+    k_level_sweep<16, FWD><<<g, LT, 0, st>>>(a);
+  else if (maxw <= 1536)
+    k_level_sweep<24, FWD><<<g, LT, 0, st>>>(a);
+  else
+    k_level_sweep<32, FWD><<<g, LT, 0, st>>>(a);
+}
+
 }  // namespace
+
+void level_sweep(const LevelSweep& a, int maxw, bool forward, hipStream_t st) {
+  if (a.ntask <= 0) return;
+  if (forward)
+    launch_level_sweep<true>(a, maxw, st);
+  else
+    launch_level_sweep<false>(a, maxw, st);
+}
+
+int level_sweep_rows(bool region) { return region ? LT : LB; }
 
 int64_t sweep_workspace(int64_t maxw) {
   const int64_t nb = (maxw + TS - 1) / TS;
