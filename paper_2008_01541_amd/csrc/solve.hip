@@ -35,82 +35,6 @@ void sentinel_fill(long n, double* p, hipStream_t st) {
   if (n > 0) k_sentinel_fill<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(n, p);
 }
 
-// Polls the cnt values v[0 .. cnt - 1] of the three columns (v[c * ldv + e])
-// into out[c][e] until none is the sentinel; false (and *err set) after the
-// spin limit or when another workgroup has set *err.  Uniform over the block.
-template <int CAP>
-__device__ inline bool poll_block(const double* v, int ldv, int cnt, double (*out)[CAP],
-                                  int (*s_miss)[4], int* err) {
-  const int t = threadIdx.x;
-  long spins = 0;
-  for (int it = 0;; it ^= 1) {
-    int miss = 0;
-    for (int e = t; e < 3 * CAP; e += 256) {
-      const int c = e / CAP, cc = e - c * CAP;
-      double val = 0.0;
-      if (cc < cnt) {
-        val = coherent_load(&v[(long)c * ldv + cc]);
-        miss |= is_sentinel(val) ? 1 : 0;
-      }
-      out[c][cc] = val;
-    }
-    // one slot per wave, two sets used alternately so that a slot is not
-    // rewritten before every wave has read it
-    const bool wmiss = __ballot(miss) != 0;
-    if ((t & 63) == 0) s_miss[it][t >> 6] = wmiss ? 1 : 0;
-    lds_barrier();
-    if (!(s_miss[it][0] | s_miss[it][1] | s_miss[it][2] | s_miss[it][3])) return true;
-    if (++spins > SPIN_LIMIT ||
-        __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-      if (t == 0) atomicExch(err, 1);
-      return false;
-    }
-    __builtin_amdgcn_s_sleep(1);
-  }
-}
-
-// Two tile rows per workgroup ("super-row" s: tile rows TR s and TR s + 1), so
-// that one cross-workgroup hand-off covers 128 rows of the solve.  Thread
-// t works on row r = t & 63 of a tile and on the 16 columns cg = t >> 6 of it;
-// the four column groups are added through LDS.
-constexpr int TR = 2;
-
-// sums the four column-group partials of part (3 x 64 per group) into out[v][rr]
-// = base[v][rr] - sum; base may be null (then out = sum).
-// out[v][rr] = b - (sum of the four column-group partials of part) for
-// thread t = 64 v + rr < 192, b = this thread's right-hand-side value.
-__device__ inline void trsv_reduce(double (*part)[3][NB], double b, double (*out)[NB]) {
-  const int t = threadIdx.x;
-  if (t < 3 * NB) {
-    const int v = t >> 6, rr = t & 63;
-    const double sum = part[0][v][rr] + part[1][v][rr] + part[2][v][rr] + part[3][v][rr];
-    out[v][rr] = b - sum;
-  }
-}
-
-// The right-hand-side values of the TR tile rows from i0 on, one per thread
-// t = 64 v + rr < 192 (rows past n: 0), read at the start so that their
-// latency is off the chain; fill (may alias base) gets the sentinel at each
-// value once it is read, by the thread that read it.
-template <int R>
-__device__ inline void load_rhs(const double* base, int ldb, int i0, int nu, int n, double* fill,
-                                int ldf, double (&b)[R]) {
-  const int t = threadIdx.x;
-#pragma unroll
-  for (int u = 0; u < R; ++u) b[u] = 0.0;
-  if (t < 3 * NB) {
-    const int v = t >> 6, rr = t & 63;
-#pragma unroll
-    for (int u = 0; u < R; ++u) {
-      const int row = (i0 + u) * NB + rr;
-      if (u < nu && row < n) {
-        b[u] = base[(long)v * ldb + row];
-        if (fill) fill[(long)v * ldf + row] = __builtin_bit_cast(double, SENTINEL);
-      }
-    }
-  }
-}
-
 // Loads of a column panel of a column-major matrix through a buffer
 // descriptor: the row goes in the lane offset, the column (relative to the
 // panel's first one) in the scalar offset, so that a load needs no 64-bit
@@ -136,299 +60,269 @@ __device__ inline float panel_load<float>(__amdgpu_buffer_rsrc_t rs, int voff, i
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff, 0));
 }
 
-// L y = g.  Tile row i: y_i = Linv_ii (g_i - sum_{p<i} L_ip y_p).
+// Forward: L y = g.  Backward: L^T x = y, with L^T read from the upper triangle
+// (U(r, c) = L(c, r)), super-rows from the bottom.  A super-row of 128 rows is
+// two tile rows i0, i0 + 1, and each workgroup finishes one:
+//   y = D^-1 (g - sum over the finished super-rows),
+//   D^-1 = [ A 0 ; V B ],  A = Linv_i0, B = Linv_i0+1, V = -B L_i0+1,i0 A
+// (transposed in the backward solve).  The chain of super-rows bounds the
+// solve (the factor is read at 1.7 TB/s at n = 12,155), so what one hand-off
+// costs is what counts: the publication (a store and a poll through memory,
+// about 1.5 us), the product with the 128 values awaited, and D^-1.  V makes the
+// latter one product instead of one per tile row with the coupling between
+// them, at the price of two 64^3 products before the first wait; the super-row
+// at the head of the chain, which waits for nothing, goes tile row by tile row
+// instead.  A wave polls just the 16 columns that it multiplies, so the
+// product needs no barrier; 512 threads, since a second wave per SIMD hides
+// the LDS latencies of the first.  Against 256 threads, a poll of the whole
+// workgroup and a product per tile row: 485 -> 350 us at n = 12,155 (5.1 -> 3.7
+// per super-row), 82 -> 58 at 2,368, float factor at 4,410 158 -> 103 (backward)
+// and 139 -> 101 (forward).
+//
 // With fflags, the factor is still being computed by a dataflow Cholesky
 // launch on another stream (its tile flags and its ticket[2], whose epoch
 // ticket[1] that launch uses): each super-row first waits until the diagonal
 // tile of its last row is published, which implies that every tile of its
 // rows and both tile inverses are final.
-template <typename T>
-__global__ __launch_bounds__(256, 2) void k_trsv3_fwd(const T* __restrict__ L, int ld, int n,
-                                                   int nt, const T* __restrict__ linv,
-                                                   const double* g, int ldg,
-                                                   double* y, int ldy,
-                                                   unsigned long long* ticket, int* err,
-                                                   const int* fflags, const unsigned* fticket,
-                                                   double* xfill, int ldxf) {
-  __shared__ int s_row, s_ok;
-  __shared__ double Ls[TR][NB][NB + 1];     // Ls[u][c][r] = Linv_{i_u}(r, c)
-  __shared__ double ys[3][TR * NB];         // y of a finished super-row / of this one
-  __shared__ int s_miss[2][4];
-  __shared__ double part[4][3][NB];
-  __shared__ double zs[3][NB];
-  const int t = threadIdx.x;
-  const int ns = (nt + TR - 1) / TR;
+//
+// fill (may alias rhs) gets the sentinel at each right-hand-side value once it
+// is read.
+constexpr int SR = 2 * NB;               // rows of a super-row
+constexpr int TT = 512;                  // threads; thread t: rows t & 63 of both tiles,
+constexpr int CG = 8;                    // columns 8 (t / 64) .. + 7 of each tile
+
+// One wave's two 16 x 16 tiles (row block wv / 2) of the product X Y of two
+// 64 x 64 matrices in LDS, X(r, k) = xm[k][r] and Y(k, c) = ym[c][k].
+__device__ inline void mul64(const double (*xm)[NB + 1], const double (*ym)[NB + 1], int wv,
+                             int lane, double4_t (&acc)[2]) {
+  const int rr = 16 * (wv >> 1) + (lane & 15), c0 = 32 * (wv & 1) + (lane & 15);
+  acc[0] = acc[1] = double4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int ks = 0; ks < NB; ks += 4) {
+    const int k = ks + (lane >> 4);
+    const double x = xm[k][rr];
+    acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ym[c0][k], x, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ym[c0 + 16][k], x, acc[1], 0, 0, 0);
+  }
+}
+// m[c][r] = sign times the product above.
+__device__ inline void put64(double (*m)[NB + 1], int wv, int lane, double sign,
+                             const double4_t (&acc)[2]) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      m[32 * (wv & 1) + 16 * h + (lane >> 4) + 4 * q][16 * (wv >> 1) + (lane & 15)] =
+          sign * acc[h][q];
+}
+
+// s[v] += sum_c l[c] x[v][c], c = 0 .. 7, x in LDS (16-byte aligned).
+__device__ inline void dot8(const double (&l)[CG], const double (*x)[SR], int c0, double (&s)[3]) {
+#pragma unroll
+  for (int v = 0; v < 3; ++v)
+#pragma unroll
+    for (int c = 0; c < CG; c += 2) {
+      const double2 w = *reinterpret_cast<const double2*>(&x[v][c0 + c]);
+      s[v] += l[c] * w.x;
+      s[v] += l[c + 1] * w.y;
+    }
+}
+
+template <typename T, bool FWD>
+__global__ __launch_bounds__(TT, 2) void k_trsv3(const T* __restrict__ L, int ld, int n, int nt,
+                                                 const T* __restrict__ linv, const double* rhs,
+                                                 int ldr, double* out, int ldo,
+                                                 unsigned long long* ticket, int* err,
+                                                 const int* fflags, const unsigned* fticket,
+                                                 double* fill, int ldf) {
+  __shared__ int s_row, s_bad;
+  __shared__ double m0[NB][NB + 1], m1[NB][NB + 1];    // [column][row]; later partial sums
+  __shared__ __attribute__((aligned(16))) double ys[3][SR];   // values of a finished super-row
+  __shared__ __attribute__((aligned(16))) double zs[3][SR];   // right-hand side less the sums
+  double (*part)[3][SR] = reinterpret_cast<double (*)[3][SR]>(&m0[0][0]);
+  static_assert(sizeof(double) * CG * 3 * SR <= sizeof(double) * NB * (NB + 1), "partial sums");
+  const int t = threadIdx.x, lane = t & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int ns = (nt + 1) / 2;
   if (t == 0) {
     const unsigned long long tk = atomicAdd(ticket, 1ull);
-    s_row = (int)(tk % (unsigned long long)ns);
-    s_ok = 1;
+    const int q = (int)(tk % (unsigned long long)ns);
+    s_row = FWD ? q : ns - 1 - q;
+    s_bad = 0;
   }
   lds_barrier();
-  const int sr = s_row;
-  const int r = t & 63, cg = t >> 6;
-  const int cgs = __builtin_amdgcn_readfirstlane(cg);    // cg is uniform per wave
-  const int i0 = TR * sr, nu = min(TR, nt - i0);
-  double rhs[TR];
-  load_rhs<TR>(g, ldg, i0, nu, n, xfill, ldxf, rhs);
+  const int sr = __builtin_amdgcn_readfirstlane(s_row);
+  const int r = lane, c8 = CG * wv;
+  const int i0 = 2 * sr, nu = min(2, nt - i0), row0 = i0 * NB;
+  const bool head = sr == (FWD ? 0 : ns - 1) && nu == 2;
+  // right-hand-side value of thread t = 128 v + row (rows past n: 0)
+  const int rv = t >> 7, rr = t & 127;
+  double b = 0.0;
+  if (t < 3 * SR && row0 + rr < n) {
+    b = rhs[(long)rv * ldr + row0 + rr];
+    if (fill) fill[(long)rv * ldf + row0 + rr] = __builtin_bit_cast(double, SENTINEL);
+  }
   if (fflags) {
     if (t == 0) {
       const int fe = (int)__hip_atomic_load(&fticket[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const int il = i0 + nu - 1;
-      if (!df_wait(&fflags[il * nt + il], fe, err)) s_ok = 0;
+      if (!df_wait(&fflags[il * nt + il], fe, err)) s_bad = 1;
     }
     lds_barrier();
-    if (!s_ok) return;
+    if (s_bad) return;
   }
-  for (int u = 0; u < nu; ++u) {
-    const T* Li = linv + (long)(i0 + u) * NB * NB;
-    double v16[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) v16[q] = Li[t + 256 * q];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) Ls[u][(t >> 6) + 4 * q][t & 63] = v16[q];
-  }
-  // the coupling tile L_{i0+1, i0} (this thread's row and 16 columns), read
-  // now so that its latency is off the path when the super-row finishes
-  static_assert(TR == 2, "the coupling prefetch assumes two tile rows per super-row");
-  T lc[16];
+  // ---- the tile inverses and the coupling tile; element e = t + 512 q of a tile
+  double va[CG], vb[CG], vc[CG];
   {
-    const int r1 = (i0 + 1) * NB + r;
-    const bool ok = nu > 1 && r1 < n;
-    const T* Lr = ok ? L + r1 + (long)(i0 * NB + cg * 16) * ld : L;
-    const long cs = ok ? (long)ld : 0;
+    const T* La = linv + (long)i0 * NB * NB;
+    const T* Lb = linv + (long)(i0 + nu - 1) * NB * NB;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) lc[c] = Lr[c * cs] * (ok ? T(1) : T(0));
+    for (int q = 0; q < CG; ++q) {
+      va[q] = La[t + TT * q];
+      vb[q] = Lb[t + TT * q];
+      // L_i0+1,i0(e) (forward) or its transpose from the upper triangle; what
+      // lies past the edge re-reads the last row or column and is masked
+      const int er = lane, ec = wv + CG * q;
+      const int lr = row0 + (FWD ? NB : 0) + er, lc = row0 + (FWD ? 0 : NB) + ec;
+      const double ok = (nu == 2 && lr < n && lc < n) ? 1.0 : 0.0;
+      vc[q] = (double)L[min(lr, n - 1) + (long)min(lc, n - 1) * ld] * ok;
+    }
   }
-  double acc[TR][3];
 #pragma unroll
-  for (int u = 0; u < TR; ++u) acc[u][0] = acc[u][1] = acc[u][2] = 0.0;
-  for (int q = 0; q < sr; ++q) {
-    // the four operand tiles L_{i_u, TR q + u'} (16 columns each) load while the flag is awaited
-    // unconditional loads from a clamped row, then a select: no branch per
-    // load, so all of them are in flight together
-    // (rows past the edge re-read row 0 and are masked by a multiply, so no
-    // load is put under a branch)
-    T lv[TR][TR][16];
-    const __amdgpu_buffer_rsrc_t prs = panel_rsrc(L, ld, TR * q * NB, TR * NB);
-#pragma unroll
-    for (int u = 0; u < TR; ++u) {
-      const int ru = (i0 + u) * NB + r;
-      const bool ok = u < nu && ru < n;
-      const int voff = (ok ? ru : 0) * (int)sizeof(T);
-#pragma unroll
-      for (int w = 0; w < TR; ++w)
-#pragma unroll
-        for (int c = 0; c < 16; ++c)
-          lv[u][w][c] = panel_load<T>(prs, voff, (w * NB + cgs * 16 + c) * ld * (int)sizeof(T)) *
-                        (ok ? T(1) : T(0));
-    }
-    if (!poll_block<TR * NB>(y + (long)TR * q * NB, ldy, TR * NB, ys, s_miss, err)) return;
-    // each operand of ys is read once and used for every tile row; four
-    // columns at a time, so that the operands are not all held at once
-#pragma unroll
-    for (int w = 0; w < TR; ++w)
-#pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        const int col = w * NB + cg * 16 + c;
-        const double y0 = ys[0][col], y1 = ys[1][col], y2 = ys[2][col];
-#pragma unroll
-        for (int u = 0; u < TR; ++u) {
-          acc[u][0] += (double)lv[u][w][c] * y0;
-          acc[u][1] += (double)lv[u][w][c] * y1;
-          acc[u][2] += (double)lv[u][w][c] * y2;
-        }
-        if ((c & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-      }
-    lds_barrier();
-  }
-  // finish the tile rows of this super-row in order (unrolled, so that the
-  // accumulators acc[u] are indexed at compile time, not through register
-  // indexing)
-#pragma unroll
-  for (int u = 0; u < TR; ++u) {
-    if (u >= nu) break;
-    const int i = i0 + u, r0 = i * NB, mr = min(NB, n - r0);
-    if (u > 0) {           // coupling to the row finished above in this super-row
-#pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        const int col = cg * 16 + c;
-        const double l = (double)lc[c];
-        acc[u][0] += l * ys[0][col];
-        acc[u][1] += l * ys[1][col];
-        acc[u][2] += l * ys[2][col];
-      }
-    }
-    part[cg][0][r] = acc[u][0];
-    part[cg][1][r] = acc[u][1];
-    part[cg][2][r] = acc[u][2];
-    lds_barrier();
-    trsv_reduce(part, rhs[u], zs);                      // zs = g_i - sum
-    lds_barrier();
-    // y_i = Linv_ii zs: column group cg adds columns 16 cg .. 16 cg + 15
-    {
-      double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-#pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        const int col = cg * 16 + c;
-        const double l = Ls[u][col][r];
-        s0 += l * zs[0][col];
-        s1 += l * zs[1][col];
-        s2 += l * zs[2][col];
-      }
-      part[cg][0][r] = s0;
-      part[cg][1][r] = s1;
-      part[cg][2][r] = s2;
-    }
-    lds_barrier();
-    if (t < 3 * NB) {
-      const int v = t >> 6, rr = t & 63;
-      const double yv = part[0][v][rr] + part[1][v][rr] + part[2][v][rr] + part[3][v][rr];
-      ys[v][u * NB + rr] = yv;
-      if (rr < mr) coherent_store(&y[(long)v * ldy + r0 + rr], yv);   // published
-    }
-    lds_barrier();
-  }
-}
-
-// L^T x = y, reading L^T from the upper triangle (U(r, c) = L(c, r) for c > r):
-// x_i = Linv_ii^T (y_i - sum_{p>i} U_ip x_p).  Super-rows from the bottom.
-template <typename T>
-__global__ __launch_bounds__(256, 2) void k_trsv3_bwd(const T* __restrict__ L, int ld, int n,
-                                                   int nt, const T* __restrict__ linv,
-                                                   double* y, int ldy,
-                                                   double* x, int ldx,
-                                                   unsigned long long* ticket, int* err) {
-  __shared__ int s_row, s_ok;
-  __shared__ double Ls[TR][NB][NB + 1];     // Ls[u][c][r] = Linv_{i_u}(r, c)
-  __shared__ double xs[3][TR * NB];
-  __shared__ int s_miss[2][4];
-  __shared__ double part[4][3][NB];
-  __shared__ double zs[3][NB];
-  const int t = threadIdx.x;
-  const int ns = (nt + TR - 1) / TR;
-  if (t == 0) {
-    const unsigned long long tk = atomicAdd(ticket, 1ull);
-    s_row = ns - 1 - (int)(tk % (unsigned long long)ns);
-    s_ok = 1;
+  for (int q = 0; q < CG; ++q) {
+    const int ec = wv + CG * q;
+    m0[ec][lane] = va[q];
+    if (FWD) m1[ec][lane] = vc[q];
+    else m1[lane][ec] = vc[q];                  // m1[c][r] = L_i0+1,i0(r, c) in both
   }
   lds_barrier();
-  const int sr = s_row;
-  const int r = t & 63, cg = t >> 6;
-  const int cgs = __builtin_amdgcn_readfirstlane(cg);    // cg is uniform per wave
-  const int i0 = TR * sr, nu = min(TR, nt - i0);
-  double rhs[TR];
-  load_rhs<TR>(y, ldy, i0, nu, n, y, ldy, rhs);        // y refilled with the sentinel
-  for (int u = 0; u < nu; ++u) {
-    const T* Li = linv + (long)(i0 + u) * NB * NB;
-    double v16[16];
+  // fragments: la = A, lb = B, lv = V (the coupling tile for the head), the
+  // transposes in the backward solve
+  double la[CG], lb[CG], lx[CG];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) v16[q] = Li[t + 256 * q];
+  for (int c = 0; c < CG; ++c) la[c] = FWD ? m0[c8 + c][r] : m0[r][c8 + c];
+  double4_t acc4[2];
+  const bool fold = nu == 2 && !head;
+  if (fold) mul64(m1, m0, wv, lane, acc4);      // P = L_i0+1,i0 A
+  lds_barrier();
 #pragma unroll
-    for (int q = 0; q < 16; ++q) Ls[u][(t >> 6) + 4 * q][t & 63] = v16[q];
+  for (int q = 0; q < CG; ++q) m0[wv + CG * q][lane] = vb[q];
+  if (fold) put64(m1, wv, lane, 1.0, acc4);
+  lds_barrier();
+#pragma unroll
+  for (int c = 0; c < CG; ++c) lb[c] = FWD ? m0[c8 + c][r] : m0[r][c8 + c];
+  if (fold) {
+    mul64(m0, m1, wv, lane, acc4);              // V = -B P
+    lds_barrier();
+    put64(m1, wv, lane, -1.0, acc4);
+    lds_barrier();
   }
-  // the coupling tile U_{i0, i0+1} (this thread's row of tile row i0, 16
-  // columns of tile i0 + 1), read now so that its latency is off the path
-  static_assert(TR == 2, "the coupling prefetch assumes two tile rows per super-row");
-  T lc[16];
-  {
-    const int wn = nu > 1 ? min(NB, n - (i0 + 1) * NB) : 0;
-    const int rr0 = i0 * NB + r;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      const int col = cg * 16 + c;
-      const bool ok = col < wn;
-      const T* p = ok ? L + rr0 + (long)((i0 + 1) * NB + col) * ld : L;
-      lc[c] = *p * (ok ? T(1) : T(0));
-    }
-  }
-  double acc[TR][3];
+  for (int c = 0; c < CG; ++c) lx[c] = FWD ? m1[c8 + c][r] : m1[r][c8 + c];
+  // ---- products with the finished super-rows
+  double acc[2][3];
 #pragma unroll
-  for (int u = 0; u < TR; ++u) acc[u][0] = acc[u][1] = acc[u][2] = 0.0;
-  for (int q = ns - 1; q > sr; --q) {
-    T lv[TR][TR][16];
-    const int pc0 = TR * q * NB;
-    const __amdgpu_buffer_rsrc_t prs = panel_rsrc(L, ld, pc0, min(TR * NB, n - pc0));
+  for (int u = 0; u < 2; ++u) acc[u][0] = acc[u][1] = acc[u][2] = 0.0;
+  // this lane's value of the 3 x 16 that the wave polls
+  const int pv = lane >> 4, pc = ((lane >> 3) & 1) * NB + c8 + (lane & 7);
+  bool bad = false;
+  for (int p = 0; p < (FWD ? sr : ns - 1 - sr) && !bad; ++p) {
+    const int q = FWD ? p : ns - 1 - p;
+    const int col0 = q * SR;
+    // both tiles' 16 columns of both tile rows load while the values are awaited
+    // (rows and columns past the edge re-read others and are masked by a
+    // multiply, so that no load is put under a branch)
+    T lv[2][2][CG];
+    const __amdgpu_buffer_rsrc_t prs = panel_rsrc(L, ld, col0, min(SR, n - col0));
 #pragma unroll
-    for (int u = 0; u < TR; ++u) {
-      const int ru = (i0 + u) * NB + r;
+    for (int u = 0; u < 2; ++u) {
+      const int ru = row0 + u * NB + r;
       const bool okr = u < nu && ru < n;
       const int voff = (okr ? ru : 0) * (int)sizeof(T);
 #pragma unroll
-      for (int w = 0; w < TR; ++w)
+      for (int w = 0; w < 2; ++w)
 #pragma unroll
-        for (int c = 0; c < 16; ++c) {
-          const int col = (TR * q + w) * NB + cgs * 16 + c;
-          // columns past the edge re-read the last one; a multiply, not a
-          // select, masks them, so that the load is not put under a branch
-          lv[u][w][c] = panel_load<T>(prs, voff, (min(col, n - 1) - pc0) * ld * (int)sizeof(T)) *
-                        ((okr && col < n) ? T(1) : T(0));
+        for (int c = 0; c < CG; ++c) {
+          const int col = w * NB + c8 + c;
+          const bool ok = okr && (FWD || col0 + col < n);
+          lv[u][w][c] = panel_load<T>(prs, voff, min(col, n - 1 - col0) * ld * (int)sizeof(T)) *
+                        (ok ? T(1) : T(0));
         }
     }
-    const int qn = min(TR * NB, n - TR * q * NB);
-    if (!poll_block<TR * NB>(x + (long)TR * q * NB, ldx, qn, xs, s_miss, err)) return;
-    // each operand of xs is read once and used for every tile row; four
-    // columns at a time, so that the operands are not all held at once
-#pragma unroll
-    for (int w = 0; w < TR; ++w)
-#pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        const int col = w * NB + cg * 16 + c;
-        const double y0 = xs[0][col], y1 = xs[1][col], y2 = xs[2][col];
-#pragma unroll
-        for (int u = 0; u < TR; ++u) {
-          acc[u][0] += (double)lv[u][w][c] * y0;
-          acc[u][1] += (double)lv[u][w][c] * y1;
-          acc[u][2] += (double)lv[u][w][c] * y2;
-        }
-        if ((c & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+    double val = 0.0;
+    long spins = 0;
+    for (;;) {
+      if (pv < 3 && col0 + pc < n) val = coherent_load(&out[(long)pv * ldo + col0 + pc]);
+      if (__ballot(is_sentinel(val)) == 0) break;
+      if (++spins > SPIN_LIMIT ||
+          __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+        bad = true;
+        break;
       }
-    lds_barrier();
+    }
+    // this wave's own columns of ys: only their order within the wave matters
+    if (pv < 3) ys[pv][pc] = val;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int w = 0; w < 2; ++w)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        double l[CG];
+#pragma unroll
+        for (int c = 0; c < CG; ++c) l[c] = (double)lv[u][w][c];
+        dot8(l, ys, w * NB + c8, acc[u]);
+      }
+    __builtin_amdgcn_wave_barrier();
   }
-  // (unrolled, so that the accumulators acc[u] are indexed at compile time)
+  if (bad && lane == 0) {
+    atomicExch(err, 1);
+    s_bad = 1;
+  }
+  lds_barrier();
+  if (s_bad) return;
+  // ---- zs = right-hand side less the sums
 #pragma unroll
-  for (int uu = 0; uu < TR; ++uu) {
-    const int u = TR - 1 - uu;
-    if (u >= nu) continue;
-    const int i = i0 + u, r0 = i * NB, mr = min(NB, n - r0);
-    if (u + 1 < nu) {      // coupling to the row finished below in this super-row
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        const int col = cg * 16 + c;
-        const double l = (double)lc[c];
-        acc[u][0] += l * xs[0][NB + col];
-        acc[u][1] += l * xs[1][NB + col];
-        acc[u][2] += l * xs[2][NB + col];
-      }
-    }
-    part[cg][0][r] = acc[u][0];
-    part[cg][1][r] = acc[u][1];
-    part[cg][2][r] = acc[u][2];
-    lds_barrier();
-    trsv_reduce(part, rhs[u], zs);                      // zs = y_i - sum
-    lds_barrier();
-    // x_i = Linv_ii^T zs: (Linv^T z)(rr) = sum_c Linv(c, rr) z(c) = sum_c Ls[rr][c] z(c);
-    // thread (r, cg) adds c = 16 cg .. 16 cg + 15 for output row r
-    {
-      double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+    for (int v = 0; v < 3; ++v) part[wv][v][u * NB + r] = acc[u][v];
+  auto total = [&]() {
+    double y = part[0][rv][rr];
 #pragma unroll
-      for (int c = 0; c < 16; ++c) {
-        const int col = cg * 16 + c;
-        const double l = Ls[u][r][col];
-        s0 += l * zs[0][col];
-        s1 += l * zs[1][col];
-        s2 += l * zs[2][col];
-      }
-      part[cg][0][r] = s0;
-      part[cg][1][r] = s1;
-      part[cg][2][r] = s2;
-    }
+    for (int q = 1; q < CG; ++q) y += part[q][rv][rr];
+    return y;
+  };
+  lds_barrier();
+  if (t < 3 * SR) zs[rv][rr] = b - total();
+  lds_barrier();
+  // ---- D^-1 zs: the head's first tile row (h = 0), then its second, less the
+  // coupling; every other super-row in one product
+  const int first = FWD ? 0 : 1;
+  for (int h = 0; h < (head ? 2 : 1); ++h) {
+    double s[2][3];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) s[u][0] = s[u][1] = s[u][2] = 0.0;
+    dot8(la, zs, c8, s[0]);
+    dot8(lb, zs, NB + c8, s[1]);
+    if (!head) dot8(lx, zs, (FWD ? 0 : NB) + c8, s[1 - first]);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 3; ++v) part[wv][v][u * NB + r] = s[u][v];
     lds_barrier();
-    if (t < 3 * NB) {
-      const int v = t >> 6, rr = t & 63;
-      const double xv = part[0][v][rr] + part[1][v][rr] + part[2][v][rr] + part[3][v][rr];
-      xs[v][u * NB + rr] = xv;
-      if (rr < mr) coherent_store(&x[(long)v * ldx + r0 + rr], xv);   // published
+    if (t < 3 * SR) {
+      const double y = total();
+      const bool mine = !head || (rr >> 6) == (h == 0 ? first : 1 - first);
+      if (mine && row0 + rr < n) coherent_store(&out[(long)rv * ldo + row0 + rr], y);
+      ys[rv][rr] = y;
     }
+    if (!head || h == 1) break;
+    lds_barrier();
+    double k[3] = {0.0, 0.0, 0.0};
+    dot8(lx, ys, first * NB + c8, k);
+#pragma unroll
+    for (int v = 0; v < 3; ++v) part[wv][v][(1 - first) * NB + r] = k[v];
+    lds_barrier();
+    if (t < 3 * SR && (rr >> 6) == 1 - first) zs[rv][rr] -= total();
     lds_barrier();
   }
 }
@@ -437,29 +331,31 @@ void trsv3_forward(const double* L, int ld, int n, const double* linv_ws, const 
                    int ldg, double* y, int ldy, unsigned long long* ticket, int* err,
                    double* xfill, int ldxf, hipStream_t st, const int* fflags,
                    const unsigned* fticket) {
-  const int nt = (n + NB - 1) / NB, ns = (nt + TR - 1) / TR;
-  k_trsv3_fwd<double><<<ns, 256, 0, st>>>(L, ld, n, nt, linv_ws, g, ldg, y, ldy, ticket, err,
-                                          fflags, fticket, xfill, ldxf);
+  const int nt = (n + NB - 1) / NB, ns = (nt + 1) / 2;
+  k_trsv3<double, true><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, g, ldg, y, ldy, ticket, err,
+                                           fflags, fticket, xfill, ldxf);
 }
 
 void trsv3_backward(const double* L, int ld, int n, const double* linv_ws, double* y, int ldy,
                     double* x, int ldx, unsigned long long* ticket, int* err, hipStream_t st) {
-  const int nt = (n + NB - 1) / NB, ns = (nt + TR - 1) / TR;
-  k_trsv3_bwd<double><<<ns, 256, 0, st>>>(L, ld, n, nt, linv_ws, y, ldy, x, ldx, ticket, err);
+  const int nt = (n + NB - 1) / NB, ns = (nt + 1) / 2;
+  k_trsv3<double, false><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, y, ldy, x, ldx, ticket, err,
+                                            nullptr, nullptr, y, ldy);
 }
 
 // The same solves with a float factor (FP64 vectors and arithmetic).
 void trsv3_forward(const float* L, int ld, int n, const float* linv_ws, const double* g, int ldg,
                    double* y, int ldy, unsigned long long* ticket, int* err, double* xfill,
                    int ldxf, hipStream_t st) {
-  const int nt = (n + NB - 1) / NB, ns = (nt + TR - 1) / TR;
-  k_trsv3_fwd<float><<<ns, 256, 0, st>>>(L, ld, n, nt, linv_ws, g, ldg, y, ldy, ticket, err,
-                                         nullptr, nullptr, xfill, ldxf);
+  const int nt = (n + NB - 1) / NB, ns = (nt + 1) / 2;
+  k_trsv3<float, true><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, g, ldg, y, ldy, ticket, err,
+                                          nullptr, nullptr, xfill, ldxf);
 }
 void trsv3_backward(const float* L, int ld, int n, const float* linv_ws, double* y, int ldy,
                     double* x, int ldx, unsigned long long* ticket, int* err, hipStream_t st) {
-  const int nt = (n + NB - 1) / NB, ns = (nt + TR - 1) / TR;
-  k_trsv3_bwd<float><<<ns, 256, 0, st>>>(L, ld, n, nt, linv_ws, y, ldy, x, ldx, ticket, err);
+  const int nt = (n + NB - 1) / NB, ns = (nt + 1) / 2;
+  k_trsv3<float, false><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, y, ldy, x, ldx, ticket, err,
+                                           nullptr, nullptr, y, ldy);
 }
 
 }  // namespace pdk

@@ -202,6 +202,12 @@ __global__ void k_sweep_assemble(int w, int nb, const double* __restrict__ Prow,
 // The published vectors are kept twice; a launch uses the copy of its parity
 // (from the ticket, so that replays of a captured launch alternate too) and
 // puts the sentinel back into the other.
+//
+// Local step and both sweeps, three launches a level against this kernel: 441
+// nodes a level (20 x 20 x 12 cells) 257 -> 95 us, 841 (x 16) 349 -> 156, 1,369
+// (x 16) 397 -> 241, 1,560 (x 20) 555 -> 362, 2,025 (x 20) 601 -> 485.  Past 1,024
+// nodes the full Z_k bounds it (2.3 TB/s); the gain runs out near 2,400, and
+// at LEVEL_MAX a thread's 64 values of Z_k still fit its registers.
 constexpr long SWEEP_SPIN_LIMIT = 1L << 22;
 constexpr int LT = 512;                // threads of a workgroup
 constexpr int LB = 16;                 // rows of a task
