@@ -1135,37 +1135,36 @@ pd_status pd_global_solve(pd_ctx* c, const double* g, double* u, pd_precision pr
   if (c->broken) return PD_ERR_HIP;
   const int m = (int)c->m;
   if (prec == PD_FP64) {
-    bool fused = false;
-    if (c->stale) {
+    const bool fused = c->stale;      // the forward substitution inside the factorization
+    if (fused) {
       build_H(c);
-      zero_int(c->d_info, c->st);
-      fused = true;
-      if (fused) rhs_pack(m, g, m, c->d_Yt, c->st);
+      rhs_pack(m, g, m, c->d_Yt, u, c->d_info, c->d_tticket, c->st);
       PhaseTimer tm(c, PD_PHASE_FACTOR);
-      cholesky(c, c->d_H, c->ldH, m, fused ? c->d_Yt : nullptr);
+      cholesky(c, c->d_H, c->ldH, m, c->d_Yt);
       c->stale = false;
       c->lp_stale = true;       // d_H was rebuilt
     }
     {
       PhaseTimer tmsolve(c, PD_PHASE_SOLVE);
       if (fused) {
-        // the forward substitution ran inside the factorization
-        rhs_unpack(m, c->d_Yt, c->d_ys, m, c->st);
-        sentinel_fill(3 * m, u, c->st);     // the backward solve publishes u by value
-      } else if (c->overlap) {
-        // the factorization may still run on another stream: the forward
-        // solve follows its tile flags, the backward one waits for its end
-        HIPCK(c, hipStreamWaitEvent(c->st, c->ev_fstart, 0));
-        trsv3_forward(c->d_H, c->ldH, m, c->d_linv, g, m, c->d_ys, m, c->d_ticket, c->d_err, u, m,
-                      c->st, c->d_tflags, c->d_tticket);
-        HIPCK(c, hipStreamWaitEvent(c->st, c->ev_fdone, 0));
-        c->overlap = false;
+        trsv3_backward_packed(c->d_H, c->ldH, m, c->d_linv, c->d_Yt, u, m, c->d_ticket + 1, c->d_err,
+                              c->st);
       } else {
-        trsv3_forward(c->d_H, c->ldH, m, c->d_linv, g, m, c->d_ys, m, c->d_ticket, c->d_err, u, m,
-                      c->st);
+        if (c->overlap) {
+          // the factorization may still run on another stream: the forward
+          // solve follows its tile flags, the backward one waits for its end
+          HIPCK(c, hipStreamWaitEvent(c->st, c->ev_fstart, 0));
+          trsv3_forward(c->d_H, c->ldH, m, c->d_linv, g, m, c->d_ys, m, c->d_ticket, c->d_err, u, m,
+                        c->st, c->d_tflags, c->d_tticket);
+          HIPCK(c, hipStreamWaitEvent(c->st, c->ev_fdone, 0));
+          c->overlap = false;
+        } else {
+          trsv3_forward(c->d_H, c->ldH, m, c->d_linv, g, m, c->d_ys, m, c->d_ticket, c->d_err, u, m,
+                        c->st);
+        }
+        trsv3_backward(c->d_H, c->ldH, m, c->d_linv, c->d_ys, m, u, m, c->d_ticket + 1, c->d_err,
+                       c->st);
       }
-      trsv3_backward(c->d_H, c->ldH, m, c->d_linv, c->d_ys, m, u, m, c->d_ticket + 1, c->d_err,
-                     c->st);
     }
     CK(c->check("pd_global_solve"));
     if (info) {

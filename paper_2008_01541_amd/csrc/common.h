@@ -33,8 +33,10 @@ void potrf_dataflow(double* A, int lda, int n, double* linv_ws, double* sbuf, in
                     int* cu_marks = nullptr,
                     hipEvent_t after_reset = nullptr);
 int potrf_cu_slots();
-void rhs_pack(int n, const double* g, int ldg, double* Yt, hipStream_t st);
-void rhs_unpack(int n, const double* Yt, double* y, int ldy, hipStream_t st);
+// Right-hand side into Yt for a factorization with it (which must follow: the
+// launch epoch is advanced here), the sentinel into fill, *info = 0.
+void rhs_pack(int n, const double* g, int ldg, double* Yt, double* fill, int* info,
+              unsigned* ticket, hipStream_t st);
 // Fill kernels (used instead of memset so the calls can be graph-captured).
 void zero_int(int* p, hipStream_t st);
 void zero_f64(long n, double* p, hipStream_t st);
@@ -57,6 +59,10 @@ void trsv3_forward(const double* L, int ld, int n, const double* linv_ws, const 
                    const unsigned* fticket = nullptr);
 void trsv3_backward(const double* L, int ld, int n, const double* linv_ws, double* y, int ldy,
                     double* x, int ldx, unsigned long long* ticket, int* err, hipStream_t st);
+// the backward solve from the packed y of a factorization with a right-hand side
+void trsv3_backward_packed(const double* L, int ld, int n, const double* linv_ws,
+                           const double* Yt, double* x, int ldx, unsigned long long* ticket,
+                           int* err, hipStream_t st);
 // the same solves with a float factor (FP64 vectors and arithmetic)
 void trsv3_forward(const float* L, int ld, int n, const float* linv_ws, const double* g, int ldg,
                    double* y, int ldy, unsigned long long* ticket, int* err, double* xfill,

@@ -704,7 +704,7 @@ void potrf_dataflow(double* A, int lda, int n, double* linv_ws, double* sbuf, in
   const int nt = (n + NB - 1) / NB;
   const int wide = df64_wide(nt);
   const int ntask = df64_task_count(nt, wide, Yt ? 1 : 0);
-  k_reset_counter<<<1, 1, 0, st>>>(ticket);
+  if (!Yt) k_reset_counter<<<1, 1, 0, st>>>(ticket);     // with Yt: done by rhs_pack
   if (after_reset) (void)hipEventRecord(after_reset, st);
   // two instances: the code of the two-tile task, unused, would cost the
   // diagonal chain 1.7 us per column through the register allocation
@@ -715,22 +715,27 @@ void potrf_dataflow(double* A, int lda, int n, double* linv_ws, double* sbuf, in
 
 int potrf_cu_slots() { return CU_SLOTS; }
 
-// Yt[v + r * 64] = g[v * ldg + r] (v < 3) and back.
-__global__ void k_rhs_pack(int n, const double* __restrict__ g, int ldg, double* __restrict__ Yt) {
+// Before a factorization that carries its right-hand side: Yt[v + r * 64] =
+// g[v * ldg + r] (v < 3), the sentinel into fill (may alias g) for the solve that
+// follows, the pivot report cleared and the launch epoch advanced.  One launch
+// instead of four (about 2 us each beside a small system).
+__global__ void k_rhs_pack(int n, const double* g, int ldg, double* __restrict__ Yt, double* fill,
+                           int* info, unsigned* ticket) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  if (r == 0) {
+    *info = 0;
+    ticket[0] = 0u;
+    ticket[1] = ticket[1] + 1u;
+  }
   if (r >= n) return;
-  for (int v = 0; v < 3; ++v) Yt[v + (long)r * NB] = g[(long)v * ldg + r];
+  for (int v = 0; v < 3; ++v) {
+    Yt[v + (long)r * NB] = g[(long)v * ldg + r];
+    fill[(long)v * ldg + r] = __builtin_bit_cast(double, SENTINEL);
+  }
 }
-__global__ void k_rhs_unpack(int n, const double* __restrict__ Yt, double* __restrict__ y, int ldy) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= n) return;
-  for (int v = 0; v < 3; ++v) y[(long)v * ldy + r] = Yt[v + (long)r * NB];
-}
-void rhs_pack(int n, const double* g, int ldg, double* Yt, hipStream_t st) {
-  k_rhs_pack<<<(n + 255) / 256, 256, 0, st>>>(n, g, ldg, Yt);
-}
-void rhs_unpack(int n, const double* Yt, double* y, int ldy, hipStream_t st) {
-  k_rhs_unpack<<<(n + 255) / 256, 256, 0, st>>>(n, Yt, y, ldy);
+void rhs_pack(int n, const double* g, int ldg, double* Yt, double* fill, int* info,
+              unsigned* ticket, hipStream_t st) {
+  k_rhs_pack<<<(n + 255) / 256, 256, 0, st>>>(n, g, ldg, Yt, fill, info, ticket);
 }
 
 __global__ void k_copy_f64(long n, const double* __restrict__ src, double* __restrict__ dst) {

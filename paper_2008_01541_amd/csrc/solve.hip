@@ -85,8 +85,8 @@ __device__ inline float panel_load<float>(__amdgpu_buffer_rsrc_t rs, int voff, i
 // tile of its last row is published, which implies that every tile of its
 // rows and both tile inverses are final.
 //
-// fill (may alias rhs) gets the sentinel at each right-hand-side value once it
-// is read.
+// The right-hand side of row i is rhs[v ldr + i rstep]; fill (may alias rhs)
+// gets the sentinel at each value once it is read.
 constexpr int SR = 2 * NB;               // rows of a super-row
 constexpr int TT = 512;                  // threads; thread t: rows t & 63 of both tiles,
 constexpr int CG = 8;                    // columns 8 (t / 64) .. + 7 of each tile
@@ -131,7 +131,7 @@ __device__ inline void dot8(const double (&l)[CG], const double (*x)[SR], int c0
 template <typename T, bool FWD>
 __global__ __launch_bounds__(TT, 2) void k_trsv3(const T* __restrict__ L, int ld, int n, int nt,
                                                  const T* __restrict__ linv, const double* rhs,
-                                                 int ldr, double* out, int ldo,
+                                                 int ldr, int rstep, double* out, int ldo,
                                                  unsigned long long* ticket, int* err,
                                                  const int* fflags, const unsigned* fticket,
                                                  double* fill, int ldf) {
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(TT, 2) void k_trsv3(const T* __restrict__ L, int ld
   const int rv = t >> 7, rr = t & 127;
   double b = 0.0;
   if (t < 3 * SR && row0 + rr < n) {
-    b = rhs[(long)rv * ldr + row0 + rr];
+    b = rhs[(long)rv * ldr + (long)(row0 + rr) * rstep];
     if (fill) fill[(long)rv * ldf + row0 + rr] = __builtin_bit_cast(double, SENTINEL);
   }
   if (fflags) {
@@ -332,15 +332,23 @@ void trsv3_forward(const double* L, int ld, int n, const double* linv_ws, const 
                    double* xfill, int ldxf, hipStream_t st, const int* fflags,
                    const unsigned* fticket) {
   const int nt = (n + NB - 1) / NB, ns = (nt + 1) / 2;
-  k_trsv3<double, true><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, g, ldg, y, ldy, ticket, err,
+  k_trsv3<double, true><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, g, ldg, 1, y, ldy, ticket, err,
                                            fflags, fticket, xfill, ldxf);
 }
 
 void trsv3_backward(const double* L, int ld, int n, const double* linv_ws, double* y, int ldy,
                     double* x, int ldx, unsigned long long* ticket, int* err, hipStream_t st) {
   const int nt = (n + NB - 1) / NB, ns = (nt + 1) / 2;
-  k_trsv3<double, false><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, y, ldy, x, ldx, ticket, err,
+  k_trsv3<double, false><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, y, ldy, 1, x, ldx, ticket, err,
                                             nullptr, nullptr, y, ldy);
+}
+
+void trsv3_backward_packed(const double* L, int ld, int n, const double* linv_ws,
+                           const double* Yt, double* x, int ldx, unsigned long long* ticket,
+                           int* err, hipStream_t st) {
+  const int nt = (n + NB - 1) / NB, ns = (nt + 1) / 2;
+  k_trsv3<double, false><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, Yt, 1, NB, x, ldx, ticket, err,
+                                            nullptr, nullptr, nullptr, 0);
 }
 
 // The same solves with a float factor (FP64 vectors and arithmetic).
@@ -348,13 +356,13 @@ void trsv3_forward(const float* L, int ld, int n, const float* linv_ws, const do
                    double* y, int ldy, unsigned long long* ticket, int* err, double* xfill,
                    int ldxf, hipStream_t st) {
   const int nt = (n + NB - 1) / NB, ns = (nt + 1) / 2;
-  k_trsv3<float, true><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, g, ldg, y, ldy, ticket, err,
+  k_trsv3<float, true><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, g, ldg, 1, y, ldy, ticket, err,
                                           nullptr, nullptr, xfill, ldxf);
 }
 void trsv3_backward(const float* L, int ld, int n, const float* linv_ws, double* y, int ldy,
                     double* x, int ldx, unsigned long long* ticket, int* err, hipStream_t st) {
   const int nt = (n + NB - 1) / NB, ns = (nt + 1) / 2;
-  k_trsv3<float, false><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, y, ldy, x, ldx, ticket, err,
+  k_trsv3<float, false><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, y, ldy, 1, x, ldx, ticket, err,
                                            nullptr, nullptr, y, ldy);
 }
 

@@ -37,3 +37,21 @@ def test_solves_match_oracle(nx, ny, prec):
         ctx.global_solve(dev(g), u, getattr(pd, MODES[prec]))
         want = np.linalg.solve(om.schur(), g.T).T
         assert rel(host(u, (3, -1)), want) <= TOL[prec], f"solve {k}"
+
+
+def test_first_solve_in_place():
+    """The right-hand side is packed for the factorization, and the sentinel of
+    the backward solve put in its place, by one kernel."""
+    import torch
+    sc = P.scene_small(14, 9, 3, h=1.0, region_top_layers=1, seed=4)
+    om = oracle_model(sc)
+    g = np.random.default_rng(6).normal(size=(3, om.i2.size))
+    want = np.linalg.solve(om.schur(), g.T).T
+    ctx = gpu_context(sc)
+    u = dev(g)
+    ctx.global_solve(u, u)
+    assert rel(host(u, (3, -1)), want) <= TOL["fp64"]
+    u = dev(g)
+    ctx.global_solve(u, u)                      # factor kept
+    assert rel(host(u, (3, -1)), want) <= TOL["fp64"]
+    torch.cuda.synchronize()
