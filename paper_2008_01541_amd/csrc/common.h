@@ -230,7 +230,8 @@ void gemm_nt(const double* A, long lda, const double* B, long ldb, double* C, lo
 // One work item of the supernodal sweeps: 4 cpw columns (cpw = 1 or 4 per
 // wave), from col0, of the matrix block at moff (leading dimension ldm,
 // rows x cols); rows below split are dotted with one vector (from xoff), the
-// rest with another (from x2off, subtracted); the results go to yoff + column.
+// rest with the solution at the boundary entries from x2off on (subtracted);
+// the results go to yoff + column.
 struct NdItem {
   int64_t moff;
   int32_t ldm, rows, cols, col0, xoff, yoff, split, x2off, cpw;
@@ -241,10 +242,6 @@ struct NdItem {
 struct alignas(16) NdTarget {
   int32_t node, out, c0, c1;
 };
-// An entry of the boundary gather: boundary entry e and its key.
-struct alignas(8) NdEntry {
-  int32_t e, key;
-};
 // Adds the lower entries (r >= c) of the b x b update matrix U of a child
 // into its parent's front: i = map[r], j = map[c]; j < ns: into the front's
 // first ns columns P (F_ss entries mirrored to the upper triangle), else into
@@ -254,16 +251,15 @@ void nd_extend_add(const double* U, long ldu, int b, const int32_t* map, int ns,
 // dst[v][out] = f[v][node] - sum_{c0 <= e < c1} contrib[v][e] for the cnt targets of trec.
 void nd_gather_rhs(int cnt, const NdTarget* trec, const double* f, long ldf,
                    const double* contrib, long ldc, double* dst, long ldd, hipStream_t st);
-// y = M^T [xa; -xb] per item (see NdItem), three right-hand sides; the result
-// of column index q = yoff + column goes to y[ymap[q]] (ymap may be null: y[q]).
+// y = M^T [xa; -xb] per item (see NdItem), three right-hand sides; xb at boundary
+// entry e is x1[bkey[e]] for a key below n1, else the region's d2[bkey[e] - n1].
+// The result of column index q = yoff + column goes to y[ymap[q]] (ymap may be
+// null: y[q]).
 void nd_gemv(int nitems, const NdItem* items, const double* M, const double* xa, long ldxa,
-             const double* xb, long ldxb, double* y, long ldy, const int32_t* ymap,
-             hipStream_t st);
+             const int32_t* bkey, int n1, const double* x1, int m, const double* d2, double* y,
+             long ldy, const int32_t* ymap, hipStream_t st);
 // dst (cols x rows) = src^T (src rows x cols), column-major.
 void nd_transpose(const double* src, long lds, int rows, int cols, double* dst, long ldd,
                   hipStream_t st);
-// zb[v][e] = key < n1 ? z[v][key] : d2[v][key - n1] for the cnt entries (e, key) of erec.
-void nd_gather_zb(int cnt, const NdEntry* erec, int n1, const double* z, long ldz,
-                  const double* d2, long ldd2, double* zb, long ldzb, hipStream_t st);
 
 }  // namespace pdk

@@ -124,11 +124,10 @@ __device__ inline double nd_wave_sum3(double s0, double s1, double s2, int& idx)
   return x;
 }
 
-// s += sign * sum_{r < n} M[r] x[r] (three columns of x, stride ldx) over
+// s += sum_{r < n} M[r] x[r] (three columns of x, stride ldx) over
 // this lane's rows lane, lane + 64, ...: four rows per step, loads guarded
 // rather than branched around, so that a short column takes one step with
 // all its loads in flight.
-template <int SIGN>
 __device__ __forceinline__ void nd_dot(const double* __restrict__ M, const double* __restrict__ x,
                                        long ldx, int n, double& s0, double& s1, double& s2) {
   const int lane = threadIdx.x & 63;
@@ -145,23 +144,16 @@ __device__ __forceinline__ void nd_dot(const double* __restrict__ M, const doubl
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      if (SIGN > 0) {
-        s0 += m[u] * v0[u];
-        s1 += m[u] * v1[u];
-        s2 += m[u] * v2[u];
-      } else {
-        s0 -= m[u] * v0[u];
-        s1 -= m[u] * v1[u];
-        s2 -= m[u] * v2[u];
-      }
+      s0 += m[u] * v0[u];
+      s1 += m[u] * v1[u];
+      s2 += m[u] * v2[u];
     }
   }
 }
 
-// The same for four columns M, M + ldm, M + 2 ldm, M + 3 ldm at once (nc of
-// them valid): the vector entries are loaded once for the four, two rows
-// per lane and step.
-template <int SIGN>
+// s[c][k] += sum_{r < n} M(r, c) x_k[r] over this lane's rows lane, lane + 64, ... of
+// four columns (nc of them valid), two rows a step, the vector entries loaded once
+// for the four.
 __device__ __forceinline__ void nd_dot4(const double* __restrict__ M, long ldm, int nc,
                                         const double* __restrict__ x, long ldx, int n,
                                         double (&s)[4][3]) {
@@ -183,60 +175,145 @@ __device__ __forceinline__ void nd_dot4(const double* __restrict__ M, long ldm, 
       for (int c = 0; c < 4; ++c)
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-          if (SIGN > 0) s[c][k] += m[u][c] * v[u][k];
-          else s[c][k] -= m[u][c] * v[u][k];
+          s[c][k] += m[u][c] * v[u][k];
         }
   }
 }
 
-// y[q] (q = yoff + c, or ymap[q]) = sum_{r < split} M(r, c) xa[xoff + r] -
-// sum_{split <= r < rows} M(r, c) xb[x2off + r - split] for the columns of an
-// item (three right-hand sides): cpw = 1, one column per wave (columns
-// col0 + w); cpw = 4, four per wave (col0 + 4 w .. + 3), for short columns,
-// whose loads are then shared.  The lanes' sums are added across the wave at
-// the end (fixed order); the storing lanes read their output index first.
-__global__ __launch_bounds__(256) void k_nd_gemv(const NdItem* __restrict__ items,
-                                                 const double* __restrict__ Mb,
-                                                 const double* __restrict__ xa, long ldxa,
-                                                 const double* __restrict__ xb, long ldxb,
-                                                 double* __restrict__ y, long ldy,
-                                                 const int32_t* __restrict__ ymap) {
+// The vector entry that meets row r of an item's columns: xa[xoff + r] for
+// r < split, else minus the solution at boundary entry x2off + r - split: its
+// key below n1 is a position of x1, n1 + i the region's row i of d2.
+struct NdVectors {
+  const double* xa;
+  long ldxa;
+  const int32_t* bkey;
+  const double* x1;
+  const double* d2;
+  int n1, m;
+};
+__device__ __forceinline__ void nd_entry(const NdItem& it, const NdVectors& v, int r,
+                                         double (&x)[3]) {
+  if (r < it.split) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) x[k] = v.xa[k * v.ldxa + it.xoff + r];
+  } else if (r < it.rows) {
+    const int key = v.bkey[it.x2off + r - it.split];
+    const double* p = key < v.n1 ? v.x1 + key : v.d2 + (key - v.n1);
+    const long ld = key < v.n1 ? v.n1 : v.m;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) x[k] = -p[k * ld];
+  } else {
+    x[0] = x[1] = x[2] = 0.0;
+  }
+}
+
+// s[c][k] += sum_r M(r, c) x_k[r] over this lane's rows lane, lane + 64, ... of
+// NC columns (nc of them valid), 64 NR rows a step: a step's entries of the
+// three vectors go through LDS, fetched once for the four waves.
+constexpr int ND_STEP = 256;           // most rows of a step
+template <int NC, int NR>
+__device__ __forceinline__ void nd_columns(const NdItem& it, const double* __restrict__ M, int nc,
+                                           const NdVectors& v, double (*xs)[ND_STEP],
+                                           double (&s)[NC][3]) {
+  constexpr int CH = 64 * NR, NX = CH / 256;
+  const int t = threadIdx.x, lane = t & 63;
+  double m[NC][NR], x[NX][3];
+  auto matrix = [&](int r0) {
+#pragma unroll
+    for (int j = 0; j < NR; ++j)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int r = r0 + lane + 64 * j;
+        m[c][j] = (r < it.rows && c < nc) ? M[(long)c * it.ldm + r] : 0.0;
+      }
+  };
+  auto fetch = [&](int r0) {
+#pragma unroll
+    for (int u = 0; u < NX; ++u) nd_entry(it, v, r0 + t + 256 * u, x[u]);
+  };
+  auto put = [&]() {
+#pragma unroll
+    for (int u = 0; u < NX; ++u)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) xs[k][t + 256 * u] = x[u][k];
+  };
+  for (int r0 = 0; r0 < it.rows; r0 += CH) {
+    fetch(r0);
+    matrix(r0);
+    if (r0 > 0) __syncthreads();
+    put();
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NR; ++j)
+      if (r0 + 64 * j < it.rows) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const double xv = xs[k][lane + 64 * j];
+#pragma unroll
+          for (int c = 0; c < NC; ++c) s[c][k] += m[c][j] * xv;
+        }
+      }
+  }
+}
+
+// y[q] (q = yoff + c, or ymap[q]) = sum_r M(r, c) x[r] for the columns of an item
+// (three right-hand sides): cpw = 1, one column per wave (columns col0 + w); cpw
+// = 4, four per wave (col0 + 4 w .. + 3), for short columns.  The lanes' sums are
+// added across the wave at the end (fixed order).  Bound by the bytes of the
+// factor and, in the upper heights with a few thousand long columns, by the
+// loads in flight.  The backward sweep (FWD = false) reads the boundary values
+// through their keys while a step is staged, instead of from a launch a height
+// that gathers them (5 us each); the forward one, whose columns are mostly less
+// than a step, reads its vector straight from memory (staged, the lower heights
+// took 10.5 -> 20 us).  Local step and both sweeps of the 56 x 56 x 32 slab (1.14
+// GB) 553 -> 507 us.  Waves, not registers, hide the latencies, since the sweeps
+// also run beside a factorization that takes 136 KB of LDS and 368 of the 512
+// registers of a lane: double-buffered steps (128 registers, 12 or 24 KB) are 30
+// us faster alone, but two pipelined iterations took 6.5 to 6.8 ms, not 6.0.
+template <bool FWD>
+__global__ __launch_bounds__(256, FWD ? 6 : 5) void k_nd_gemv(const NdItem* __restrict__ items,
+                                                    const double* __restrict__ Mb, NdVectors vec,
+                                                    double* y, long ldy,
+                                                    const int32_t* __restrict__ ymap) {
+  __shared__ double xs[3][FWD ? 1 : ND_STEP];
   const NdItem it = items[blockIdx.x];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (it.cpw == 1) {
     const int c = it.col0 + w;
-    if (c >= it.cols) return;
+    const bool on = c < it.cols;        // every wave fetches vector entries
     // lanes 0, 16, 32 store the three sums (nd_wave_sum3)
-    const bool store = (lane & 15) == 0 && (lane >> 4) < 3;
+    const bool store = on && (lane & 15) == 0 && (lane >> 4) < 3;
     const int o = store ? (ymap ? ymap[it.yoff + c] : it.yoff + c) : 0;
-    const double* M = Mb + it.moff + (long)c * it.ldm;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    nd_dot<1>(M, xa + it.xoff, ldxa, it.split, s0, s1, s2);
-    if (it.rows > it.split)
-      nd_dot<-1>(M + it.split, xb + it.x2off, ldxb, it.rows - it.split, s0, s1, s2);
+    const double* M = Mb + it.moff + (long)(on ? c : 0) * it.ldm;
+    double s[1][3] = {{0.0, 0.0, 0.0}};
+    if constexpr (FWD)
+      nd_dot(M, vec.xa + it.xoff, vec.ldxa, it.rows, s[0][0], s[0][1], s[0][2]);
+    else
+      nd_columns<1, 4>(it, M, on ? 1 : 0, vec, xs, s);
     int k;
-    const double v = nd_wave_sum3(s0, s1, s2, k);
+    const double v = nd_wave_sum3(s[0][0], s[0][1], s[0][2], k);
     if (store) y[k * ldy + o] = v;
     return;
   }
   const int c0 = it.col0 + 4 * w;
-  if (c0 >= it.cols) return;
-  const int nc = min(4, it.cols - c0);
+  const int nc = max(0, min(4, it.cols - c0));
   // the lane that stores sum idx (nd_wave_sum12): column idx / 3, component idx % 3
   const int sidx = ((lane & 32) ? 6 : 0) + ((lane & 16) ? 3 : 0) + ((lane & 8) ? 2 : 0) +
                    ((lane & 4) ? 1 : 0);
   const int sc = sidx / 3;
   const bool store = (lane & 3) == 0 && (lane & 12) != 12 && sc < nc;
   const int o = store ? (ymap ? ymap[it.yoff + c0 + sc] : it.yoff + c0 + sc) : 0;
-  const double* M = Mb + it.moff + (long)c0 * it.ldm;
   double s[4][3];
 #pragma unroll
   for (int c = 0; c < 4; ++c)
 #pragma unroll
     for (int k = 0; k < 3; ++k) s[c][k] = 0.0;
-  nd_dot4<1>(M, it.ldm, nc, xa + it.xoff, ldxa, it.split, s);
-  if (it.rows > it.split)
-    nd_dot4<-1>(M + it.split, it.ldm, nc, xb + it.x2off, ldxb, it.rows - it.split, s);
+  const double* M = Mb + it.moff + (long)(nc > 0 ? c0 : 0) * it.ldm;
+  if constexpr (FWD)
+    nd_dot4(M, it.ldm, nc, vec.xa + it.xoff, vec.ldxa, it.rows, s);
+  else
+    nd_columns<4, 4>(it, M, nc, vec, xs, s);
   double sf[12];
 #pragma unroll
   for (int c = 0; c < 4; ++c)
@@ -247,9 +324,14 @@ __global__ __launch_bounds__(256) void k_nd_gemv(const NdItem* __restrict__ item
   if (store) y[(idx - 3 * sc) * ldy + o] = v;
 }
 void nd_gemv(int nitems, const NdItem* items, const double* M, const double* xa, long ldxa,
-             const double* xb, long ldxb, double* y, long ldy, const int32_t* ymap,
-             hipStream_t st) {
-  if (nitems > 0) k_nd_gemv<<<nitems, 256, 0, st>>>(items, M, xa, ldxa, xb, ldxb, y, ldy, ymap);
+             const int32_t* bkey, int n1, const double* x1, int m, const double* d2, double* y,
+             long ldy, const int32_t* ymap, hipStream_t st) {
+  if (nitems <= 0) return;
+  const NdVectors v{xa, ldxa, bkey, x1, d2, n1, m};
+  if (bkey)
+    k_nd_gemv<false><<<nitems, 256, 0, st>>>(items, M, v, y, ldy, ymap);
+  else                                  // no boundary rows (forward sweep)
+    k_nd_gemv<true><<<nitems, 256, 0, st>>>(items, M, v, y, ldy, ymap);
 }
 
 // dst (cols x rows, leading dimension ldd) = transpose of src (rows x cols,
@@ -271,26 +353,6 @@ void nd_transpose(const double* src, long lds, int rows, int cols, double* dst, 
   if (rows <= 0 || cols <= 0) return;
   dim3 grid((rows + 31) / 32, (cols + 31) / 32);
   k_nd_transpose<<<grid, 256, 0, st>>>(src, lds, rows, cols, dst, ldd);
-}
-
-// zb[v][e] = (key < n1) ? z[v][key] : d2[v][key - n1] for the cnt entries
-// (e, key) of erec.
-__global__ void k_nd_gather_zb(int cnt, const NdEntry* __restrict__ erec, int n1,
-                               const double* __restrict__ z, long ldz,
-                               const double* __restrict__ d2, long ldd2, double* __restrict__ zb,
-                               long ldzb) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= cnt) return;
-  const NdEntry en = erec[i];
-  const int t = en.key;
-#pragma unroll
-  for (int v = 0; v < 3; ++v)
-    zb[v * ldzb + en.e] = t < n1 ? z[v * ldz + t] : d2[v * ldd2 + (t - n1)];
-}
-void nd_gather_zb(int cnt, const NdEntry* erec, int n1, const double* z, long ldz,
-                  const double* d2, long ldd2, double* zb, long ldzb, hipStream_t st) {
-  if (cnt > 0)
-    k_nd_gather_zb<<<(cnt + 255) / 256, 256, 0, st>>>(cnt, erec, n1, z, ldz, d2, ldd2, zb, ldzb);
 }
 
 }  // namespace pdk

@@ -250,8 +250,8 @@ struct NdFactor {
   // ldzw) and W_s^T (n_s x b_s, leading dimension ldwt)
   std::vector<int64_t> zwoff, wtoff;
   std::vector<int32_t> ldzw, ldwt;
-  struct Level {                          // one tree height: ranges in tlist / items / elist
-    int32_t t_off, t_cnt, fw_off, fw_cnt, bw_off, bw_cnt, e_off, e_cnt;
+  struct Level {                          // one tree height: ranges in tlist / items
+    int32_t t_off, t_cnt, fw_off, fw_cnt, bw_off, bw_cnt;
   };
   std::vector<Level> levels;
   int32_t treg_off = 0;                   // region targets in tlist
@@ -259,9 +259,9 @@ struct NdFactor {
   double* d_fac = nullptr;
   int32_t *d_node_of = nullptr, *d_cpos = nullptr;
   NdTarget* d_trec = nullptr;             // targets of the right-hand-side gathers, tlist order
-  NdEntry* d_erec = nullptr;              // entries of the boundary gathers, elist order
+  int32_t* d_bkey = nullptr;              // boundary keys
   NdItem* d_items = nullptr;
-  double *d_r = nullptr, *d_x1 = nullptr, *d_contrib = nullptr, *d_zb = nullptr;
+  double *d_r = nullptr, *d_x1 = nullptr, *d_contrib = nullptr;
 };
 
 void nd_free(NdFactor* f) { delete f; }   // device memory belongs to the context
@@ -493,19 +493,15 @@ pd_status nd_factor(pd_ctx* c, const int32_t* tets, int64_t T, const std::vector
     for (int64_t s = 0; s < ns; ++s) H = std::max(H, S.height[s] + 1);
     std::vector<std::vector<int32_t>> at(H);
     for (int64_t s = 0; s < ns; ++s) at[S.height[s]].push_back((int32_t)s);
-    std::vector<int32_t> tlist, elist;
+    std::vector<int32_t> tlist;
     std::vector<NdItem> items;
     F->levels.assign(H, NdFactor::Level{});
     for (int h = 0; h < H; ++h) {
       NdFactor::Level& L = F->levels[h];
       L.t_off = (int32_t)tlist.size();
-      L.e_off = (int32_t)elist.size();
-      for (int32_t s : at[h]) {
+      for (int32_t s : at[h])
         for (int32_t p = S.first[s]; p < S.first[s + 1]; ++p) tlist.push_back(p);
-        for (int64_t e = S.bptr[s]; e < S.bptr[s + 1]; ++e) elist.push_back((int32_t)e);
-      }
       L.t_cnt = (int32_t)tlist.size() - L.t_off;
-      L.e_cnt = (int32_t)elist.size() - L.e_off;
       // four columns per item: the forward sweep's W_s r_s (columns of
       // W_s^T), the backward sweep's Z_s r_s - W_s^T zb_s (columns of [Z_s; W_s])
       // (four per wave when the columns are short: their vector loads are
@@ -538,18 +534,15 @@ pd_status nd_factor(pd_ctx* c, const int32_t* tets, int64_t T, const std::vector
       const int32_t t = tlist[g];
       trec[g] = NdTarget{node_of[t], t < n1 ? t : (int32_t)(t - n1), cptr[t], cptr[t + 1]};
     }
-    std::vector<NdEntry> erec(std::max<size_t>(elist.size(), 1), NdEntry{0, 0});
-    for (size_t i = 0; i < elist.size(); ++i) erec[i] = NdEntry{elist[i], S.bkey[elist[i]]};
     CK(c->upload(&F->d_node_of, node_of));
     CK(c->upload(&F->d_cpos, cpos));
     CK(c->upload(&F->d_trec, trec));
-    CK(c->upload(&F->d_erec, erec));
+    CK(c->upload(&F->d_bkey, S.bkey));
     CK(c->upload(&F->d_items, items));
     const int64_t v1 = 3 * std::max<int64_t>(n1, 1), vb = 3 * std::max<int64_t>(nb, 1);
     CK(c->alloc(&F->d_r, v1));
     CK(c->alloc(&F->d_x1, v1));
     CK(c->alloc(&F->d_contrib, vb));
-    CK(c->alloc(&F->d_zb, vb));
   }
   HIPCK(c, hipStreamSynchronize(c->st));
   return PD_OK;
@@ -563,8 +556,8 @@ void nd_condense(pd_ctx* c, const double* f, double* y2) {
     // r = f1 - (contributions of the descendants), then the contributions
     // W r of this height to its boundary
     nd_gather_rhs(L.t_cnt, F->d_trec + L.t_off, f, c->n, F->d_contrib, nb, F->d_r, n1, c->st);
-    nd_gemv(L.fw_cnt, F->d_items + L.fw_off, F->d_fac, F->d_r, n1, nullptr, 0, F->d_contrib, nb,
-            F->d_cpos, c->st);
+    nd_gemv(L.fw_cnt, F->d_items + L.fw_off, F->d_fac, F->d_r, n1, nullptr, n1, nullptr, m, nullptr,
+            F->d_contrib, nb, F->d_cpos, c->st);
   }
   nd_gather_rhs(m, F->d_trec + F->treg_off, f, c->n, F->d_contrib, nb, y2, m, c->st);
 }
@@ -572,16 +565,14 @@ void nd_condense(pd_ctx* c, const double* f, double* y2) {
 void nd_backsub(pd_ctx* c, const double* delta2, double* x, bool zero_w) {
   NdFactor* F = c->nd;
   const int n1 = F->sym.n1, m = F->sym.m;
-  const long nb = (long)F->nb;
   if (n1 == 0) return;
   if (zero_w) zero_f64(3L * n1, F->d_r, c->st);
   for (size_t h = F->levels.size(); h-- > 0;) {
     const NdFactor::Level& L = F->levels[h];
-    // zb = solution at the boundary (ancestors, or delta2 on the region),
-    // x1 = Z r - W^T zb
-    nd_gather_zb(L.e_cnt, F->d_erec + L.e_off, n1, F->d_x1, n1, delta2, m, F->d_zb, nb, c->st);
-    nd_gemv(L.bw_cnt, F->d_items + L.bw_off, F->d_fac, F->d_r, n1, F->d_zb, nb, F->d_x1, n1,
-            nullptr, c->st);
+    // x1 = Z r - W^T zb, zb the solution at the boundary (ancestors, or delta2
+    // on the region)
+    nd_gemv(L.bw_cnt, F->d_items + L.bw_off, F->d_fac, F->d_r, n1, F->d_bkey, n1, F->d_x1, m,
+            delta2, F->d_x1, n1, nullptr, c->st);
   }
   scatter_add_rows3(n1, F->d_node_of, F->d_x1, n1, x, c->n, c->st);
 }
