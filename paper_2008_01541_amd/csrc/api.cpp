@@ -590,6 +590,11 @@ pd_status build_impl(pd_ctx* c, const pd_mesh* M) {
   CK(c->alloc(&c->d_Yt, (int64_t)NB * m));
   CK(c->alloc(&c->d_res, 3 * m));
   CK(c->alloc(&c->d_norms, 8));
+  if (hipHostMalloc((void**)&c->h_norms, 8 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    c->h_norms = nullptr;
+    return c->fail(PD_ERR_OOM, "pinned host allocation failed");
+  }
   // boxes of the level-set detection's candidates: as many as E_beta has tets
   c->box_len = 12 * ((c->nbeta + 63) / 64);
   CK(c->alloc(&c->d_box, std::max<int64_t>(c->box_len, 1)));
@@ -1017,11 +1022,9 @@ pd_status residual(pd_ctx* c, const double* g, const double* u, double* rel) {
                   0.0, u, m, nullptr, 0, c->d_y, c->st);
     axpy3_sum(m, c->d_res, c->d_y, nullptr, c->d_res, c->st);
   }
-  colnorm2_3(m, c->d_res, c->d_norms, c->st);
-  colnorm2_3(m, g, c->d_norms + 3, c->st);
-  double nrm[6];
-  HIPCK(c, hipMemcpyAsync(nrm, c->d_norms, 6 * sizeof(double), hipMemcpyDeviceToHost, c->st));
+  colnorm2_3(m, c->d_res, g, c->h_norms, c->st);
   HIPCK(c, hipStreamSynchronize(c->st));
+  const double* nrm = c->h_norms;
   double rr = 0.0;
   for (int v = 0; v < 3; ++v)
     if (nrm[3 + v] > 0) rr = std::max(rr, std::sqrt(nrm[v] / nrm[3 + v]));
@@ -1050,11 +1053,9 @@ void lp_precondition(pd_ctx* c, const double* r, double* z) {
 // device (synchronizes).
 pd_status column_ratio(pd_ctx* c, const double* r, const double* g, double* rel) {
   const int m = (int)c->m;
-  colnorm2_3(m, r, c->d_norms, c->st);
-  colnorm2_3(m, g, c->d_norms + 3, c->st);
-  double nrm[6];
-  HIPCK(c, hipMemcpyAsync(nrm, c->d_norms, 6 * sizeof(double), hipMemcpyDeviceToHost, c->st));
+  colnorm2_3(m, r, g, c->h_norms, c->st);
   HIPCK(c, hipStreamSynchronize(c->st));
+  const double* nrm = c->h_norms;
   double rr = 0.0;
   for (int v = 0; v < 3; ++v)
     if (nrm[3 + v] > 0) rr = std::max(rr, std::sqrt(nrm[v] / nrm[3 + v]));

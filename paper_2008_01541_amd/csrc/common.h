@@ -199,7 +199,7 @@ void penalty_apply(int n_pen, const int32_t* act, const int32_t* rowptr, const i
 void change_norms(int64_t cnt, const int32_t* ids, const double* x, const double* xp,
                   const double* X, int64_t n, double* out, hipStream_t st);
 // out[v] = sum_i a[v][i]^2 for the three columns (out: 3 doubles, device).
-void colnorm2_3(int m, const double* a, double* out, hipStream_t st);
+void colnorm2_3(int m, const double* a, const double* b, double* out, hipStream_t st);
 void ws_input(int m, const double* x2, const double* x2p, float scale, int n_prox,
               const int32_t* prox, const double* c, float* out, hipStream_t st);
 void add_at(int64_t count, const int64_t* dst, const double* val, double* base, hipStream_t st);

@@ -77,6 +77,7 @@ struct pd_ctx {
   double* d_Yt = nullptr;             // 64 x m right-hand-side tile row of the fused solve
   double* d_res = nullptr;
   double* d_norms = nullptr;
+  double* h_norms = nullptr;          // squared norms that a kernel leaves in pinned host memory
   int* d_info = nullptr;
   int* d_err = nullptr;
   unsigned long long* d_ticket = nullptr;
@@ -150,6 +151,7 @@ struct pd_ctx {
     for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
     if (ev_fstart) (void)hipEventDestroy(ev_fstart);
     if (ev_fdone) (void)hipEventDestroy(ev_fdone);
+    if (h_norms) (void)hipHostFree(h_norms);
   }
 
   pd_status fail(pd_status s, const char* fmt, ...) {

@@ -525,20 +525,22 @@ void trsv3_lp_solve(const float* L, int ld, int n, const float* linv_ws, const d
 // The scalars live in device memory so that no iteration waits for the host.
 
 // out[v] = sum_i a[v][i] b[v][i], one workgroup per column, fixed order.
-__global__ __launch_bounds__(256) void k_dot3(int n, const double* __restrict__ a,
-                                              const double* __restrict__ b,
-                                              double* __restrict__ out) {
-  __shared__ double part[256];
-  const int v = blockIdx.x;
+__global__ __launch_bounds__(1024) void k_dot3(int n, const double* __restrict__ a,
+                                               const double* __restrict__ b,
+                                               double* __restrict__ out) {
+  __shared__ double part[16];
+  const long c0 = (long)blockIdx.x * n;
   double s = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) s += a[(long)v * n + i] * b[(long)v * n + i];
-  part[threadIdx.x] = s;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n; i += 1024) s += a[c0 + i] * b[c0 + i];
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) part[threadIdx.x] += part[threadIdx.x + o];
-    __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = part[0];
+    for (int k = 1; k < 16; ++k) t += part[k];
+    out[blockIdx.x] = t;
   }
-  if (threadIdx.x == 0) out[v] = part[0];
 }
 
 // With nq = -H p and pnq[v] = p_v . nq_v (= -p_v^T H p_v):
@@ -570,7 +572,7 @@ __global__ void k_cg_direction(int n, const double* __restrict__ rz_new,
 }
 
 void dot3(int n, const double* a, const double* b, double* out, hipStream_t st) {
-  k_dot3<<<3, 256, 0, st>>>(n, a, b, out);
+  k_dot3<<<3, 1024, 0, st>>>(n, a, b, out);
 }
 
 void cg_update(int n, const double* rz, const double* pnq, const double* p, const double* nq,
