@@ -404,6 +404,13 @@ pd_status pd_mlp_create(int32_t n_in, int32_t n_h1, int32_t n_h2, int32_t n_out,
                         int32_t max_batch, const float *params_host, void *hip_stream,
                         pd_mlp **out);
 
+/* Workspace of the products that are split over their inner dimension, for
+ * checking its size on the host (no GPU work): *used receives the floats that
+ * a call with batch rows writes at most, *held those that pd_mlp_create
+ * allocates.  Sizes < 1 or batch > max_batch -> PD_ERR_INVALID. */
+pd_status pd_mlp_workspace(int32_t n_in, int32_t n_h1, int32_t n_h2, int32_t n_out,
+                           int32_t max_batch, int32_t batch, int64_t *used, int64_t *held);
+
 /* host params (packed as above) <- current FP32 master parameters.  Synchronous. */
 pd_status pd_mlp_get_params(pd_mlp *mlp, float *params_host);
 

@@ -62,6 +62,8 @@ _SIGS = {
     "pd_backsub": [_P, _P, _P],
     "pd_mlp_create": [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, _P, _P,
                       C.POINTER(_P)],
+    "pd_mlp_workspace": [C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32,
+                         C.POINTER(C.c_int64), C.POINTER(C.c_int64)],
     "pd_mlp_get_params": [_P, _P],
     "pd_mlp_forward": [_P, _P, _P, C.c_int32],
     "pd_mlp_train_step": [_P, _P, _P, C.c_int32, C.c_float, C.POINTER(C.c_double), _P],

@@ -43,7 +43,6 @@ struct pd_mlp {
   __bf16* wb = nullptr;
   float *H1 = nullptr, *H2 = nullptr, *Y = nullptr, *dY = nullptr, *dA2 = nullptr, *dA1 = nullptr;
   float* part = nullptr;
-  long part_size = 0;
   double *lpart = nullptr, *loss = nullptr;
   std::vector<void*> mem;
   ~pd_mlp() {
@@ -68,6 +67,35 @@ int pick_split(int M, int N, int K) {
   int s = (int)std::max<long>(1, 512 / std::max<long>(tiles, 1));
   s = std::min(s, std::max(1, K / 256));
   return s;
+}
+
+// Split sums that a product out [M][N] over K leaves in the workspace.
+long split_floats(int M, int N, int K) {
+  return (long)mlp_gemm_nsplit(M, N, K, pick_split(M, N, K)) * M * N;
+}
+
+// The most that a call with B rows leaves there: the layers of the forward
+// pass, the backward products and the weights' gradients.
+long call_floats(const int (&n)[4], int B) {
+  long most = 0;
+  for (int i = 0; i < 3; ++i) {
+    most = std::max(most, split_floats(B, n[i + 1], n[i]));
+    if (i > 0) most = std::max(most, split_floats(B, n[i], n[i + 1]));
+    most = std::max(most, split_floats(n[i + 1], n[i], B));
+  }
+  return most;
+}
+
+// The same for every batch of up to max_batch rows.  Within 64 rows (a row of
+// tiles) the number of splits of a product over a layer's width stays the same,
+// and from 257 rows of tiles on nothing is split; a gradient has at most
+// pick_split(max_batch) splits.
+long workspace_floats(const int (&n)[4], int max_batch) {
+  long most = call_floats(n, max_batch);
+  for (int b = 64; b < max_batch && b <= 257 * 64; b += 64) most = std::max(most, call_floats(n, b));
+  for (int i = 0; i < 3; ++i)
+    most = std::max(most, (long)pick_split(n[i + 1], n[i], max_batch) * n[i + 1] * n[i]);
+  return most;
 }
 
 // W-shaped gradient out [M][N] = dZ^T X over the batch (K rows of both)
@@ -109,9 +137,7 @@ pd_status pd_mlp_create(int32_t n_in, int32_t n_h1, int32_t n_h2, int32_t n_out,
   h->boff[2] = sizes[0] + sizes[2];
   h->boff[3] = sizes[0] + sizes[2] + sizes[4];
   const long np = h->off[6];
-  long part = (long)std::max({n_h1, n_h2, n_out}) * std::max<long>(n_in, n_h2);   // gradient of W
-  part = std::max<long>(part, 64L * max_batch * std::max({n_h1, n_h2, n_out}));
-  h->part_size = part;
+  const long part = workspace_floats({n_in, n_h1, n_h2, n_out}, max_batch);
   bool ok = h->alloc(&h->p, np) && h->alloc(&h->g, np) && h->alloc(&h->m, np) && h->alloc(&h->v, np) &&
             h->alloc(&h->wb, h->boff[3]) && h->alloc(&h->H1, (long)max_batch * n_h1) &&
             h->alloc(&h->H2, (long)max_batch * n_h2) && h->alloc(&h->Y, (long)max_batch * n_out) &&
@@ -136,6 +162,17 @@ pd_status pd_mlp_create(int32_t n_in, int32_t n_h1, int32_t n_h2, int32_t n_out,
     return PD_ERR_HIP;
   }
   *out = h;
+  return PD_OK;
+}
+
+pd_status pd_mlp_workspace(int32_t n_in, int32_t n_h1, int32_t n_h2, int32_t n_out,
+                           int32_t max_batch, int32_t batch, int64_t* used, int64_t* held) {
+  if (n_in <= 0 || n_h1 <= 0 || n_h2 <= 0 || n_out <= 0 || batch <= 0 || batch > max_batch ||
+      !used || !held)
+    return PD_ERR_INVALID;
+  const int n[4] = {n_in, n_h1, n_h2, n_out};
+  *used = call_floats(n, batch);
+  *held = workspace_floats(n, max_batch);
   return PD_OK;
 }
 
