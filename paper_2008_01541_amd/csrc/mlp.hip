@@ -162,6 +162,16 @@ __device__ __forceinline__ void rows_times_weights(float4_t (&acc)[MB], int M, i
   }
 }
 
+// Block of outputs (of nb) and first row of a workgroup: the blocks of rows lie
+// behind one another in the grid's x, since y and z are bounded (65,535 blocks
+// of 32 rows, 2,097,120 rows).
+template <int MB>
+__device__ __forceinline__ void rows_block(int nb, int& nblk, int& m0) {
+  const int mb = blockIdx.x / nb;
+  nblk = blockIdx.x - mb * nb;
+  m0 = mb * 16 * MB;
+}
+
 // part[z][m][n] = sum over the k of split z; four waves of 16 n each
 template <int MB>
 __global__ __launch_bounds__(256) void k_rows_part(int M, int N, int K, int ks,
@@ -169,7 +179,9 @@ __global__ __launch_bounds__(256) void k_rows_part(int M, int N, int K, int ks,
                                                    const __bf16* __restrict__ W,
                                                    float* __restrict__ part) {
   const int lane = threadIdx.x & 63;
-  const int n0 = blockIdx.x * 64 + 16 * (threadIdx.x >> 6), z = blockIdx.y, m0 = blockIdx.z * 16 * MB;
+  int nblk, m0;
+  rows_block<MB>((N + 63) / 64, nblk, m0);
+  const int n0 = nblk * 64 + 16 * (threadIdx.x >> 6), z = blockIdx.y;
   if (n0 >= N) return;
   float4_t acc[MB];
   rows_times_weights<MB>(acc, M, N, K, m0, n0, z * ks, min(K, (z + 1) * ks), X, W);
@@ -192,7 +204,9 @@ __global__ __launch_bounds__(256) void k_rows_full(int M, int N, int K, int ks, 
                                                    float* __restrict__ out) {
   __shared__ float4_t red[4][MB][64];
   const int lane = threadIdx.x & 63, z = threadIdx.x >> 6, nz = blockDim.x >> 6;
-  const int n0 = blockIdx.x * 16, m0 = blockIdx.z * 16 * MB;
+  int nblk, m0;
+  rows_block<MB>((N + 15) / 16, nblk, m0);
+  const int n0 = nblk * 16;
   float4_t acc[MB];
   rows_times_weights<MB>(acc, M, N, K, m0, n0, z * ks, min(K, (z + 1) * ks), X, W);
 #pragma unroll
@@ -226,7 +240,9 @@ __global__ __launch_bounds__(256) void k_cols_part(int M, int N, int K, int ks,
                                                    float* __restrict__ part) {
   __shared__ __attribute__((aligned(16))) __bf16 Ws[2][64][MLD];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, ko = 8 * (lane >> 4);
-  const int n0 = blockIdx.x * 64, z = blockIdx.y, m0 = blockIdx.z * 16 * MB;
+  int nblk, m0;
+  rows_block<MB>((N + 63) / 64, nblk, m0);
+  const int n0 = nblk * 64, z = blockIdx.y;
   const int kbeg = z * ks, kend = min(K, kbeg + ks);
   const int kr = t >> 3, nc = n0 + 8 * (t & 7);        // this thread's weights of a chunk
   const float* px[MB];
@@ -319,12 +335,12 @@ void mlp_rows(int M, int N, int K, const float* X, const __bf16* W, const float*
   const int nz = (K + ks - 1) / ks;
   const unsigned gm = (unsigned)((M + 31) / 32);
   if (nz <= 4) {
-    const dim3 g((unsigned)((N + 15) / 16), 1, gm);
+    const dim3 g((unsigned)((N + 15) / 16) * gm);
     if (M <= 16) k_rows_full<1><<<g, 64 * nz, 0, st>>>(M, N, K, ks, relu, X, W, bias, out);
     else k_rows_full<2><<<g, 64 * nz, 0, st>>>(M, N, K, ks, relu, X, W, bias, out);
     return;
   }
-  const dim3 g((unsigned)((N + 63) / 64), (unsigned)nz, gm);
+  const dim3 g((unsigned)((N + 63) / 64) * gm, (unsigned)nz);
   if (M <= 16) k_rows_part<1><<<g, 256, 0, st>>>(M, N, K, ks, X, W, part);
   else k_rows_part<2><<<g, 256, 0, st>>>(M, N, K, ks, X, W, part);
   mlp_split_reduce(M, N, nz, part, bias, relu, nullptr, out, st);
@@ -335,7 +351,7 @@ void mlp_cols(int M, int N, int K, const float* X, const __bf16* W, const float*
               int nsplit, float* out, hipStream_t st) {
   const int ks = ((K + nsplit - 1) / nsplit + MKC - 1) / MKC * MKC;
   const int nz = (K + ks - 1) / ks;
-  const dim3 g((unsigned)((N + 63) / 64), (unsigned)nz, (unsigned)((M + 31) / 32));
+  const dim3 g((unsigned)((N + 63) / 64) * (unsigned)((M + 31) / 32), (unsigned)nz);
   if (M <= 16) k_cols_part<1><<<g, 256, 0, st>>>(M, N, K, ks, X, W, part);
   else k_cols_part<2><<<g, 256, 0, st>>>(M, N, K, ks, X, W, part);
   mlp_split_reduce(M, N, nz, part, nullptr, 0, H, out, st);

@@ -1,6 +1,6 @@
-"""The split sums of the warm-start network's products stay inside the
-workspace (host only), and a batch above the first rows' tile with more than
-64 splits of the widest layer gives the oracle's result (GPU)."""
+"""Large batches of the warm-start network: the split sums of its products
+stay inside the workspace (host only); a wide layer with more than 64 splits,
+and more blocks of rows than a grid's y or z holds, against the oracle (GPU)."""
 import ctypes as C
 
 import numpy as np
@@ -78,4 +78,31 @@ def test_wide_input_of_many_splits():
     got = y.cpu().numpy().reshape(B, shape[3])
     # FP32 sums against FP64 ones, with the odd BF16 rounding that goes the other way
     assert np.linalg.norm(got - Y) <= 1e-3 * np.linalg.norm(Y)
+    net.close()
+
+
+@pytest.mark.gpu
+def test_more_row_blocks_than_a_grid_dimension_holds():
+    import torch
+    from oracle import mlp as omlp
+    from paper_2008_01541_amd import MLP
+    from pd_inputs.mlp_init import mlp_init_params, pack, unpack
+    shape, B = (3, 2, 2, 3), 65535 * 32 + 33
+    flat = pack(mlp_init_params(*shape, seed=7))
+    rng = np.random.default_rng(8)
+    X = rng.normal(size=(B, 3)).astype(np.float32)
+    T = rng.normal(size=(B, 3)).astype(np.float32)
+    net = MLP(*shape, max_batch=B, params_flat=flat)
+    x, y = torch.tensor(X.reshape(-1), device="cuda"), torch.empty(3 * B, device="cuda")
+    net.forward(x, y)
+    p = unpack(flat, *shape)
+    Y, cache = omlp.forward(p, X.astype(np.float64))
+    got = y.cpu().numpy().reshape(B, 3)
+    assert np.linalg.norm(got - Y) <= 1e-3 * np.linalg.norm(Y)
+    assert np.linalg.norm(got[-33:] - Y[-33:]) <= 1e-2 * np.linalg.norm(Y[-33:])
+    # the backward products take the same grid
+    g, _ = net.gradients(x, torch.tensor(T.reshape(-1), device="cuda"))
+    gd, ref = unpack(g, *shape), omlp.backward(p, cache, Y, T.astype(np.float64))
+    for k in ref:
+        assert np.linalg.norm(gd[k] - ref[k]) <= 5e-3 * np.linalg.norm(ref[k]), k
     net.close()
