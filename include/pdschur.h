@@ -455,6 +455,15 @@ pd_status pd_set_stream(pd_ctx *ctx, void *hip_stream);
  * ordered after them. */
 pd_status pd_use_stream(pd_ctx *ctx, void *hip_stream);
 
+/* Bound of the waits of the interior_order = 0 sweeps that hand values from
+ * one workgroup to another inside a launch (pd_condense_rhs, pd_backsub,
+ * pd_warmstart_apply): a workgroup gives up after this many polls (default
+ * 4,194,304, seconds; a poll takes a microsecond or more).  The launch then
+ * ends with incomplete results, the next call that synchronizes, or any call
+ * made after the launch has ended, returns PD_ERR_HIP, and the context can
+ * only be destroyed.  polls < 1 -> PD_ERR_INVALID. */
+pd_status pd_set_wait_limit(pd_ctx *ctx, int64_t polls);
+
 /* Phases timed by pd_get_timings. */
 typedef enum {
   PD_PHASE_LOCAL_FULL = 0,    /* pd_local_step_full */

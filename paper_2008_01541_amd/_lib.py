@@ -86,6 +86,7 @@ _SIGS = {
     "pd_use_stream": [_P, _P],
     "pd_factor": [_P, C.c_int32, C.c_int32],
     "pd_set_refinement": [_P, C.c_int32, C.c_double, C.c_int32],
+    "pd_set_wait_limit": [_P, C.c_int64],
     "pd_set_timing": [_P, C.c_int],
     "pd_get_timings": [_P, _P, _P],
     "pd_destroy": [_P],
@@ -463,6 +464,10 @@ class PDContext(_Handle):
         """Enqueue later calls on stream without synchronizing (pd_use_stream)."""
         self._chk(self._lib.pd_use_stream(self._ctx, C.c_void_p(stream.cuda_stream)))
         self.stream = stream
+
+    def set_wait_limit(self, polls):
+        """Polls after which a wait inside a sweep is given up (pd_set_wait_limit)."""
+        self._chk(self._lib.pd_set_wait_limit(self._ctx, int(polls)))
 
     def set_timing(self, on=True):
         self._chk(self._lib.pd_set_timing(self._ctx, 1 if on else 0))

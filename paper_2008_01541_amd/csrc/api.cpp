@@ -590,11 +590,13 @@ pd_status build_impl(pd_ctx* c, const pd_mesh* M) {
   CK(c->alloc(&c->d_Yt, (int64_t)NB * m));
   CK(c->alloc(&c->d_res, 3 * m));
   CK(c->alloc(&c->d_norms, 8));
-  if (hipHostMalloc((void**)&c->h_norms, 8 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc((void**)&c->h_norms, 9 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     c->h_norms = nullptr;
     return c->fail(PD_ERR_OOM, "pinned host allocation failed");
   }
+  c->h_gave_up = reinterpret_cast<int*>(c->h_norms + 8);
+  *c->h_gave_up = 0;
   // boxes of the level-set detection's candidates: as many as E_beta has tets
   c->box_len = 12 * ((c->nbeta + 63) / 64);
   CK(c->alloc(&c->d_box, std::max<int64_t>(c->box_len, 1)));
@@ -736,21 +738,21 @@ pd_status pd_region_nodes(const pd_ctx* c, int32_t* ids) {
 
 pd_status pd_get_schur(pd_ctx* c, double* S) {
   if (bad_ctx(c) || !S) return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   HIPCK(c, hipMemcpyAsync(S, c->d_S, c->m * c->m * sizeof(double), hipMemcpyDeviceToDevice, c->st));
   return PD_OK;
 }
 
 pd_status pd_region_gather(pd_ctx* c, const double* x, double* x2) {
   if (bad_ctx(c) || !x || !x2) return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   gather_rows3(c->m, c->d_region_ids, x, c->n, x2, c->m, c->st);
   return c->check("pd_region_gather");
 }
 
 pd_status pd_local_step_full(pd_ctx* c, const double* x, void* R_alpha, double* f, int rot_fp32) {
   if (bad_ctx(c) || !x || !f) return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   if (c->dt > 0.0 && !c->d_target)
     return c->fail(PD_ERR_STATE, "backward Euler: pd_set_inertia_target before pd_local_step_full");
   PhaseTimer tm(c, PD_PHASE_LOCAL_FULL);
@@ -770,7 +772,7 @@ pd_status pd_set_inertia_target(pd_ctx* c, const double* y) {
 
 pd_status pd_time_step_advance(pd_ctx* c, const double* x, double* x_prev, double* v, double* y) {
   if (bad_ctx(c) || !x || !x_prev || !v || !y) return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   if (!(c->dt > 0.0)) return c->fail(PD_ERR_STATE, "quasistatic context: no time step");
   time_step_advance(3 * c->n, c->dt, x, x_prev, v, y, c->st);
   return c->check("pd_time_step_advance");
@@ -793,6 +795,8 @@ static LevelSweep level_sweep_args(pd_ctx* c, int d, const double* in, int64_t l
   a.pub = c->d_spub[d];
   a.ticket = c->d_sticket + d;
   a.err = c->d_err;
+  a.gave_up = c->h_gave_up;
+  a.polls = c->wait_polls;
   a.n1 = c->n1;
   a.ldi = ldi;
   a.ldo = ldo;
@@ -804,7 +808,7 @@ static LevelSweep level_sweep_args(pd_ctx* c, int d, const double* in, int64_t l
 
 pd_status pd_condense_rhs(pd_ctx* c, const double* f, double* y2) {
   if (bad_ctx(c) || !f || !y2) return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   const int64_t n1 = c->n1, m = c->m;
   PhaseTimer tm(c, PD_PHASE_CONDENSE);
   if (c->nd || c->n_stask[0] > 0) {
@@ -871,7 +875,7 @@ static void backsub_levels(pd_ctx* c, const double* delta2, double* x, bool zero
 
 pd_status pd_backsub(pd_ctx* c, const double* delta2, double* x) {
   if (bad_ctx(c) || !delta2 || !x) return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   if (!c->have_condense) return c->fail(PD_ERR_STATE, "pd_backsub needs a preceding pd_condense_rhs");
   PhaseTimer tm(c, PD_PHASE_BACKSUB);
   backsub_levels(c, delta2, x, false);
@@ -882,7 +886,7 @@ pd_status pd_warmstart_apply(pd_ctx* c, const float* d2, double scale, const dou
                              const double* x2_prev2, double* x) {
   if (bad_ctx(c) || !d2 || !x || !std::isfinite(scale) || (!x2_prev1 != !x2_prev2))
     return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   if (!c->d_ext) CK(c->alloc(&c->d_ext, 3 * std::max<int64_t>(1, c->m)));
   scale_f32_to_f64(3 * c->m, d2, scale, x2_prev1, x2_prev2, c->d_ext, c->st);
   // the elastic response of the interior with f1 = 0
@@ -897,7 +901,7 @@ pd_status pd_detect_spheres(pd_ctx* c, int32_t n_prox, const int32_t* prox, int3
   if (bad_ctx(c) || n_prox < 0 || n_sph < 0 || (n_prox > 0 && (!prox || !x2 || !idx || !w || !cc || !t)) ||
       (n_sph > 0 && !spheres) || !(k >= 0.0))
     return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   PhaseTimer tm(c, PD_PHASE_DETECT);
   detect_spheres(n_prox, prox, n_sph, spheres, k, x2, (int)c->m, idx, w, cc, t, c->st);
   return c->check("pd_detect_spheres");
@@ -908,7 +912,7 @@ pd_status pd_detect_pairs(pd_ctx* c, int32_t n_pairs, const int32_t* pairs, doub
   if (bad_ctx(c) || n_pairs < 0 || !(k >= 0.0) ||
       (n_pairs > 0 && (!pairs || !x2 || !idx || !w || !cc || !t)))
     return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   PhaseTimer tm(c, PD_PHASE_DETECT);
   detect_pairs(n_pairs, pairs, k, x2, (int)c->m, idx, w, cc, t, c->st);
   return c->check("pd_detect_pairs");
@@ -920,7 +924,7 @@ pd_status pd_embed_points(pd_ctx* c, int32_t n_pts, const double* pts, int32_t n
   if (bad_ctx(c) || n_pts < 0 || n_cand < 0 ||
       (n_pts > 0 && (!pts || !pos || !tet || !eidx || !ew || (n_cand > 0 && !cand))))
     return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   embed_points(n_pts, pts, n_cand, cand, pos, (int)c->m, tet, eidx, ew, c->st);
   return c->check("pd_embed_points");
 }
@@ -932,7 +936,7 @@ pd_status pd_detect_embedded_spheres(pd_ctx* c, int32_t n_prox, const int32_t* e
   if (bad_ctx(c) || n_prox < 0 || n_sph < 0 || !(k >= 0.0) ||
       (n_prox > 0 && (!eidx || !ew || !x2 || !idx || !w || !cc || !t)) || (n_sph > 0 && !spheres))
     return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   PhaseTimer tm(c, PD_PHASE_DETECT);
   detect_embedded_spheres(n_prox, eidx, ew, n_sph, spheres, k, x2, (int)c->m, idx, w, cc, t,
                           c->st);
@@ -948,7 +952,7 @@ pd_status pd_detect_levelset(pd_ctx* c, int32_t n_prox, const int32_t* eidx, con
       (n_prox > 0 && (!eidx || !ew || !prox_body || !rest2 || !x2 || !idx || !w || !cc || !t)) ||
       (n_cand > 0 && (!cand || !cand_phi || !cand_body)))
     return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   PhaseTimer tm(c, PD_PHASE_DETECT);
   detect_levelset(n_prox, eidx, ew, prox_body, n_cand, cand, cand_phi, cand_body, rest2, k, x2,
                   (int)c->m, c->d_box, c->box_len, idx, w, cc, t, c->st);
@@ -959,7 +963,7 @@ pd_status pd_collision_update(pd_ctx* c, int32_t n_pen, const int32_t* idx, cons
                               const double* cc, const double* t, const double* x2, double* f_col) {
   if (bad_ctx(c) || n_pen < 0 || !x2 || !f_col || (n_pen > 0 && (!idx || !w || !cc || !t)))
     return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   CK(ensure_pen_cap(c, std::max<int32_t>(n_pen, 1)));
   PhaseTimer tm(c, PD_PHASE_COLLISION);
   if (n_pen > 0) {                    // copied by a kernel (capturable like every other step)
@@ -978,7 +982,7 @@ pd_status pd_collision_update(pd_ctx* c, int32_t n_pen, const int32_t* idx, cons
 pd_status pd_local_step_region(pd_ctx* c, const double* x2, void* R_beta, double* f_beta,
                                int rot_fp32) {
   if (bad_ctx(c) || !x2 || !f_beta) return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   if (c->nbeta == 0) {
     zero_f64(3 * c->m, f_beta, c->st);
     return c->check("pd_local_step_region");
@@ -994,7 +998,7 @@ pd_status pd_local_step_region(pd_ctx* c, const double* x2, void* R_beta, double
 pd_status pd_assemble_rhs(pd_ctx* c, const double* ft, const double* f_beta, const double* f_col,
                           double* g) {
   if (bad_ctx(c) || !ft || !g) return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   PhaseTimer tm(c, PD_PHASE_ASSEMBLE);
   axpy3_sum((int)c->m, ft, f_beta, f_col, g, c->st);
   return c->check("pd_assemble_rhs");
@@ -1023,7 +1027,7 @@ pd_status residual(pd_ctx* c, const double* g, const double* u, double* rel) {
     axpy3_sum(m, c->d_res, c->d_y, nullptr, c->d_res, c->st);
   }
   colnorm2_3(m, c->d_res, g, c->h_norms, c->st);
-  HIPCK(c, hipStreamSynchronize(c->st));
+  CK(c->synchronize());
   const double* nrm = c->h_norms;
   double rr = 0.0;
   for (int v = 0; v < 3; ++v)
@@ -1054,7 +1058,7 @@ void lp_precondition(pd_ctx* c, const double* r, double* z) {
 pd_status column_ratio(pd_ctx* c, const double* r, const double* g, double* rel) {
   const int m = (int)c->m;
   colnorm2_3(m, r, g, c->h_norms, c->st);
-  HIPCK(c, hipStreamSynchronize(c->st));
+  CK(c->synchronize());
   const double* nrm = c->h_norms;
   double rr = 0.0;
   for (int v = 0; v < 3; ++v)
@@ -1133,7 +1137,7 @@ pd_status pd_global_solve(pd_ctx* c, const double* g, double* u, pd_precision pr
   if (bad_ctx(c) || !g || !u) return PD_ERR_INVALID;
   if (prec != PD_FP64 && prec != PD_FP32_IR && prec != PD_BF16_IR)
     return c->fail(PD_ERR_INVALID, "unknown precision mode %d", (int)prec);
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   const int m = (int)c->m;
   if (prec == PD_FP64) {
     const bool fused = c->stale;      // the forward substitution inside the factorization
@@ -1280,7 +1284,7 @@ pd_status pd_set_refinement(pd_ctx* c, int32_t max_steps, double tol, int32_t fa
 
 pd_status pd_factor(pd_ctx* c, int32_t n_workgroups, int32_t overlap_forward) {
   if (bad_ctx(c)) return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   if (overlap_forward != 0 && overlap_forward != 1)
     return c->fail(PD_ERR_INVALID, "overlap_forward must be 0 or 1 (got %d)", (int)overlap_forward);
   if (!c->stale) return PD_OK;
@@ -1305,7 +1309,7 @@ pd_status pd_factor(pd_ctx* c, int32_t n_workgroups, int32_t overlap_forward) {
 
 pd_status pd_inner_update(pd_ctx* c, const double* u2, double* x2, double* delta2, double* ft) {
   if (bad_ctx(c) || !u2 || !x2 || !delta2 || !ft) return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   const int m = (int)c->m;
   PhaseTimer tm(c, PD_PHASE_INNER_UPDATE);
   inner_update(m, u2, x2, delta2, c->st);
@@ -1319,7 +1323,7 @@ pd_status pd_warmstart_input(pd_ctx* c, const double* x2, const double* x2_prev,
                              int32_t n_prox, const int32_t* prox, const double* cpen, float* out) {
   if (bad_ctx(c) || !x2 || !x2_prev || !out || n_prox < 0 || (n_prox > 0 && (!prox || !cpen)))
     return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   ws_input((int)c->m, x2, x2_prev, scale, n_prox, prox, cpen, out, c->st);
   return c->check("pd_warmstart_input");
 }
@@ -1327,25 +1331,25 @@ pd_status pd_warmstart_input(pd_ctx* c, const double* x2, const double* x2_prev,
 pd_status pd_warmstart_target(pd_ctx* c, const double* x2, const double* x2_prev1,
                               const double* x2_prev2, float scale, float* out) {
   if (bad_ctx(c) || !x2 || !x2_prev1 || !x2_prev2 || !out) return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   ws_target(3 * c->m, x2, x2_prev1, x2_prev2, scale, out, c->st);
   return c->check("pd_warmstart_target");
 }
 
 pd_status pd_region_add_f32(pd_ctx* c, const float* d2, double scale, double* x) {
   if (bad_ctx(c) || !d2 || !x) return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   region_add_f32(c->m, c->d_region_ids, d2, scale, x, c->n, c->st);
   return c->check("pd_region_add_f32");
 }
 
 pd_status pd_displacement_change(pd_ctx* c, const double* x, const double* x_prev, double* out) {
   if (bad_ctx(c) || !x || !x_prev || !out) return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   change_norms(c->n_free, c->d_free_ids, x, x_prev, c->d_rest, c->n, c->d_norms, c->st);
   double h[2];
   HIPCK(c, hipMemcpyAsync(h, c->d_norms, 2 * sizeof(double), hipMemcpyDeviceToHost, c->st));
-  HIPCK(c, hipStreamSynchronize(c->st));
+  CK(c->synchronize());
   out[0] = std::sqrt(h[0]);
   out[1] = std::sqrt(h[1]);
   return PD_OK;
@@ -1353,16 +1357,22 @@ pd_status pd_displacement_change(pd_ctx* c, const double* x, const double* x_pre
 
 pd_status pd_set_stream(pd_ctx* c, void* hip_stream) {
   if (bad_ctx(c)) return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
-  HIPCK(c, hipStreamSynchronize(c->st));
+  if (c->unusable()) return PD_ERR_HIP;
+  CK(c->synchronize());
   c->st = (hipStream_t)hip_stream;
   return PD_OK;
 }
 
 pd_status pd_use_stream(pd_ctx* c, void* hip_stream) {
   if (bad_ctx(c)) return PD_ERR_INVALID;
-  if (c->broken) return PD_ERR_HIP;
+  if (c->unusable()) return PD_ERR_HIP;
   c->st = (hipStream_t)hip_stream;
+  return PD_OK;
+}
+
+pd_status pd_set_wait_limit(pd_ctx* c, int64_t polls) {
+  if (bad_ctx(c) || polls < 1) return PD_ERR_INVALID;
+  c->wait_polls = polls;
   return PD_OK;
 }
 
@@ -1374,7 +1384,7 @@ pd_status pd_set_timing(pd_ctx* c, int on) {
 
 pd_status pd_get_timings(pd_ctx* c, double* ms, int64_t* counts) {
   if (bad_ctx(c) || !ms) return PD_ERR_INVALID;
-  HIPCK(c, hipStreamSynchronize(c->st));
+  CK(c->synchronize());
   for (int p = 0; p < PD_N_PHASES; ++p) {
     ms[p] = 0.0;
     if (counts) counts[p] = 0;

@@ -129,6 +129,8 @@ struct LevelSweep {
   double* pub;                         // two copies of 3 n1 values, filled with the sentinel
   unsigned long long* ticket;
   int* err;
+  int* gave_up;                        // host memory: set when a wait is given up
+  long polls;                          // after this many polls
   long n1, ldi, ldo;
   int ntask, K, m;
 };

@@ -78,6 +78,8 @@ struct pd_ctx {
   double* d_res = nullptr;
   double* d_norms = nullptr;
   double* h_norms = nullptr;          // squared norms that a kernel leaves in pinned host memory
+  int* h_gave_up = nullptr;           // behind them: set by a sweep whose wait was given up
+  int64_t wait_polls = int64_t{1} << 22;   // bound of a sweep's waits
   int* d_info = nullptr;
   int* d_err = nullptr;
   unsigned long long* d_ticket = nullptr;
@@ -152,6 +154,21 @@ struct pd_ctx {
     if (ev_fstart) (void)hipEventDestroy(ev_fstart);
     if (ev_fdone) (void)hipEventDestroy(ev_fdone);
     if (h_norms) (void)hipHostFree(h_norms);
+  }
+
+  // A wait inside a sweep that was given up leaves results and published
+  // vectors incomplete: the first call that finds the word set reports it,
+  // and the context is broken from then on.
+  bool unusable() {
+    if (!broken && h_gave_up && *(volatile int*)h_gave_up)
+      (void)fail(PD_ERR_HIP, "a wait inside a sweep was given up");
+    return broken;
+  }
+  pd_status synchronize() {
+    const bool was = broken;
+    if (hipError_t e = hipStreamSynchronize(st); e != hipSuccess)
+      return fail(PD_ERR_HIP, "hipStreamSynchronize: %s", hipGetErrorString(e));
+    return unusable() && !was ? PD_ERR_HIP : PD_OK;
   }
 
   pd_status fail(pd_status s, const char* fmt, ...) {

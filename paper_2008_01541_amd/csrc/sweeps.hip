@@ -208,7 +208,6 @@ __global__ void k_sweep_assemble(int w, int nb, const double* __restrict__ Prow,
 // (x 16) 397 -> 241, 1,560 (x 20) 555 -> 362, 2,025 (x 20) 601 -> 485.  Past 1,024
 // nodes the full Z_k bounds it (2.3 TB/s); the gain runs out near 2,400, and
 // at LEVEL_MAX a thread's 64 values of Z_k still fit its registers.
-constexpr long SWEEP_SPIN_LIMIT = 1L << 22;
 constexpr int LT = 512;                // threads of a workgroup
 constexpr int LB = 16;                 // rows of a task
 
@@ -302,7 +301,7 @@ __global__ __launch_bounds__(LT, 2) void k_level_sweep(LevelSweep a) {
       long spins = 0;
       while (is_sentinel(coherent_load(&pub[L.goff]))) {
         __builtin_amdgcn_s_sleep(8);
-        if (++spins > SWEEP_SPIN_LIMIT ||
+        if (++spins > a.polls ||
             __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
           bad = true;
           break;
@@ -327,7 +326,7 @@ __global__ __launch_bounds__(LT, 2) void k_level_sweep(LevelSweep a) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) miss |= is_sentinel(pv[i][c]) ? 1 : 0;
       if (__ballot(miss) == 0) break;
-      if (spins > SWEEP_SPIN_LIMIT ||
+      if (spins > a.polls ||
           __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)
         bad = true;
     }
@@ -342,7 +341,10 @@ __global__ __launch_bounds__(LT, 2) void k_level_sweep(LevelSweep a) {
 #pragma unroll
     for (int q = 0; q < LT / 64; ++q) any |= s_bad[q];
     if (any) {
-      if (t == 0) atomicExch(a.err, 1);
+      if (t == 0) {
+        atomicExch(a.err, 1);
+        __hip_atomic_store(a.gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      }
       return;
     }
   }
