@@ -356,19 +356,39 @@ pd_status pd_chol_factor_noalloc(double *A, int64_t lda, int64_t n, int32_t n_wo
                                  void *hip_stream, int32_t *info_host);
 
 
-/* Schedule of the single-launch dataflow Cholesky (pd_chol_factor, the
- * factorization of H = S + P in pd_global_solve / pd_factor), for checking
- * its index ranges on the host (no GPU work; the kernels decode their
- * tickets with the same code).  For order n (tiles of 64, nt = ceil(n/64)),
+/* Order in which the single-launch dataflow Cholesky (pd_chol_factor, the
+ * factorization of H = S + P in pd_global_solve / pd_factor) gives out the
+ * tiles (host only, no GPU work; pd_factor_schedule has the tasks themselves).
+ * For order n (tiles of 64, nt = ceil(n/64)),
  * rhs = 1 when the three right-hand sides ride along as an extra tile row:
  * *ntask receives the number of tiles, and for 0 <= q < *ntask the q-th tile
  * (*i, *j) in the order in which tickets are given out (*i == nt: the
  * right-hand-side row; a ticket of two tiles gives two consecutive entries),
  * and *kend, the number of 64-column steps summed for the tile before its own
- * last step.  n < 1, rhs not 0/1, or q outside [0, *ntask) (q < 0 only queries
+ * last step, by its own task or by those that it takes partial sums from.
+ * n < 1, rhs not 0/1, or q outside [0, *ntask) (q < 0 only queries
  * the count) -> PD_ERR_INVALID. */
 pd_status pd_dataflow_task(int64_t n, int32_t rhs, int64_t q, int32_t *i, int32_t *j,
                            int32_t *kend, int64_t *ntask);
+
+/* The tasks that the factorization kernels run, and the workspace they run in
+ * (host only, from the code that the kernels decode their tickets with and that
+ * sizes the allocations).  A task holds tiles (1 or 2) tiles of row i, (i, j)
+ * the first, and sums steps 64-column steps of published tiles.  With slot >= 0
+ * it leaves that partial sum in the slot (64 x 64 values) and publishes flag;
+ * the diagonal task of row i finishes the tile.  In FP64 those are the two
+ * tiles left of each diagonal (none is left where steps = 0), in the
+ * low-precision kernel one. */
+typedef struct {
+  int32_t i, j, tiles, steps, slot, flag;
+} pd_factor_task;
+
+/* sizes (host [3]) <- tickets, flags and slots for order n; for 0 <= ticket <
+ * sizes[0], *task <- that ticket's task (ticket < 0 only queries the sizes).
+ * low_precision = 1: the FP32 / BF16 kernel, which carries no right-hand side.
+ * Other values, n < 1 or a ticket past the end -> PD_ERR_INVALID. */
+pd_status pd_factor_schedule(int64_t n, int32_t low_precision, int32_t rhs, int64_t ticket,
+                             pd_factor_task *task, int64_t *sizes);
 
 /* The nested-dissection ordering and symbolic factorization that
  * pd_schur_build uses for interior_order = 1 (host only, no GPU work;

@@ -74,6 +74,7 @@ _SIGS = {
     "pd_chol_factor": [_P, _P, C.c_int64, C.c_int64, C.c_int32, C.POINTER(C.c_int32)],
     "pd_chol_destroy": [_P],
     "pd_nd_analyse": [C.POINTER(pd_mesh), C.c_int32, _P, _P, _P, _P, _P, _P],
+    "pd_factor_schedule": [C.c_int64, C.c_int32, C.c_int32, C.c_int64, _P, _P],
     "pd_dataflow_task": [C.c_int64, C.c_int32, C.c_int64, C.POINTER(C.c_int32),
                          C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_int64)],
     "pd_chol_factor_noalloc": [_P, C.c_int64, C.c_int64, C.c_int32, _P, C.POINTER(C.c_int32)],

@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "ctx.h"
+#include "df_schedule.h"
 
 using namespace pdk;
 
@@ -470,7 +471,7 @@ pd_status build_impl(pd_ctx* c, const pd_mesh* M) {
   c->ntm = (int)((m + NB - 1) / NB);
   const int64_t ntmax = (std::max<int64_t>(c->maxw, m) + NB - 1) / NB;
   CK(c->alloc(&c->d_linv, ntmax * NB * NB));
-  CK(c->alloc(&c->d_sbuf, 2 * ntmax * NB * NB));
+  CK(c->alloc(&c->d_sbuf, df_slots(ntmax) * NB * NB));
   CK(c->alloc(&c->d_info, 1));
   CK(c->alloc(&c->d_err, 1));
   CK(c->alloc(&c->d_ticket, 4));
@@ -478,7 +479,7 @@ pd_status build_impl(pd_ctx* c, const pd_mesh* M) {
   HIPCK(c, hipMemsetAsync(c->d_err, 0, sizeof(int), c->st));
   HIPCK(c, hipMemsetAsync(c->d_ticket, 0, 4 * sizeof(unsigned long long), c->st));
   {
-    const int64_t nt2 = ntmax * (ntmax + 3);
+    const int64_t nt2 = df_flags(ntmax);
     CK(c->alloc(&c->d_tflags, nt2));
     CK(c->alloc(&c->d_tticket, 4));
     CK(c->alloc(&c->d_cumarks, potrf_cu_slots()));

@@ -15,8 +15,8 @@ struct pd_chol {
   int64_t n_max = 0;
   int n_wg = 512;
   double* linv = nullptr;      // tile inverses, nt x 64 x 64
-  double* sbuf = nullptr;      // partial sums of the tiles left of the diagonal, 2 nt x 64 x 64
-  int* flags = nullptr;        // (nt + 3) x nt ready flags (launch epochs)
+  double* sbuf = nullptr;      // partial sums of the tiles left of the diagonal, df_slots(nt) x 64 x 64
+  int* flags = nullptr;        // df_flags(nt) ready flags (launch epochs)
   unsigned* ticket = nullptr;  // task ticket and launch epoch
   int* info = nullptr;
   int* err = nullptr;
@@ -36,8 +36,8 @@ struct pd_chol {
 constexpr int64_t NA_NT = (PD_CHOL_NOALLOC_MAX_N + NB - 1) / NB;
 constexpr int64_t NA_LINV = 0;                               // doubles
 constexpr int64_t NA_SBUF = NA_LINV + NA_NT * NB * NB;       // doubles
-constexpr int64_t NA_INTS = NA_SBUF + 2 * NA_NT * NB * NB;       // doubles: start of the int area
-constexpr int64_t NA_FLAGS_N = (NA_NT + 3) * NA_NT;
+constexpr int64_t NA_INTS = NA_SBUF + df_slots(NA_NT) * NB * NB;     // doubles: start of the int area
+constexpr int64_t NA_FLAGS_N = df_flags(NA_NT);
 constexpr int64_t NA_MARKS_N = 2048;
 constexpr int64_t NA_INT_N = NA_FLAGS_N + 4 + 1 + 1 + NA_MARKS_N;
 constexpr int64_t NA_DOUBLES = NA_INTS + (NA_INT_N + 1) / 2;
@@ -89,8 +89,8 @@ pd_status pd_chol_create(int64_t n_max, void* stream, pd_chol** out) {
     h->n_wg = 2 * ncu;
   const int nmarks = potrf_cu_slots();
   bool ok = hipMalloc(&h->linv, nt * NB * NB * sizeof(double)) == hipSuccess &&
-            hipMalloc(&h->sbuf, 2 * nt * NB * NB * sizeof(double)) == hipSuccess &&
-            hipMalloc(&h->flags, (nt + 3) * nt * sizeof(int)) == hipSuccess &&
+            hipMalloc(&h->sbuf, df_slots(nt) * NB * NB * sizeof(double)) == hipSuccess &&
+            hipMalloc(&h->flags, df_flags(nt) * sizeof(int)) == hipSuccess &&
             hipMalloc(&h->ticket, 4 * sizeof(unsigned)) == hipSuccess &&
             hipMalloc(&h->info, sizeof(int)) == hipSuccess &&
             hipMalloc(&h->err, sizeof(int)) == hipSuccess &&
@@ -99,7 +99,7 @@ pd_status pd_chol_create(int64_t n_max, void* stream, pd_chol** out) {
     delete h;
     return PD_ERR_OOM;
   }
-  ok = hipMemsetAsync(h->flags, 0, (nt + 3) * nt * sizeof(int), h->st) == hipSuccess &&
+  ok = hipMemsetAsync(h->flags, 0, df_flags(nt) * sizeof(int), h->st) == hipSuccess &&
        hipMemsetAsync(h->ticket, 0, 4 * sizeof(unsigned), h->st) == hipSuccess &&
        hipMemsetAsync(h->marks, 0, nmarks * sizeof(int), h->st) == hipSuccess &&
        hipStreamSynchronize(h->st) == hipSuccess;
@@ -202,6 +202,29 @@ pd_status pd_dataflow_task(int64_t n, int32_t rhs, int64_t q, int32_t* i, int32_
   *i = ti;
   *j = tj;
   *kend = df_task_kend(ti, tj);
+  return PD_OK;
+}
+
+pd_status pd_factor_schedule(int64_t n, int32_t low_precision, int32_t rhs, int64_t ticket,
+                             pd_factor_task* task, int64_t* sizes) {
+  if (n < 1 || n > 46340 || (low_precision != 0 && low_precision != 1) || (rhs != 0 && rhs != 1) ||
+      (low_precision && rhs) || !sizes)
+    return PD_ERR_INVALID;
+  const int nt = (int)((n + NB - 1) / NB), wide = low_precision ? 0 : df64_wide(nt);
+  sizes[0] = df64_task_count(nt, wide, rhs);
+  sizes[1] = df_flags(nt);
+  sizes[2] = df_slots(nt);
+  if (ticket < 0) return PD_OK;
+  if (ticket >= sizes[0] || !task) return PD_ERR_INVALID;
+  const DfTask d = df64_task((int)ticket, nt, wide, rhs);
+  const int slot = low_precision ? (d.i == d.j + 1 ? df_part_slot(d.i, d.j, nt) : -1)
+                                 : df_part_slot(d.i, d.j, nt);
+  task->i = d.i;
+  task->j = d.j;
+  task->tiles = d.cols;
+  task->steps = low_precision ? df_task_kend(d.i, d.j) : df_acc_steps(d.i, d.j, nt);
+  task->slot = slot;
+  task->flag = slot < 0 ? -1 : df_part_flag(slot, nt);
   return PD_OK;
 }
 

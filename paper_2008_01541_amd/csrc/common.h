@@ -16,9 +16,9 @@ typedef float float4_t __attribute__((ext_vector_type(4)));
 
 // dense FP64
 void copy_lower_tiles(const double* S, int lds, double* H, int ldh, int n, hipStream_t st);
-// Single-launch dataflow Cholesky; flags: (nt + 3) * nt ints and ticket[2]
+// Single-launch dataflow Cholesky; flags: df_flags(nt) ints and ticket[2]
 // (task counter, launch epoch), all zero-initialised once; each call advances
-// the epoch on the device (safe under graph replay).  sbuf: 2 * nt * NB * NB
+// the epoch on the device (safe under graph replay).  sbuf: df_slots(nt) * NB * NB
 // doubles of workspace (partial sums of the two tiles left of each diagonal).
 // With Yt (64 x n, rows 0..2 = g^T) the forward substitution L^-1 g is fused
 // in (result in the same rows).  A task never waits for work enqueued on

@@ -413,9 +413,8 @@ __device__ inline void stage_tile(double (*T)[LDS_LD], const double* __restrict_
 //    row (Yt: 64 x n, column-major, rows 0..2 = g^T on entry): its tasks
 //    compute Y_j = (G_j - sum_{k<j} Y_k L_jk^T) Linv_jj^T, i.e. the forward
 //    substitution y = L^-1 g, on the same schedule.
-// Flags: nt x nt for the tiles, nt for the right-hand-side row, nt for P1 and
-// nt for P2.  sbuf: nt slots for P1, then nt for P2, in the register order of
-// the task that writes them.
+// Flags and slots of sbuf: df_schedule.h; a partial sum is kept in the register
+// order of the task that writes it.
 template <int WIDE>
 __global__ __launch_bounds__(256, 2) void k_potrf_dataflow(double* A, int lda, int n, int nt,
                                                            double* linv_ws, double* sbuf,
@@ -424,8 +423,7 @@ __global__ __launch_bounds__(256, 2) void k_potrf_dataflow(double* A, int lda, i
   const int epoch = (int)ticket[1];
   const int rhs = Yt != nullptr ? 1 : 0;
   int* const mark = cu_marks ? cu_marks + cu_slot() : nullptr;
-  int* const p1flags = flags + (nt + 1) * nt;
-  int* const p2flags = p1flags + nt;
+  int* const pflags = flags + df_part_flag(0, nt);
   // two 64 x 68 double tiles (69,632 bytes): the operand chunks of the
   // accumulation, then a tile and an operand of the finishing steps
   __shared__ __attribute__((aligned(16))) double buf0[2 * NB][LDS_LD];
@@ -558,11 +556,11 @@ __global__ __launch_bounds__(256, 2) void k_potrf_dataflow(double* A, int lda, i
       if (t == 0 && mark) __hip_atomic_store(mark, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     if (part) {
-      const int slot = i == j + 1 ? i : nt + i;
+      const int slot = df_part_slot(i, j, nt);
       double* Sb = sbuf + (long)slot * NB * NB;
 #pragma unroll
       for (int e = 0; e < 16; ++e) coherent_store(&Sb[e * 256 + t], acc.c[e >> 3][(e >> 2) & 1][e & 3]);
-      publish_flag(&p1flags[slot], epoch);
+      publish_flag(&pflags[slot], epoch);
       __builtin_amdgcn_s_setprio(0);
       continue;
     }
@@ -587,8 +585,8 @@ __global__ __launch_bounds__(256, 2) void k_potrf_dataflow(double* A, int lda, i
             if (!await(&flags[(j - 2) * nt + (j - 2)])) return;
             stage_tile(buf1, linv_ws + (long)(j - 2) * NB * NB, NB);   // buf1[kk][c] = Linv(c, kk)
             if (j > 2) {
-              if (!await(&p1flags[nt + j])) return;
-              subtract_part(v2, nt + j);
+              if (!await(&pflags[df_part_slot(j, j - 2, nt)])) return;
+              subtract_part(v2, df_part_slot(j, j - 2, nt));
             }
             own_to_lds(v2, buf0);
           }
@@ -603,12 +601,12 @@ __global__ __launch_bounds__(256, 2) void k_potrf_dataflow(double* A, int lda, i
           pair_product(acc, buf0, buf0, 0, NB);
           publish_flag(&flags[j * nt + (j - 2)], epoch);
           if (t == 0 && (!df_wait(&flags[(j - 1) * nt + (j - 2)], epoch, err) ||
-                         (j > 2 && !df_wait(&p1flags[j], epoch, err))))
+                         (j > 2 && !df_wait(&pflags[df_part_slot(j, j - 1, nt)], epoch, err))))
             s_ok = 0;
           __syncthreads();
           if (!s_ok) return;
           stage_tile(buf1, A + (long)(j - 1) * NB + (long)(j - 2) * NB * lda, lda);
-          if (j > 2) subtract_part(v, j);
+          if (j > 2) subtract_part(v, df_part_slot(j, j - 1, nt));
           __syncthreads();
           Acc s;                                   // L_{j,j-2} L_{j-1,j-2}^T
           acc_zero(s);

@@ -287,7 +287,7 @@ __global__ __launch_bounds__(256, 2) void k_potrf_dataflow_lp(float* A, int lda,
                                                               int* flags, unsigned* ticket,
                                                               int* info, int* err, int* cu_marks) {
   const int epoch = (int)ticket[1];
-  int* sflags = flags + (nt + 1) * nt;
+  int* sflags = flags + df_part_flag(0, nt);
   int* const mark = cu_marks ? cu_marks + cu_slot() : nullptr;
   // FP64 tile and inverse of the diagonal factor; the float operand tiles of
   // the products live in the same memory

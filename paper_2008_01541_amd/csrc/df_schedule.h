@@ -1,8 +1,9 @@
 // Task schedules of the single-launch dataflow Cholesky: the ticket -> tile
 // mappings (one tile per task in the low-precision kernel, one or two in the FP64
-// kernel) and the accumulation depth of a task.  Host and device: the kernels decode their tickets with it, and the
-// library exports it (pd_dataflow_task) so that the host can check the index
-// ranges of every task against the buffers.
+// kernel), the accumulation depth of a task, and where its flags and partial
+// sums lie.  Host and device: the kernels decode their tickets with it, the
+// workspaces are sized by it, and the library exports it (pd_factor_schedule,
+// pd_dataflow_task) so that the host can check every task against the buffers.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -36,6 +37,16 @@ __host__ __device__ inline int df_acc_steps(int i, int j, int nt) {
   const int steps = i == nt || i > j + 1 ? j : (i == j + 1 ? j - 1 : j - 2);
   return steps > 0 ? steps : 0;
 }
+
+// Partial sums: tile (j + 1, j) in slot j + 1, tile (j + 2, j) in slot nt + j + 2
+// (-1: the task leaves none).  The low-precision kernel has the first kind only.
+// Flags: nt x nt for the tiles, nt for the right-hand-side row's, then one per slot.
+__host__ __device__ constexpr int df_part_slot(int i, int j, int nt) {
+  return i == nt ? -1 : i == j + 1 ? i : i == j + 2 ? nt + i : -1;
+}
+__host__ __device__ constexpr int df_part_flag(int slot, int nt) { return (nt + 1) * nt + slot; }
+__host__ __device__ constexpr int64_t df_slots(int64_t nt) { return 2 * nt; }
+__host__ __device__ constexpr int64_t df_flags(int64_t nt) { return (nt + 1) * nt + df_slots(nt); }
 
 // Tickets of the FP64 kernel.  With wide = 0, those above.  With wide = 1 they
 // go by pairs of tile columns (j0, j0 + 1), j0 even: the diagonal task
