@@ -79,6 +79,14 @@ __device__ inline float panel_load<float>(__amdgpu_buffer_rsrc_t rs, int voff, i
 // per super-row), 82 -> 58 at 2,368, float factor at 4,410 158 -> 103 (backward)
 // and 139 -> 101 (forward).
 //
+// A workgroup fits on a compute unit beside one workgroup of the factorization
+// (208 of the 512 registers of a lane at most and 70 KB of LDS): two waves per
+// SIMD of up to 152 registers each.  With 200 (V in registers from the start, the
+// operands of both tile columns held, the edge masked in every product) a solve
+// beside another handle's factorization of 256 workgroups waited for its end,
+// 13 ms instead of 0.8; alone it takes 372 us here and took 374 (both solves, n =
+// 6,498).
+//
 // With fflags, the factor is still being computed by a dataflow Cholesky
 // launch on another stream (its tile flags and its ticket[2], whose epoch
 // ticket[1] that launch uses): each super-row first waits until the diagonal
@@ -196,9 +204,9 @@ __global__ __launch_bounds__(TT, 2) void k_trsv3(const T* __restrict__ L, int ld
     else m1[lane][ec] = vc[q];                  // m1[c][r] = L_i0+1,i0(r, c) in both
   }
   lds_barrier();
-  // fragments: la = A, lb = B, lv = V (the coupling tile for the head), the
-  // transposes in the backward solve
-  double la[CG], lb[CG], lx[CG];
+  // fragments: la = A, lb = B, the transposes in the backward solve (V, or the
+  // coupling tile for the head, stays in m1 until the products are done)
+  double la[CG], lb[CG];
 #pragma unroll
   for (int c = 0; c < CG; ++c) la[c] = FWD ? m0[c8 + c][r] : m0[r][c8 + c];
   double4_t acc4[2];
@@ -217,8 +225,6 @@ __global__ __launch_bounds__(TT, 2) void k_trsv3(const T* __restrict__ L, int ld
     put64(m1, wv, lane, -1.0, acc4);
     lds_barrier();
   }
-#pragma unroll
-  for (int c = 0; c < CG; ++c) lx[c] = FWD ? m1[c8 + c][r] : m1[r][c8 + c];
   // ---- products with the finished super-rows
   double acc[2][3];
 #pragma unroll
@@ -230,24 +236,18 @@ __global__ __launch_bounds__(TT, 2) void k_trsv3(const T* __restrict__ L, int ld
     const int q = FWD ? p : ns - 1 - p;
     const int col0 = q * SR;
     // both tiles' 16 columns of both tile rows load while the values are awaited
-    // (rows and columns past the edge re-read others and are masked by a
-    // multiply, so that no load is put under a branch)
+    // (a row past the edge re-reads the last one and gives a sum that is not
+    // used; a column past the edge re-reads the last one and meets a zero)
     T lv[2][2][CG];
     const __amdgpu_buffer_rsrc_t prs = panel_rsrc(L, ld, col0, min(SR, n - col0));
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const int ru = row0 + u * NB + r;
-      const bool okr = u < nu && ru < n;
-      const int voff = (okr ? ru : 0) * (int)sizeof(T);
+      const int voff = min(row0 + u * NB + r, n - 1) * (int)sizeof(T);
 #pragma unroll
       for (int w = 0; w < 2; ++w)
 #pragma unroll
-        for (int c = 0; c < CG; ++c) {
-          const int col = w * NB + c8 + c;
-          const bool ok = okr && (FWD || col0 + col < n);
-          lv[u][w][c] = panel_load<T>(prs, voff, min(col, n - 1 - col0) * ld * (int)sizeof(T)) *
-                        (ok ? T(1) : T(0));
-        }
+        for (int c = 0; c < CG; ++c)
+          lv[u][w][c] = panel_load<T>(prs, voff, min(w * NB + c8 + c, n - 1 - col0) * ld * (int)sizeof(T));
     }
     double val = 0.0;
     long spins = 0;
@@ -263,15 +263,26 @@ __global__ __launch_bounds__(TT, 2) void k_trsv3(const T* __restrict__ L, int ld
     // this wave's own columns of ys: only their order within the wave matters
     if (pv < 3) ys[pv][pc] = val;
     __builtin_amdgcn_wave_barrier();
+    // one tile column at a time, so that the values of only one are held
+    // beside the tiles
 #pragma unroll
-    for (int w = 0; w < 2; ++w)
+    for (int w = 0; w < 2; ++w) {
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        double l[CG];
+      for (int v = 0; v < 3; ++v) {
+        double x[CG];
 #pragma unroll
-        for (int c = 0; c < CG; ++c) l[c] = (double)lv[u][w][c];
-        dot8(l, ys, w * NB + c8, acc[u]);
+        for (int c = 0; c < CG; c += 2) {
+          const double2 y2 = *reinterpret_cast<const double2*>(&ys[v][w * NB + c8 + c]);
+          x[c] = y2.x;
+          x[c + 1] = y2.y;
+        }
+#pragma unroll
+        for (int c = 0; c < CG; ++c)
+#pragma unroll
+          for (int u = 0; u < 2; ++u) acc[u][v] += (double)lv[u][w][c] * x[c];
       }
+      __builtin_amdgcn_sched_barrier(0);
+    }
     __builtin_amdgcn_wave_barrier();
   }
   if (bad && lane == 0) {
@@ -285,6 +296,9 @@ __global__ __launch_bounds__(TT, 2) void k_trsv3(const T* __restrict__ L, int ld
   for (int u = 0; u < 2; ++u)
 #pragma unroll
     for (int v = 0; v < 3; ++v) part[wv][v][u * NB + r] = acc[u][v];
+  double lx[CG];                                // V
+#pragma unroll
+  for (int c = 0; c < CG; ++c) lx[c] = FWD ? m1[c8 + c][r] : m1[r][c8 + c];
   auto total = [&]() {
     double y = part[0][rv][rr];
 #pragma unroll
@@ -292,7 +306,7 @@ __global__ __launch_bounds__(TT, 2) void k_trsv3(const T* __restrict__ L, int ld
     return y;
   };
   lds_barrier();
-  if (t < 3 * SR) zs[rv][rr] = b - total();
+  if (t < 3 * SR) zs[rv][rr] = row0 + rr < n ? b - total() : 0.0;
   lds_barrier();
   // ---- D^-1 zs: the head's first tile row (h = 0), then its second, less the
   // coupling; every other super-row in one product
