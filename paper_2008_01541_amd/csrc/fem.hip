@@ -603,11 +603,11 @@ __device__ inline int block_exclusive_scan(int v, int* wsum, int* total) {
 }
 
 // CNT_LDS: the row counters and, if all fit, the keys live in dynamic LDS (m
-// ints, then up to ent_cap ints) instead of cursor[] and ent[].  One workgroup: with
+// ints, then up to ent_cap keys) instead of cursor[] and ent[].  One workgroup: with
 // everything in global memory it is a chain of dependent loads and atomics
 // (92 us for 2,688 level-set penalties of eight slots, 58 us for 2,990 pairs);
 // in LDS, with eight entries of a thread in flight, 38 and 30 us.
-template <bool CNT_LDS>
+template <bool CNT_LDS, typename Key>
 __global__ __launch_bounds__(1024) void k_penalty_prepare(int n_pen, int m, const double* __restrict__ c,
                                                           const int32_t* __restrict__ idx,
                                                           int32_t* __restrict__ act,
@@ -675,24 +675,30 @@ __global__ __launch_bounds__(1024) void k_penalty_prepare(int n_pen, int m, cons
   if (t == 0) rowptr[m] = base;
   __syncthreads();
   // fill, then order each row's keys
-  int32_t* const ent = CNT_LDS && base <= ent_cap ? dyn + m : ent_out;
-  each_slot([&](int e, int r) { ent[cnt_add(r)] = e; });
-  __syncthreads();
-  for (int a = t; a < m; a += 1024) {
-    const int e0 = rowptr[a], e1 = rowptr[a + 1];
-    for (int i = e0 + 1; i < e1; ++i) {
-      const int key = ent[i];
-      int k = i - 1;
-      while (k >= e0 && ent[k] > key) {
-        ent[k + 1] = ent[k];
-        --k;
+  const auto fill = [&](auto* ent) {
+    each_slot([&](int e, int r) { ent[cnt_add(r)] = e; });
+    __syncthreads();
+    for (int a = t; a < m; a += 1024) {
+      const int e0 = rowptr[a], e1 = rowptr[a + 1];
+      for (int i = e0 + 1; i < e1; ++i) {
+        const auto key = ent[i];
+        int k = i - 1;
+        while (k >= e0 && ent[k] > key) {
+          ent[k + 1] = ent[k];
+          --k;
+        }
+        ent[k + 1] = key;
       }
-      ent[k + 1] = key;
     }
+  };
+  if (CNT_LDS && base <= ent_cap) {
+    Key* const ent = reinterpret_cast<Key*>(dyn + m);
+    fill(ent);
+    __syncthreads();
+    for (int e = t; e < base; e += 1024) ent_out[e] = ent[e];
+  } else {
+    fill(ent_out);
   }
-  if (ent == ent_out) return;
-  __syncthreads();
-  for (int e = t; e < base; e += 1024) ent_out[e] = ent[e];
 }
 
 __global__ void k_copy_penalties(int n, const int32_t* __restrict__ idx, const double* __restrict__ w,
@@ -840,17 +846,27 @@ __global__ __launch_bounds__(256) void k_penalty_force(int n_pen, const int32_t*
 
 void penalty_prepare(int n_pen, int m, const double* c, const int32_t* idx, int32_t* act,
                      int32_t* cnt, int32_t* rowptr, int32_t* cursor, int32_t* ent, hipStream_t st) {
-  // the counters in LDS while they fit a third of a compute unit's 160 KB, the
-  // keys beside them as far as 144 KB in all reach (no more than can be there)
-  const int64_t cap = 144 * 1024 / 4;
-  if (m <= cap / 3) {
-    const int ent_cap = (int)std::min<int64_t>(8 * (int64_t)n_pen, cap - m);
-    const size_t bytes = sizeof(int32_t) * (m + (size_t)ent_cap);
-    k_penalty_prepare<true><<<1, 1024, bytes, st>>>(n_pen, m, c, idx, act, cnt, rowptr, cursor, ent,
-                                                    ent_cap);
-  } else {
-    k_penalty_prepare<false><<<1, 1024, 0, st>>>(n_pen, m, c, idx, act, cnt, rowptr, cursor, ent, 0);
+  // The counters in LDS as long as they fit, the keys beside them as far as that
+  // reaches (16 bits each where 8 n_pen values do).  88 KB in all, which a compute
+  // unit has left beside one workgroup of a factorization (70 KB): with 130 KB a
+  // call for 3,249 penalties of 6,498 rows waited for the end of another handle's
+  // factorization of 256 workgroups, 13 ms instead of 50 us.  In global memory /
+  // in LDS, whole call: 12,544 rows and penalties of one slot 119 / 70 us, 20,449
+  // 184 / 104, 2,688 of eight slots and 20,449 rows 153 / 71; of the latter, 46
+  // with the keys in LDS as well (12,100 rows and room for them), 63 without.
+  constexpr int64_t cap = 88 * 1024;
+  const int64_t left = cap - 4 * (int64_t)m;
+  if (left < 0) {
+    k_penalty_prepare<false, int32_t><<<1, 1024, 0, st>>>(n_pen, m, c, idx, act, cnt, rowptr, cursor,
+                                                          ent, 0);
+    return;
   }
+  const bool narrow = 8 * (int64_t)n_pen <= 65536;
+  const int size = narrow ? 2 : 4;
+  const int ent_cap = (int)std::min<int64_t>(8 * (int64_t)n_pen, left / size);
+  const size_t bytes = 4 * (size_t)m + (size_t)size * ent_cap;
+  const auto kernel = narrow ? k_penalty_prepare<true, uint16_t> : k_penalty_prepare<true, int32_t>;
+  kernel<<<1, 1024, bytes, st>>>(n_pen, m, c, idx, act, cnt, rowptr, cursor, ent, ent_cap);
 }
 
 void penalty_apply(int n_pen, const int32_t* act, const int32_t* rowptr, const int32_t* ent,

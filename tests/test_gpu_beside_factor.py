@@ -20,7 +20,9 @@ def factor():
     import ctypes as C
     import torch
     from paper_2008_01541_amd import DenseCholesky
-    st = torch.cuda.Stream()
+    # two streams for the whole module: they may share a hardware queue, which
+    # runs in order, with others created later
+    st, main = torch.cuda.Stream(), torch.cuda.Stream()
     with torch.cuda.stream(st):
         h = DenseCholesky(N)
         a = torch.rand(N, N, dtype=torch.float64, device="cuda") - 0.5
@@ -40,7 +42,7 @@ def factor():
         time.sleep(0.002)                     # the factorization is running
         return e0, e1
 
-    yield run
+    yield run, main
     h.close()
 
 
@@ -56,14 +58,14 @@ def _runner(nx, ny, nz, interior):
     return r
 
 
-def _beside(factor, wg, call, results):
+def _beside(run, wg, call, results):
     """Runs call alone and beside the factorization; the same results twice."""
     import torch
     call()
     torch.cuda.synchronize()
     alone = [t.clone() for t in results]
     torch.cuda.synchronize()
-    f0, f1 = factor(wg)
+    f0, f1 = run(wg)
     c0, c1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     c0.record()
     call()
@@ -79,9 +81,20 @@ def _beside(factor, wg, call, results):
 @pytest.mark.parametrize("grid", [(20, 20, 6), (56, 56, 4)])
 def test_solve(factor, wg, grid):
     import torch
-    main = torch.cuda.Stream()
+    run, main = factor
     with torch.cuda.stream(main):
         r = _runner(*grid, "nd")
         g = torch.linspace(-1.0, 1.0, 3 * r.ctx.m, dtype=torch.float64, device="cuda")
-        _beside(factor, wg, lambda: r.ctx.global_solve(g, r.u), [r.u])
+        _beside(run, wg, lambda: r.ctx.global_solve(g, r.u), [r.u])
+        r.close()
+
+
+@pytest.mark.parametrize("wg", [256, 384])
+def test_collision_update(factor, wg):
+    import torch
+    run, main = factor
+    with torch.cuda.stream(main):
+        r = _runner(56, 56, 4, "nd")
+        _beside(run, wg,
+                lambda: r.ctx.collision_update(r.idx, r.w, r.c, r.t, r.x2, r.fcol), [r.fcol])
         r.close()
