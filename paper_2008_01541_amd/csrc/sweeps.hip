@@ -191,8 +191,8 @@ __global__ void k_sweep_assemble(int w, int nb, const double* __restrict__ Prow,
 // arithmetic returns), each value is one agent-coherent store, and a workgroup
 // of the next level polls the whole vector of the level before it.  Whatever
 // does not depend on that vector is read before it is awaited: the 16 rows of
-// Z_k (registers, all of them: at most 64 values per thread), the right-hand
-// side, and the first four coupling entries of every row.  What is left on the
+// Z_k (in registers; past 1,024 nodes a part of them, see below), the right-hand
+// side, and the first coupling entries of every row.  What is left on the
 // chain is one hand-off, the coupling product (every workgroup forms the whole
 // operand of its level itself: a second hand-off would take longer), and
 // 16 x w products per column.  The full Z_k is read, twice the bytes of the
@@ -203,20 +203,54 @@ __global__ void k_sweep_assemble(int w, int nb, const double* __restrict__ Prow,
 // (from the ticket, so that replays of a captured launch alternate too) and
 // puts the sentinel back into the other.
 //
-// Local step and both sweeps, three launches a level against this kernel: 441
-// nodes a level (20 x 20 x 12 cells) 257 -> 95 us, 841 (x 16) 349 -> 156, 1,369
-// (x 16) 397 -> 241, 1,560 (x 20) 555 -> 362, 2,025 (x 20) 601 -> 485.  Past 1,024
-// nodes the full Z_k bounds it (2.3 TB/s); the gain runs out near 2,400, and
-// at LEVEL_MAX a thread's 64 values of Z_k still fit its registers.
+// A workgroup fits on a compute unit beside one workgroup of a factorization
+// (at most 224 of the 512 registers of a lane, 70 KB of LDS): two waves per SIMD of
+// up to 144 registers each.  Up to 1,024 nodes the rows of Z_k and the coupling
+// read ahead fit in that.  Past it, only the first N1 pairs of columns are read
+// before the wait, those up to N2 into the registers that the awaited values
+// leave, the rest once the operand has left its own.  With all of Z_k held (up to
+// 246 registers) a sweep beside another handle's factorization of 256 workgroups
+// waited for its end, 12 ms instead of 0.2 to 0.6, and one in the two-stream
+// loop until units were empty: a pipelined iteration took 705 us, now 676, at
+// 1,184 nodes, 1,030, now 924, at 1,560 and 1,633, now 1,400, at 2,025.  Alone, both
+// sweeps: 1,184 nodes 170 -> 190 us, 1,560 249 -> 275, 2,025 446 -> 465.  Eight rows a
+// task hold half as much, but read half lines and form the operand twice as
+// often (1,184 nodes: 253 us); the rest of Z_k in LDS (87 KB and more) leaves no
+// room either.
+//
+// Three launches a level against this kernel, both sweeps alone: 928 nodes (16
+// levels) 312 -> 118 us, 1,184 (18) 349 -> 190, 1,369 (16) 332 -> 199, 1,935 (16)
+// 408 -> 361, 2,025 (20) 544 -> 465.  The gain ends near LEVEL_MAX, where the full Z_k
+// bounds it (2.8 TB/s).
 constexpr int LT = 512;                // threads of a workgroup
 constexpr int LB = 16;                 // rows of a task
 
+// Pairs I0 .. I1 - 1 of a thread's columns of its row zp; columns past the last
+// one re-read it: they meet zeros of the operand.
+template <int I0, int I1, int N>
+__device__ __forceinline__ void read_z(double (&z)[N], const double* zp, int ld, int cg, int w) {
+#pragma unroll
+  for (int i = I0; i < I1; ++i)
+    if (64 * i < w) {
+      const int c = 2 * (cg + 32 * i);
+      z[2 * i] = zp[(long)min(c, w - 1) * ld];
+      z[2 * i + 1] = zp[(long)min(c + 1, w - 1) * ld];
+    }
+}
+
 // NP: pairs of columns per thread (thread t holds row t & 15 and the columns
-// 2 (t / 16 + 32 i) + {0, 1}); levels of up to 64 NP nodes.
+// 2 (t / 16 + 32 i) + {0, 1}); levels of up to 64 NP nodes.  LE, N1, N2, N3: as many
+// as 144 registers allow.
 template <int NP, bool FWD>
-__global__ __launch_bounds__(LT, 2) void k_level_sweep(LevelSweep a) {
+__global__ __launch_bounds__(LT, NP > 16 ? 3 : 2) void k_level_sweep(LevelSweep a) {
   constexpr int S = 64 * NP, RPT = (S + LT - 1) / LT;
-  constexpr int LE = NP > 24 ? 2 : 4;   // coupling entries of a row read ahead (registers)
+  constexpr bool WIDE = NP > 16;
+  // coupling entries of a row read ahead
+  constexpr int LE = !WIDE || (FWD && NP <= 24) ? 4 : 2;
+  // pairs read before the wait, by the end of it, and before the product
+  constexpr int N1 = !WIDE ? NP : NP > 24 ? 6 : FWD ? 7 : 15;
+  constexpr int N2 = !WIDE ? NP : NP > 24 ? 13 : FWD ? 14 : 20;
+  constexpr int N3 = NP > 28 ? 26 : NP;
   __shared__ __attribute__((aligned(16))) double xs[3][S];
   __shared__ double red[LT / 64][3][LB];
   __shared__ int s_bad[LT / 64];
@@ -246,16 +280,8 @@ __global__ __launch_bounds__(LT, 2) void k_level_sweep(LevelSweep a) {
   // ---- everything that does not depend on the level before
   double z[2 * NP];
   const int r = t & (LB - 1), cg = t / LB;
-  if (!region) {
-    const double* zp = a.Z + L.mat + r0 + r;           // r0 + r < ld, a multiple of 16
-#pragma unroll
-    for (int i = 0; i < NP; ++i)
-      if (64 * i < w) {
-        const int c = 2 * (cg + 32 * i);
-        // columns past the last one re-read it: they meet zeros of the operand
-        z[2 * i] = zp[(long)min(c, w - 1) * L.ld];
-        z[2 * i + 1] = zp[(long)min(c + 1, w - 1) * L.ld];
-      }
+  if (!region) {                        // r0 + r < ld, a multiple of 16
+    read_z<0, N1>(z, a.Z + L.mat + r0 + r, L.ld, cg, w);
     if (t < 3 * LB && r0 + r < w)
       clear[(long)cg * a.n1 + L.off + r0 + r] = __builtin_bit_cast(double, SENTINEL);
   }
@@ -336,6 +362,7 @@ __global__ __launch_bounds__(LT, 2) void k_level_sweep(LevelSweep a) {
 #pragma unroll
       for (int c = 0; c < 3; ++c)
         if (t + LT * i < S) xs[c][t + LT * i] = pv[i][c];
+    if (N2 > N1 && !region) read_z<N1, N2>(z, a.Z + L.mat + r0 + r, L.ld, cg, w);
     lds_barrier();
     int any = 0;
 #pragma unroll
@@ -347,6 +374,8 @@ __global__ __launch_bounds__(LT, 2) void k_level_sweep(LevelSweep a) {
       }
       return;
     }
+  } else if (N2 > N1 && !region) {
+    read_z<N1, N2>(z, a.Z + L.mat + r0 + r, L.ld, cg, w);
   }
   // ---- operand of this level: f - B v (forward) or B^T x (backward)
   const double* src = polled ? &xs[0][0] : a.in;
@@ -393,6 +422,7 @@ __global__ __launch_bounds__(LT, 2) void k_level_sweep(LevelSweep a) {
     if (t + LT * i < S)
 #pragma unroll
       for (int c = 0; c < 3; ++c) xs[c][t + LT * i] = b[i][c];
+  if (N3 > N2) read_z<N2, N3>(z, a.Z + L.mat + r0 + r, L.ld, cg, w);
   lds_barrier();
   // ---- the 16 rows of Z times the operand
   double s[3] = {0.0, 0.0, 0.0};
@@ -405,6 +435,10 @@ __global__ __launch_bounds__(LT, 2) void k_level_sweep(LevelSweep a) {
         const double2 x2 = *reinterpret_cast<const double2*>(&xs[v][c]);
         s[v] += z[2 * i] * x2.x;
         s[v] += z[2 * i + 1] * x2.y;
+      }
+      if (NP > N3 && i == NP - N3 - 1) {               // into the registers of the first pairs
+        __builtin_amdgcn_sched_barrier(0);
+        read_z<N3, NP>(z, a.Z + L.mat + r0 + r, L.ld, cg, w);
       }
     }
 #pragma unroll
@@ -439,8 +473,12 @@ void launch_level_sweep(const LevelSweep& a, int maxw, hipStream_t st) {
     k_level_sweep<8, FWD><<<g, LT, 0, st>>>(a);
   else if (maxw <= 1024)
     k_level_sweep<16, FWD><<<g, LT, 0, st>>>(a);
+  else if (maxw <= 1280)
+    k_level_sweep<20, FWD><<<g, LT, 0, st>>>(a);
   else if (maxw <= 1536)
     k_level_sweep<24, FWD><<<g, LT, 0, st>>>(a);
+  else if (maxw <= 1792)
+    k_level_sweep<28, FWD><<<g, LT, 0, st>>>(a);
   else
     k_level_sweep<32, FWD><<<g, LT, 0, st>>>(a);
 }

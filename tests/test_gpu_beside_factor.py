@@ -98,3 +98,24 @@ def test_collision_update(factor, wg):
         _beside(run, wg,
                 lambda: r.ctx.collision_update(r.idx, r.w, r.c, r.t, r.x2, r.fcol), [r.fcol])
         r.close()
+
+
+# levels of 441 and 928 nodes, and one width of each instance past 1,024
+@pytest.mark.parametrize("wg", [256, 384])
+@pytest.mark.parametrize("grid", [(20, 20, 6), (31, 28, 6), (33, 33, 6), (38, 38, 6), (40, 41, 6),
+                                  (44, 44, 6)])
+def test_level_sweeps(factor, wg, grid):
+    import torch
+    run, main = factor
+    with torch.cuda.stream(main):
+        r = _runner(*grid, "levels")
+        _beside(run, wg, lambda: r.ctx.condense_rhs(r.f, r.ft), [r.ft])
+        d2 = torch.linspace(-1.0, 1.0, 3 * r.ctx.m, dtype=torch.float64, device="cuda")
+        x = torch.empty_like(r.x)
+
+        def backsub():
+            x.zero_()
+            r.ctx.backsub(d2, x)
+
+        _beside(run, wg, backsub, [x])
+        r.close()
