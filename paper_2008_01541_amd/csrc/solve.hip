@@ -70,9 +70,12 @@ __device__ inline float panel_load<float>(__amdgpu_buffer_rsrc_t rs, int voff, i
 // costs is what counts: the publication (a store and a poll through memory,
 // about 1.5 us), the product with the 128 values awaited, and D^-1.  V makes the
 // latter one product instead of one per tile row with the coupling between
-// them, at the price of two 64^3 products before the first wait; the super-row
-// at the head of the chain, which waits for nothing, goes tile row by tile row
-// instead.  A wave polls just the 16 columns that it multiplies, so the
+// them, at the price of two 64^3 products before the first wait, about 4 us.  The
+// first two super-rows of the chain, whose turn comes before that is done, and
+// all of them in a chain of up to SHORT super-rows go tile row by tile row
+// instead.  Both solves, V in all but the first / in none: n = 162 20.8 / 16.4 us,
+// 264 30.2 / 21.4, 512 35.8 / 30.4, 760 47.1 / 43.8; at 882 (7 super-rows) 52.6 /
+// 50.7, but with the float factor a refined solve of six 222 / 231.  A wave polls just the 16 columns that it multiplies, so the
 // product needs no barrier; 512 threads, since a second wave per SIMD hides
 // the LDS latencies of the first.  Against 256 threads, a poll of the whole
 // workgroup and a product per tile row: 485 -> 350 us at n = 12,155 (5.1 -> 3.7
@@ -98,6 +101,7 @@ __device__ inline float panel_load<float>(__amdgpu_buffer_rsrc_t rs, int voff, i
 constexpr int SR = 2 * NB;               // rows of a super-row
 constexpr int TT = 512;                  // threads; thread t: rows t & 63 of both tiles,
 constexpr int CG = 8;                    // columns 8 (t / 64) .. + 7 of each tile
+constexpr int HEADS = 2, SHORT = 6;
 
 // One wave's two 16 x 16 tiles (row block wv / 2) of the product X Y of two
 // 64 x 64 matrices in LDS, X(r, k) = xm[k][r] and Y(k, c) = ym[c][k].
@@ -136,7 +140,8 @@ __device__ inline void dot8(const double (&l)[CG], const double (*x)[SR], int c0
     }
 }
 
-template <typename T, bool FWD>
+// FOLD: the instance with V, for chains of more than SHORT super-rows.
+template <typename T, bool FWD, bool FOLD>
 __global__ __launch_bounds__(TT, 2) void k_trsv3(const T* __restrict__ L, int ld, int n, int nt,
                                                  const T* __restrict__ linv, const double* rhs,
                                                  int ldr, int rstep, double* out, int ldo,
@@ -162,7 +167,8 @@ __global__ __launch_bounds__(TT, 2) void k_trsv3(const T* __restrict__ L, int ld
   const int sr = __builtin_amdgcn_readfirstlane(s_row);
   const int r = lane, c8 = CG * wv;
   const int i0 = 2 * sr, nu = min(2, nt - i0), row0 = i0 * NB;
-  const bool head = sr == (FWD ? 0 : ns - 1) && nu == 2;
+  const int pos = FWD ? sr : ns - 1 - sr;      // place in the chain
+  const bool head = nu == 2 && (!FOLD || pos < HEADS);
   // right-hand-side value of thread t = 128 v + row (rows past n: 0)
   const int rv = t >> 7, rr = t & 127;
   double b = 0.0;
@@ -179,50 +185,75 @@ __global__ __launch_bounds__(TT, 2) void k_trsv3(const T* __restrict__ L, int ld
     lds_barrier();
     if (s_bad) return;
   }
-  // ---- the tile inverses and the coupling tile; element e = t + 512 q of a tile
-  double va[CG], vb[CG], vc[CG];
-  {
-    const T* La = linv + (long)i0 * NB * NB;
-    const T* Lb = linv + (long)(i0 + nu - 1) * NB * NB;
+  // ---- the tile inverses and the coupling tile: la = A, lb = B (the transposes in
+  // the backward solve), and in m1 V or, for a super-row taken tile row by tile
+  // row, the coupling tile
+  double la[CG], lb[CG];
+  const T* La = linv + (long)i0 * NB * NB;
+  const T* Lb = linv + (long)(i0 + nu - 1) * NB * NB;
+  // m[c][r] = element (r, c) of a tile, from a thread's elements t + 512 q
+  const auto put = [&](double (*m)[NB + 1], const double (&x)[CG]) {
+#pragma unroll
+    for (int q = 0; q < CG; ++q) m[wv + CG * q][lane] = x[q];
+  };
+  if (nu == 2) {
+    // L_i0+1,i0, or its transpose from the upper triangle; what lies past the
+    // edge re-reads the last row or column and is masked
+#pragma unroll
+    for (int q = 0; q < CG; ++q) {
+      const int ec = wv + CG * q;
+      const int lr = row0 + (FWD ? NB : 0) + lane, lc = row0 + (FWD ? 0 : NB) + ec;
+      const double ok = (lr < n && lc < n) ? 1.0 : 0.0;
+      const double v = (double)L[min(lr, n - 1) + (long)min(lc, n - 1) * ld] * ok;
+      if (FWD) m1[ec][lane] = v;
+      else m1[lane][ec] = v;                    // m1[c][r] = L_i0+1,i0(r, c) in both
+    }
+  }
+  if (FOLD && nu == 2 && !head) {
+    double va[CG], vb[CG];
 #pragma unroll
     for (int q = 0; q < CG; ++q) {
       va[q] = La[t + TT * q];
       vb[q] = Lb[t + TT * q];
-      // L_i0+1,i0(e) (forward) or its transpose from the upper triangle; what
-      // lies past the edge re-reads the last row or column and is masked
-      const int er = lane, ec = wv + CG * q;
-      const int lr = row0 + (FWD ? NB : 0) + er, lc = row0 + (FWD ? 0 : NB) + ec;
-      const double ok = (nu == 2 && lr < n && lc < n) ? 1.0 : 0.0;
-      vc[q] = (double)L[min(lr, n - 1) + (long)min(lc, n - 1) * ld] * ok;
     }
-  }
+    double4_t acc4[2];
+    put(m0, va);
+    lds_barrier();
 #pragma unroll
-  for (int q = 0; q < CG; ++q) {
-    const int ec = wv + CG * q;
-    m0[ec][lane] = va[q];
-    if (FWD) m1[ec][lane] = vc[q];
-    else m1[lane][ec] = vc[q];                  // m1[c][r] = L_i0+1,i0(r, c) in both
-  }
-  lds_barrier();
-  // fragments: la = A, lb = B, the transposes in the backward solve (V, or the
-  // coupling tile for the head, stays in m1 until the products are done)
-  double la[CG], lb[CG];
+    for (int c = 0; c < CG; ++c) la[c] = FWD ? m0[c8 + c][r] : m0[r][c8 + c];
+    mul64(m1, m0, wv, lane, acc4);              // P = L_i0+1,i0 A
+    lds_barrier();
+    put(m0, vb);
+    put64(m1, wv, lane, 1.0, acc4);
+    lds_barrier();
 #pragma unroll
-  for (int c = 0; c < CG; ++c) la[c] = FWD ? m0[c8 + c][r] : m0[r][c8 + c];
-  double4_t acc4[2];
-  const bool fold = nu == 2 && !head;
-  if (fold) mul64(m1, m0, wv, lane, acc4);      // P = L_i0+1,i0 A
-  lds_barrier();
-#pragma unroll
-  for (int q = 0; q < CG; ++q) m0[wv + CG * q][lane] = vb[q];
-  if (fold) put64(m1, wv, lane, 1.0, acc4);
-  lds_barrier();
-#pragma unroll
-  for (int c = 0; c < CG; ++c) lb[c] = FWD ? m0[c8 + c][r] : m0[r][c8 + c];
-  if (fold) {
+    for (int c = 0; c < CG; ++c) lb[c] = FWD ? m0[c8 + c][r] : m0[r][c8 + c];
     mul64(m0, m1, wv, lane, acc4);              // V = -B P
     lds_barrier();
     put64(m1, wv, lane, -1.0, acc4);
+    lds_barrier();
+  } else if (FWD) {
+#pragma unroll
+    for (int c = 0; c < CG; ++c) {
+      la[c] = La[r + NB * (c8 + c)];
+      lb[c] = Lb[r + NB * (c8 + c)];
+    }
+  } else {
+    // B, which is needed first, is turned through LDS; A straight from memory
+    // (64 lines a load, behind the first tile row)
+    double vb[CG];
+#pragma unroll
+    for (int q = 0; q < CG; ++q) vb[q] = Lb[t + TT * q];
+    if (nu == 2)
+#pragma unroll
+      for (int c = 0; c < CG; ++c) la[c] = La[c8 + c + NB * r];
+    put(m0, vb);
+    lds_barrier();
+#pragma unroll
+    for (int c = 0; c < CG; ++c) lb[c] = m0[r][c8 + c];
+    if (nu == 1)
+#pragma unroll
+      for (int c = 0; c < CG; ++c) la[c] = lb[c];
     lds_barrier();
   }
   // ---- products with the finished super-rows
@@ -232,7 +263,7 @@ __global__ __launch_bounds__(TT, 2) void k_trsv3(const T* __restrict__ L, int ld
   // this lane's value of the 3 x 16 that the wave polls
   const int pv = lane >> 4, pc = ((lane >> 3) & 1) * NB + c8 + (lane & 7);
   bool bad = false;
-  for (int p = 0; p < (FWD ? sr : ns - 1 - sr) && !bad; ++p) {
+  for (int p = 0; p < pos && !bad; ++p) {
     const int q = FWD ? p : ns - 1 - p;
     const int col0 = q * SR;
     // both tiles' 16 columns of both tile rows load while the values are awaited
@@ -285,99 +316,126 @@ __global__ __launch_bounds__(TT, 2) void k_trsv3(const T* __restrict__ L, int ld
     }
     __builtin_amdgcn_wave_barrier();
   }
-  if (bad && lane == 0) {
-    atomicExch(err, 1);
-    s_bad = 1;
-  }
-  lds_barrier();
-  if (s_bad) return;
-  // ---- zs = right-hand side less the sums
-#pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int v = 0; v < 3; ++v) part[wv][v][u * NB + r] = acc[u][v];
-  double lx[CG];                                // V
-#pragma unroll
-  for (int c = 0; c < CG; ++c) lx[c] = FWD ? m1[c8 + c][r] : m1[r][c8 + c];
   auto total = [&]() {
     double y = part[0][rv][rr];
 #pragma unroll
     for (int q = 1; q < CG; ++q) y += part[q][rv][rr];
     return y;
   };
+  const bool mine = t < 3 * SR && row0 + rr < n;
+  double lx[CG];                                // V, or the coupling tile
+  const auto read_lx = [&]() {
+#pragma unroll
+    for (int c = 0; c < CG; ++c) lx[c] = FWD ? m1[c8 + c][r] : m1[r][c8 + c];
+  };
+  // ---- zs = right-hand side less the sums
+  if (pos > 0) {
+    if (bad && lane == 0) {
+      atomicExch(err, 1);
+      s_bad = 1;
+    }
+    lds_barrier();
+    if (s_bad) return;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int v = 0; v < 3; ++v) part[wv][v][u * NB + r] = acc[u][v];
+    if (nu == 2) read_lx();
+    lds_barrier();
+    if (mine) b -= total();
+  }
+  if (t < 3 * SR) zs[rv][rr] = b;
   lds_barrier();
-  if (t < 3 * SR) zs[rv][rr] = row0 + rr < n ? b - total() : 0.0;
-  lds_barrier();
-  // ---- D^-1 zs: the head's first tile row (h = 0), then its second, less the
-  // coupling; every other super-row in one product
-  const int first = FWD ? 0 : 1;
-  for (int h = 0; h < (head ? 2 : 1); ++h) {
+  // ---- D^-1 zs in one product, or the first tile row (h = 0), then the second,
+  // less the coupling
+  if (nu == 2 && !head) {
     double s[2][3];
 #pragma unroll
     for (int u = 0; u < 2; ++u) s[u][0] = s[u][1] = s[u][2] = 0.0;
     dot8(la, zs, c8, s[0]);
     dot8(lb, zs, NB + c8, s[1]);
-    if (!head) dot8(lx, zs, (FWD ? 0 : NB) + c8, s[1 - first]);
+    dot8(lx, zs, (FWD ? 0 : NB) + c8, s[FWD ? 1 : 0]);
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int v = 0; v < 3; ++v) part[wv][v][u * NB + r] = s[u][v];
     lds_barrier();
-    if (t < 3 * SR) {
+    if (mine) coherent_store(&out[(long)rv * ldo + row0 + rr], total());
+    return;
+  }
+  const auto tile_row = [&](const double (&l)[CG], int h) {
+    double s[3] = {0.0, 0.0, 0.0};
+    dot8(l, zs, h * NB + c8, s);
+#pragma unroll
+    for (int v = 0; v < 3; ++v) part[wv][v][h * NB + r] = s[v];
+    lds_barrier();
+    if (t < 3 * SR && (rr >> 6) == h) {
       const double y = total();
-      const bool mine = !head || (rr >> 6) == (h == 0 ? first : 1 - first);
-      if (mine && row0 + rr < n) coherent_store(&out[(long)rv * ldo + row0 + rr], y);
+      if (mine) coherent_store(&out[(long)rv * ldo + row0 + rr], y);
       ys[rv][rr] = y;
     }
-    if (!head || h == 1) break;
-    lds_barrier();
-    double k[3] = {0.0, 0.0, 0.0};
-    dot8(lx, ys, first * NB + c8, k);
-#pragma unroll
-    for (int v = 0; v < 3; ++v) part[wv][v][(1 - first) * NB + r] = k[v];
-    lds_barrier();
-    if (t < 3 * SR && (rr >> 6) == 1 - first) zs[rv][rr] -= total();
-    lds_barrier();
+  };
+  constexpr int H0 = FWD ? 0 : 1;
+  if (nu == 1) {
+    tile_row(la, 0);
+    return;
   }
+  if (pos == 0) read_lx();
+  tile_row(H0 == 0 ? la : lb, H0);
+  lds_barrier();
+  double k[3] = {0.0, 0.0, 0.0};
+  dot8(lx, ys, H0 * NB + c8, k);
+#pragma unroll
+  for (int v = 0; v < 3; ++v) part[wv][v][(1 - H0) * NB + r] = k[v];
+  lds_barrier();
+  if (t < 3 * SR && (rr >> 6) == 1 - H0) zs[rv][rr] -= total();
+  lds_barrier();
+  tile_row(H0 == 0 ? lb : la, 1 - H0);
+}
+
+template <typename T, bool FWD>
+static void launch_trsv3(const T* L, int ld, int n, const T* linv, const double* rhs, int ldr,
+                         int rstep, double* out, int ldo, unsigned long long* ticket, int* err,
+                         const int* fflags, const unsigned* fticket, double* fill, int ldf,
+                         hipStream_t st) {
+  const int nt = (n + NB - 1) / NB, ns = (nt + 1) / 2;
+  const auto kernel = ns <= SHORT ? k_trsv3<T, FWD, false> : k_trsv3<T, FWD, true>;
+  kernel<<<ns, TT, 0, st>>>(L, ld, n, nt, linv, rhs, ldr, rstep, out, ldo, ticket, err, fflags,
+                            fticket, fill, ldf);
 }
 
 void trsv3_forward(const double* L, int ld, int n, const double* linv_ws, const double* g,
                    int ldg, double* y, int ldy, unsigned long long* ticket, int* err,
                    double* xfill, int ldxf, hipStream_t st, const int* fflags,
                    const unsigned* fticket) {
-  const int nt = (n + NB - 1) / NB, ns = (nt + 1) / 2;
-  k_trsv3<double, true><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, g, ldg, 1, y, ldy, ticket, err,
-                                           fflags, fticket, xfill, ldxf);
+  launch_trsv3<double, true>(L, ld, n, linv_ws, g, ldg, 1, y, ldy, ticket, err, fflags, fticket,
+                             xfill, ldxf, st);
 }
 
 void trsv3_backward(const double* L, int ld, int n, const double* linv_ws, double* y, int ldy,
                     double* x, int ldx, unsigned long long* ticket, int* err, hipStream_t st) {
-  const int nt = (n + NB - 1) / NB, ns = (nt + 1) / 2;
-  k_trsv3<double, false><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, y, ldy, 1, x, ldx, ticket, err,
-                                            nullptr, nullptr, y, ldy);
+  launch_trsv3<double, false>(L, ld, n, linv_ws, y, ldy, 1, x, ldx, ticket, err, nullptr, nullptr,
+                              y, ldy, st);
 }
 
 void trsv3_backward_packed(const double* L, int ld, int n, const double* linv_ws,
                            const double* Yt, double* x, int ldx, unsigned long long* ticket,
                            int* err, hipStream_t st) {
-  const int nt = (n + NB - 1) / NB, ns = (nt + 1) / 2;
-  k_trsv3<double, false><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, Yt, 1, NB, x, ldx, ticket, err,
-                                            nullptr, nullptr, nullptr, 0);
+  launch_trsv3<double, false>(L, ld, n, linv_ws, Yt, 1, NB, x, ldx, ticket, err, nullptr, nullptr,
+                              nullptr, 0, st);
 }
 
 // The same solves with a float factor (FP64 vectors and arithmetic).
 void trsv3_forward(const float* L, int ld, int n, const float* linv_ws, const double* g, int ldg,
                    double* y, int ldy, unsigned long long* ticket, int* err, double* xfill,
                    int ldxf, hipStream_t st) {
-  const int nt = (n + NB - 1) / NB, ns = (nt + 1) / 2;
-  k_trsv3<float, true><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, g, ldg, 1, y, ldy, ticket, err,
-                                          nullptr, nullptr, xfill, ldxf);
+  launch_trsv3<float, true>(L, ld, n, linv_ws, g, ldg, 1, y, ldy, ticket, err, nullptr, nullptr,
+                            xfill, ldxf, st);
 }
 void trsv3_backward(const float* L, int ld, int n, const float* linv_ws, double* y, int ldy,
                     double* x, int ldx, unsigned long long* ticket, int* err, hipStream_t st) {
-  const int nt = (n + NB - 1) / NB, ns = (nt + 1) / 2;
-  k_trsv3<float, false><<<ns, TT, 0, st>>>(L, ld, n, nt, linv_ws, y, ldy, 1, x, ldx, ticket, err,
-                                           nullptr, nullptr, y, ldy);
+  launch_trsv3<float, false>(L, ld, n, linv_ws, y, ldy, 1, x, ldx, ticket, err, nullptr, nullptr,
+                             y, ldy, st);
 }
 
 }  // namespace pdk
