@@ -153,40 +153,47 @@ __device__ int wave_locate(const double p[3], int nc, const int32_t* __restrict_
         if (p[d] < o[(long)d * nb] || p[d] > o[(long)(3 + d) * nb]) maybe = false;
     }
     unsigned long long todo = __ballot(maybe);
-    while (todo) {
-      const int base = 64 * (b0 + __ffsll((long long)todo) - 1);
+    // the next batch's nodes load while this one's positions are awaited
+    int base = 0, v[4], bd = 0;
+    const auto next = [&]() {
+      base = todo ? 64 * (b0 + __ffsll((long long)todo) - 1) : -1;
       todo &= todo - 1;
-      const int e = base + lane;
+      if (base < 0) return;
+      const int e = min(base + lane, nc - 1);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = cand[q * nc + e];
+      if (mode != 0) bd = body[e];
+    };
+    next();
+    while (base >= 0) {
+      const int first = base;
       bool hit = false;
       double l[4] = {0.0, 0.0, 0.0, 0.0};
-      if (e < nc) {
-        const int v0 = cand[e], v1 = cand[nc + e], v2 = cand[2 * nc + e], v3 = cand[3 * nc + e];
-        bool ok = v0 >= 0 && v0 < m && v1 >= 0 && v1 < m && v2 >= 0 && v2 < m && v3 >= 0 && v3 < m;
-        if (ok && mode != 0) {
-          const int bd = body[e];
-          ok = (mode == 1) ? (bd == want_body) : (bd != want_body);
-        }
-        if (ok && excl[0] >= 0) {
+      bool ok = first + lane < nc;
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            ok = ok && v0 != excl[q] && v1 != excl[q] && v2 != excl[q] && v3 != excl[q];
-        }
-        if (ok) {
-          double a[3], b[3], c[3], d[3];
-          load3(pos, m, v0, a);
-          load3(pos, m, v1, b);
-          load3(pos, m, v2, c);
-          load3(pos, m, v3, d);
-          bary(p, a, b, c, d, l);
-          hit = l[0] >= -BARY_TOL && l[1] >= -BARY_TOL && l[2] >= -BARY_TOL && l[3] >= -BARY_TOL;
-        }
+      for (int q = 0; q < 4; ++q) ok = ok && v[q] >= 0 && v[q] < m;
+      if (mode != 0) ok = ok && ((mode == 1) == (bd == want_body));
+      if (excl[0] >= 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) ok = ok && v[u] != excl[q];
+      }
+      const int w[4] = {v[0], v[1], v[2], v[3]};
+      next();
+      if (ok) {
+        double x[4][3];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) load3(pos, m, w[q], x[q]);
+        bary(p, x[0], x[1], x[2], x[3], l);
+        hit = l[0] >= -BARY_TOL && l[1] >= -BARY_TOL && l[2] >= -BARY_TOL && l[3] >= -BARY_TOL;
       }
       const unsigned long long mask = __ballot(hit);
       if (mask) {
         const int src = __ffsll((long long)mask) - 1;
 #pragma unroll
         for (int q = 0; q < 4; ++q) l_out[q] = __shfl(l[q], src, 64);
-        return base + src;
+        return first + src;
       }
     }
   }
@@ -430,11 +437,13 @@ void detect_embedded_spheres(int n_prox, const int32_t* eidx, const double* ew, 
 }
 
 // With box (12 doubles per batch of 64 candidates) the batches' boxes are formed
-// first.  2,688 proxies against 16,128 candidates: 504 -> 33 us for the
+// first.  2,688 proxies against 16,128 candidates: 504 -> 29 us for the
 // detection (boxes included), bound by the latency of a few dependent batches
-// per proxy; the linear scan tested 190 of 252 batches on average.  Below
-// BOX_MIN candidates the scan is as short as the extra launch.
-constexpr int BOX_MIN = 512;
+// per proxy; the linear scan tested 190 of 252 batches on average.  Candidates in
+// no spatial order, which no box separates: 905 -> 855 us.  The boxes take 6 us,
+// so that the scan is as short below about BOX_MIN candidates (one proxy, shuffled
+// candidates, with them and without: 700 20 / 14 us, 1,500 30 / 29).
+constexpr int BOX_MIN = 1024;
 void detect_levelset(int n_prox, const int32_t* eidx, const double* ew, const int32_t* prox_body,
                      int nc, const int32_t* cand, const double* cand_phi,
                      const int32_t* cand_body, const double* rest2, double k, const double* x2,
