@@ -41,7 +41,6 @@ void rhs_pack(int n, const double* g, int ldg, double* Yt, double* fill, int* in
 void zero_int(int* p, hipStream_t st);
 void zero_f64(long n, double* p, hipStream_t st);
 void copy_f64(long n, const double* src, double* dst, hipStream_t st);
-void copy_i32(long n, const int32_t* src, int32_t* dst, hipStream_t st);
 void trtri_from_factor(const double* L, int ldl, int n, const double* linv_ws, double* M,
                        double* X, int ldx, hipStream_t st);
 void lauum_full(const double* X, int ldx, int n, double* Z, int ldz, hipStream_t st);
@@ -73,8 +72,9 @@ void trsv3_backward(const float* L, int ld, int n, const float* linv_ws, double*
 void symv3(const double* A, int lda, int n, const double* v, int ldv, double alpha,
            double beta, double* y, int ldy, hipStream_t st);
 
-// low precision (FP32 / BF16-operand) factor of the equilibrated system, on
-// the schedule of potrf_dataflow (same flags layout; sbuf: nt * NB * NB floats)
+// low precision (FP32 / BF16-operand) factor of the equilibrated system: the
+// tasks of df_schedule.h with one tile each and one partial sum per column
+// (df_flags(nt) flags; sbuf: nt * NB * NB floats)
 void potrf_dataflow_lp(float* A, int lda, int n, float* linv_ws, float* sbuf, int* flags,
                        unsigned* ticket, int* info, int* err, int n_wg, bool bf16, hipStream_t st,
                        int* cu_marks = nullptr);
