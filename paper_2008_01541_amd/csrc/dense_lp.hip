@@ -15,7 +15,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 constexpr int LP_LD = NB + 4;     // FP32 LDS row (floats)
 constexpr int KC32 = 32;          // K chunk of the staged products
-constexpr int BF_LD = KC32 + 8;   // BF16 LDS row (k contiguous, 16-byte aligned rows)
 
 struct AccF {
   float4_t c[2][2];
@@ -36,68 +35,6 @@ __device__ inline int accf_row(int mb) {
 __device__ inline int accf_col(int nb, int q) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   return (w & 1) * 32 + nb * 16 + 4 * (lane >> 4) + q;
-}
-
-// ---- FP32-operand product: acc += Ahat Bhat^T, Ahat/Bhat read as tiles of a
-// column-major FP32 matrix (rows r0.., cols k0..), K = 64 (one tile).
-__device__ void gemm_f32_tile(AccF& acc, float (*As)[LP_LD], float (*Bs)[LP_LD],
-                              const float* __restrict__ A, long lda, int ar0, int amr,
-                              const float* __restrict__ B, long ldb, int br0, int bmr, int k0) {
-  const int t = threadIdx.x;
-  const int lane = t & 63, w = t >> 6;
-  const int wr = w >> 1, wc = w & 1;
-  for (int kk = 0; kk < NB; kk += KC32) {
-    __syncthreads();
-    const int r = t & 63;
-#pragma unroll
-    for (int q = 0; q < KC32 / 4; ++q) {
-      const int k = (t >> 6) + 4 * q;
-      As[k][r] = (r < amr) ? A[(long)(ar0 + r) + (long)(k0 + kk + k) * lda] : 0.f;
-      Bs[k][r] = (r < bmr) ? B[(long)(br0 + r) + (long)(k0 + kk + k) * ldb] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < KC32 / 4; ++ks) {
-      const int k = ks * 4 + (lane >> 4);
-      const float a0 = As[k][wr * 32 + (lane & 15)];
-      const float a1 = As[k][wr * 32 + 16 + (lane & 15)];
-      const float b0 = Bs[k][wc * 32 + (lane & 15)];
-      const float b1 = Bs[k][wc * 32 + 16 + (lane & 15)];
-      acc.c[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(b0, a0, acc.c[0][0], 0, 0, 0);
-      acc.c[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(b1, a0, acc.c[0][1], 0, 0, 0);
-      acc.c[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(b0, a1, acc.c[1][0], 0, 0, 0);
-      acc.c[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(b1, a1, acc.c[1][1], 0, 0, 0);
-    }
-  }
-}
-
-// ---- BF16-operand product (FP32 accumulation), same contract.
-__device__ void gemm_bf16_tile(AccF& acc, __bf16 (*As)[BF_LD], __bf16 (*Bs)[BF_LD],
-                               const float* __restrict__ A, long lda, int ar0, int amr,
-                               const float* __restrict__ B, long ldb, int br0, int bmr, int k0) {
-  const int t = threadIdx.x;
-  const int lane = t & 63, w = t >> 6;
-  const int wr = w >> 1, wc = w & 1;
-  for (int kk = 0; kk < NB; kk += KC32) {
-    __syncthreads();
-    const int r = t & 63;
-#pragma unroll
-    for (int q = 0; q < KC32 / 4; ++q) {
-      const int k = (t >> 6) + 4 * q;
-      As[r][k] = (__bf16)((r < amr) ? A[(long)(ar0 + r) + (long)(k0 + kk + k) * lda] : 0.f);
-      Bs[r][k] = (__bf16)((r < bmr) ? B[(long)(br0 + r) + (long)(k0 + kk + k) * ldb] : 0.f);
-    }
-    __syncthreads();
-    const int ko = 8 * (lane >> 4);
-    const bf16x8_t a0 = *(const bf16x8_t*)&As[wr * 32 + (lane & 15)][ko];
-    const bf16x8_t a1 = *(const bf16x8_t*)&As[wr * 32 + 16 + (lane & 15)][ko];
-    const bf16x8_t b0 = *(const bf16x8_t*)&Bs[wc * 32 + (lane & 15)][ko];
-    const bf16x8_t b1 = *(const bf16x8_t*)&Bs[wc * 32 + 16 + (lane & 15)][ko];
-    acc.c[0][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b0, a0, acc.c[0][0], 0, 0, 0);
-    acc.c[0][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b1, a0, acc.c[0][1], 0, 0, 0);
-    acc.c[1][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b0, a1, acc.c[1][0], 0, 0, 0);
-    acc.c[1][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b1, a1, acc.c[1][1], 0, 0, 0);
-  }
 }
 
 constexpr long LP_SPIN_LIMIT = 1L << 24;
