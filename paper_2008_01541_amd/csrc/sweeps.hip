@@ -206,24 +206,38 @@ __global__ void k_sweep_assemble(int w, int nb, const double* __restrict__ Prow,
 // A workgroup fits on a compute unit beside one workgroup of a factorization
 // (at most 224 of the 512 registers of a lane, 70 KB of LDS): two waves per SIMD of
 // up to 144 registers each.  Up to 1,024 nodes the rows of Z_k and the coupling
-// read ahead fit in that.  Past it, only the first N1 pairs of columns are read
-// before the wait, those up to N2 into the registers that the awaited values
-// leave, the rest once the operand has left its own.  With all of Z_k held (up to
-// 246 registers) a sweep beside another handle's factorization of 256 workgroups
+// read ahead fit in that.  Past it, only the first pairs of columns are read
+// before the wait, more into the registers that the awaited values leave, the
+// rest once the operand has left its own (read_ahead), and up to 1,792 nodes a
+// part of the coupling entries goes to LDS.  With all of Z_k held (up to 246
+// registers) a sweep beside another handle's factorization of 256 workgroups
 // waited for its end, 12 ms instead of 0.2 to 0.6, and one in the two-stream
-// loop until units were empty: a pipelined iteration took 705 us, now 676, at
-// 1,184 nodes, 1,030, now 924, at 1,560 and 1,633, now 1,400, at 2,025.  Alone, both
-// sweeps: 1,184 nodes 170 -> 190 us, 1,560 249 -> 275, 2,025 446 -> 465.  Eight rows a
-// task hold half as much, but read half lines and form the operand twice as
-// often (1,184 nodes: 253 us); the rest of Z_k in LDS (87 KB and more) leaves no
-// room either.
+// loop until units were empty: a pipelined iteration took 705 us, now 692, at
+// 1,184 nodes, 1,030, now 934, at 1,560 and 1,633, now 1,400, at 2,025.  Alone, both
+// sweeps: 1,184 nodes 170 -> 176 us, 1,369 183 -> 185, 1,521 305 -> 291, 1,560
+// 248 -> 257, 2,025 446 -> 466.  Eight rows a task hold half as much, but read half
+// lines and form the operand twice as often (1,184 nodes: 253 us); the rest of
+// Z_k in LDS (87 KB and more in all) leaves no room either.
 //
 // Three launches a level against this kernel, both sweeps alone: 928 nodes (16
-// levels) 312 -> 118 us, 1,184 (18) 349 -> 190, 1,369 (16) 332 -> 199, 1,935 (16)
-// 408 -> 361, 2,025 (20) 544 -> 465.  The gain ends near LEVEL_MAX, where the full Z_k
+// levels) 312 -> 118 us, 1,184 (18) 349 -> 176, 1,369 (16) 332 -> 185, 1,935 (16)
+// 408 -> 360, 2,025 (20) 544 -> 466.  The gain ends near LEVEL_MAX, where the full Z_k
 // bounds it (2.8 TB/s).
 constexpr int LT = 512;                // threads of a workgroup
 constexpr int LB = 16;                 // rows of a task
+
+// What an instance reads before the wait, as far as 144 registers and 72 KB of LDS
+// reach: the first coupling entries of a row (le in registers, ls in LDS) and n1
+// pairs of columns; n2 by the end of the wait, n3 before the product.
+struct Ahead {
+  int le, ls, n1, n2, n3;
+};
+constexpr Ahead read_ahead(int np, bool fwd) {
+  return np <= 16   ? Ahead{4, 0, np, np, np}
+         : np <= 24 ? (fwd ? Ahead{2, 2, 12, 18, np} : Ahead{2, 2, 14, 20, np})
+         : np <= 28 ? (fwd ? Ahead{3, 1, 2, 10, np} : Ahead{3, 1, 4, 12, np})
+                    : Ahead{2, 0, 6, 13, 26};
+}
 
 // Pairs I0 .. I1 - 1 of a thread's columns of its row zp; columns past the last
 // one re-read it: they meet zeros of the operand.
@@ -239,20 +253,16 @@ __device__ __forceinline__ void read_z(double (&z)[N], const double* zp, int ld,
 }
 
 // NP: pairs of columns per thread (thread t holds row t & 15 and the columns
-// 2 (t / 16 + 32 i) + {0, 1}); levels of up to 64 NP nodes.  LE, N1, N2, N3: as many
-// as 144 registers allow.
+// 2 (t / 16 + 32 i) + {0, 1}); levels of up to 64 NP nodes.
 template <int NP, bool FWD>
 __global__ __launch_bounds__(LT, NP > 16 ? 3 : 2) void k_level_sweep(LevelSweep a) {
   constexpr int S = 64 * NP, RPT = (S + LT - 1) / LT;
-  constexpr bool WIDE = NP > 16;
-  // coupling entries of a row read ahead
-  constexpr int LE = !WIDE || (FWD && NP <= 24) ? 4 : 2;
-  // pairs read before the wait, by the end of it, and before the product
-  constexpr int N1 = !WIDE ? NP : NP > 24 ? 6 : FWD ? 7 : 15;
-  constexpr int N2 = !WIDE ? NP : NP > 24 ? 13 : FWD ? 14 : 20;
-  constexpr int N3 = NP > 28 ? 26 : NP;
+  constexpr Ahead A = read_ahead(NP, FWD);
+  constexpr int LE = A.le, LS = A.ls, N1 = A.n1, N2 = A.n2, N3 = A.n3;
   __shared__ __attribute__((aligned(16))) double xs[3][S];
   __shared__ double red[LT / 64][3][LB];
+  __shared__ double lv[LS > 0 ? LS : 1][LS > 0 ? S : 1];             // a thread's own rows
+  __shared__ unsigned short lc[LS > 0 ? LS : 1][LS > 0 ? S : 1];
   __shared__ int s_bad[LT / 64];
   __shared__ unsigned long long s_tk;
   const int t = threadIdx.x, wv = t >> 6;
@@ -315,6 +325,17 @@ __global__ __launch_bounds__(LT, NP > 16 ? 3 : 2) void k_level_sweep(LevelSweep 
         cc[i][j] = a.col[L.nnz + es[i] + j];
       }
     }
+  if constexpr (LS > 0) {
+#pragma unroll
+    for (int i = 0; i < RPT; ++i)
+#pragma unroll
+      for (int j = 0; j < LS; ++j)
+        if (t + LT * i < S) {
+          const bool on = es[i] + LE + j < ee[i];
+          lv[j][t + LT * i] = on ? a.val[L.nnz + es[i] + LE + j] : 0.0;
+          lc[j][t + LT * i] = on ? (unsigned short)a.col[L.nnz + es[i] + LE + j] : 0;
+        }
+  }
   double vown = 0.0;
   if (!FWD && a.v && t < 3 * LB && r0 + r < w) vown = a.v[(long)cg * a.n1 + L.off + r0 + r];
   // ---- the level before: nothing (first of a forward sweep), the caller's
@@ -390,7 +411,19 @@ __global__ __launch_bounds__(LT, NP > 16 ? 3 : 2) void k_level_sweep(LevelSweep 
         s1 += cv[i][j] * xs[1][cc[i][j]];
         s2 += cv[i][j] * xs[2][cc[i][j]];
       }
-      for (int e = es[i] + LE; e < ee[i]; ++e) {
+      if constexpr (LS > 0) {
+        if (t + LT * i < S) {
+#pragma unroll
+          for (int j = 0; j < LS; ++j) {
+            const double v = lv[j][t + LT * i];
+            const int c = lc[j][t + LT * i];
+            s0 += v * xs[0][c];
+            s1 += v * xs[1][c];
+            s2 += v * xs[2][c];
+          }
+        }
+      }
+      for (int e = es[i] + LE + LS; e < ee[i]; ++e) {
         const double v = a.val[L.nnz + e];
         const int c = a.col[L.nnz + e];
         s0 += v * xs[0][c];
