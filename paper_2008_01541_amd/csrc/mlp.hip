@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(int M, int N, int K, const fl
 // output's sum goes over chunks of MKC, splits in order, as the gradients' in
 // k_gemm_bf16.  Network 25,992-512-512-19,494, forward / training step in us,
 // 64 x 64 tiles staged through LDS (the kernel before) -> these: batch 1 117 -> 32
-// / 449 -> 187, 32 131 -> 54 / 512 -> 269, 64 156 -> 80 / 570 -> 357, 128 215 -> 132 /
+// / 449 -> 187, 32 131 -> 54 / 512 -> 269, 64 156 -> 82 / 570 -> 352, 128 215 -> 132 /
 // 761 -> 537, 1,024 1,378 -> 808 / 4,042 -> 3,200; so all batches take them.
 
 typedef float float4u_t __attribute__((ext_vector_type(4), aligned(4)));
@@ -166,14 +166,23 @@ __device__ __forceinline__ void rows_times_weights(float4_t (&acc)[MB], int M, i
   }
 }
 
-// Block of outputs (of nb) and first row of a workgroup: the blocks of rows lie
-// behind one another in the grid's x, since y and z are bounded (65,535 blocks
-// of 32 rows, 2,097,120 rows).
+// Block of outputs (of nb) and first row of a workgroup.  The blocks of rows lie
+// in the grid's z, what passes its bound (ZMAX blocks of 32 rows, 2,097,120 rows)
+// behind the blocks of outputs in x.  All of them in x: the division at the start
+// costs a small network's forward pass 1.5 % (22.9 us), and at batch 33 the order of
+// the blocks 7 % (25,992-512-512-19,494: 68.6 us).
+constexpr int ZMAX = 65535;
 template <int MB>
-__device__ __forceinline__ void rows_block(int nb, int& nblk, int& m0) {
-  const int mb = blockIdx.x / nb;
-  nblk = blockIdx.x - mb * nb;
-  m0 = mb * 16 * MB;
+__device__ __forceinline__ bool rows_block(int M, int nb, int& nblk, int& m0) {
+  const int q = (M - 1) / (16 * MB) >= ZMAX ? blockIdx.x / nb : 0;
+  nblk = blockIdx.x - q * nb;
+  const long first = ((long)q * ZMAX + blockIdx.z) * 16 * MB;
+  m0 = (int)first;
+  return first < M;                     // false: past the last row
+}
+static dim3 rows_grid(int nb, int nz, int M) {
+  const unsigned gm = (unsigned)((M + 31) / 32);
+  return dim3((unsigned)nb * ((gm + ZMAX - 1) / ZMAX), (unsigned)nz, gm < ZMAX ? gm : ZMAX);
 }
 
 // part[z][m][n] = sum over the k of split z; four waves of 16 n each
@@ -184,7 +193,7 @@ __global__ __launch_bounds__(256) void k_rows_part(int M, int N, int K, int ks,
                                                    float* __restrict__ part) {
   const int lane = threadIdx.x & 63;
   int nblk, m0;
-  rows_block<MB>((N + 63) / 64, nblk, m0);
+  if (!rows_block<MB>(M, (N + 63) / 64, nblk, m0)) return;
   const int n0 = nblk * 64 + 16 * (threadIdx.x >> 6), z = blockIdx.y;
   if (n0 >= N) return;
   float4_t acc[MB];
@@ -209,7 +218,7 @@ __global__ __launch_bounds__(256) void k_rows_full(int M, int N, int K, int ks, 
   __shared__ float4_t red[4][MB][64];
   const int lane = threadIdx.x & 63, z = threadIdx.x >> 6, nz = blockDim.x >> 6;
   int nblk, m0;
-  rows_block<MB>((N + 15) / 16, nblk, m0);
+  if (!rows_block<MB>(M, (N + 15) / 16, nblk, m0)) return;
   const int n0 = nblk * 16;
   float4_t acc[MB];
   rows_times_weights<MB>(acc, M, N, K, m0, n0, z * ks, min(K, (z + 1) * ks), X, W);
@@ -245,7 +254,7 @@ __global__ __launch_bounds__(256) void k_cols_part(int M, int N, int K, int ks,
   __shared__ __attribute__((aligned(16))) __bf16 Ws[2][64][MLD];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, ko = 8 * (lane >> 4);
   int nblk, m0;
-  rows_block<MB>((N + 63) / 64, nblk, m0);
+  if (!rows_block<MB>(M, (N + 63) / 64, nblk, m0)) return;
   const int n0 = nblk * 64, z = blockIdx.y;
   const int kbeg = z * ks, kend = min(K, kbeg + ks);
   const int kr = t >> 3, nc = n0 + 8 * (t & 7);        // this thread's weights of a chunk
@@ -337,14 +346,13 @@ void mlp_rows(int M, int N, int K, const float* X, const __bf16* W, const float*
               float* part, int nsplit, float* out, hipStream_t st) {
   const int ks = ((K + nsplit - 1) / nsplit + MKC - 1) / MKC * MKC;
   const int nz = (K + ks - 1) / ks;
-  const unsigned gm = (unsigned)((M + 31) / 32);
   if (nz <= 4) {
-    const dim3 g((unsigned)((N + 15) / 16) * gm);
+    const dim3 g = rows_grid((N + 15) / 16, 1, M);
     if (M <= 16) k_rows_full<1><<<g, 64 * nz, 0, st>>>(M, N, K, ks, relu, X, W, bias, out);
     else k_rows_full<2><<<g, 64 * nz, 0, st>>>(M, N, K, ks, relu, X, W, bias, out);
     return;
   }
-  const dim3 g((unsigned)((N + 63) / 64) * gm, (unsigned)nz);
+  const dim3 g = rows_grid((N + 63) / 64, nz, M);
   if (M <= 16) k_rows_part<1><<<g, 256, 0, st>>>(M, N, K, ks, X, W, part);
   else k_rows_part<2><<<g, 256, 0, st>>>(M, N, K, ks, X, W, part);
   mlp_split_reduce(M, N, nz, part, bias, relu, nullptr, out, st);
@@ -355,7 +363,7 @@ void mlp_cols(int M, int N, int K, const float* X, const __bf16* W, const float*
               int nsplit, float* out, hipStream_t st) {
   const int ks = ((K + nsplit - 1) / nsplit + MKC - 1) / MKC * MKC;
   const int nz = (K + ks - 1) / ks;
-  const dim3 g((unsigned)((N + 63) / 64) * (unsigned)((M + 31) / 32), (unsigned)nz);
+  const dim3 g = rows_grid((N + 63) / 64, nz, M);
   if (M <= 16) k_cols_part<1><<<g, 256, 0, st>>>(M, N, K, ks, X, W, part);
   else k_cols_part<2><<<g, 256, 0, st>>>(M, N, K, ks, X, W, part);
   mlp_split_reduce(M, N, nz, part, nullptr, 0, H, out, st);
