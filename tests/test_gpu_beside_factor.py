@@ -59,22 +59,27 @@ def _runner(nx, ny, nz, interior):
 
 
 def _beside(run, wg, call, results):
-    """Runs call alone and beside the factorization; the same results twice."""
+    """Runs call alone and beside the factorization; the same results twice.  A
+    call that waits for the factorization does so every time; one that ran late
+    because the host was held up is tried again."""
     import torch
     call()
     torch.cuda.synchronize()
     alone = [t.clone() for t in results]
     torch.cuda.synchronize()
-    f0, f1 = run(wg)
-    c0, c1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    c0.record()
-    call()
-    c1.record()
-    torch.cuda.synchronize()
-    for t, s in zip(results, alone):
-        assert torch.equal(t, s)
-    begun, done, total = f0.elapsed_time(c0), f0.elapsed_time(c1), f0.elapsed_time(f1)
-    assert 0 < begun < done < 0.5 * total, "the call waited for the factorization"
+    for _ in range(3):
+        f0, f1 = run(wg)
+        c0, c1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        c0.record()
+        call()
+        c1.record()
+        torch.cuda.synchronize()
+        for t, s in zip(results, alone):
+            assert torch.equal(t, s)
+        begun, done, total = f0.elapsed_time(c0), f0.elapsed_time(c1), f0.elapsed_time(f1)
+        if 0 < begun < done < 0.5 * total:
+            return
+    assert False, "the call waited for the factorization"
 
 
 @pytest.mark.parametrize("wg", [256, 384])
